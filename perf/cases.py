@@ -1,0 +1,490 @@
+"""Timed cases of the search, one call a user's program makes per case.
+
+Sizes are those of the seeded workloads (``synth``): one chip of 2048 x 4096
+px is voted with a grid of 4e2 to 1.2e6 trial velocities, a night holds many
+chips of 5e4 to 5e5 detections, candidates are extracted, refined and vetted.
+A case is a dict of plain values:
+
+  kind "vote"      one catalog: Search.vote and Search.peaks
+  kind "batch"     a night's chips: Batch.vote and Batch.peaks of each
+  kind "extract"   Step 3 over the candidates of a vote (Search.extract)
+  kind "refine"    Steps 4-6 over the extracted clusters (Search.refine)
+  kind "features"  features of a pool of candidates (Search.features)
+  kind "train"     training steps of the vetting network, then its weights
+  kind "score"     logits of a pool of candidates
+
+Everything a program prepares once (plan, buffers, catalog in device memory)
+is made by prepare() from the case and the seed.
+"""
+from __future__ import annotations
+
+import math
+
+import numpy as np
+import torch
+
+from paper_2509_26279_amd import autotune, sas, synth
+
+FIELDS = ("v_idx", "bx", "by", "count", "flags")
+CAND_CAP = 1 << 16  # candidates a program keeps room for, per catalog
+
+
+def listed():
+    return [
+        # the smallest search: 512 x 512 px, 20 epochs, 441 velocities; one call's latency
+        {"name": "tiny vote", "kind": "vote", "style": "tiny"},
+        # slow movers in one chip: 3.0e5 detections, 8.4e4 velocities, 100 epochs, 4 px bins
+        {"name": "wide vote", "kind": "vote", "style": "wide", "epochs": 100, "noise": 3000},
+        # fast movers in one chip: 1.8e5 detections, 1.2e6 velocities, 60 epochs, 16 px bins
+        {"name": "fast vote", "kind": "vote", "style": "fast", "epochs": 60, "noise": 3000},
+        # detections counted instead of epochs, the 1000 highest stacks asked for
+        {"name": "faint detections vote", "kind": "vote", "style": "faint", "epochs": 57,
+         "noise": 3011, "mode": "detections", "order": "by_count", "top_k": 1000},
+        # likelihood weights in place of the indicator
+        {"name": "faint weighted vote", "kind": "vote", "style": "faint", "epochs": 60,
+         "noise": 3000, "mode": "weighted_epochs"},
+        # the sort path: a block of the fast grid (footprints the dense tiles do not fit)
+        {"name": "sort path vote", "kind": "vote", "style": "fast", "epochs": 60, "noise": 3000,
+         "path": "sort", "v_block": 512},
+        # the first chips of the night, both styles, one launch per kernel class
+        {"name": "night batch", "kind": "batch", "chips": 5, "first": 0},
+        # Step 3 over the stacks of a wide chip
+        {"name": "wide extract", "kind": "extract", "style": "wide", "epochs": 100,
+         "noise": 3000},
+        # Steps 4-6 over the clusters of a fast chip, 500 starts per fit
+        {"name": "fast refine", "kind": "refine", "style": "fast", "epochs": 60, "noise": 3000,
+         "starts": 500},
+        # the pool of a wide-style chip at a low threshold, noise dominated
+        {"name": "wide pool features", "kind": "features", "style": "wide", "epochs": 100,
+         "noise": 3000, "half_height": 110, "n_pool": 8, "pool": 200000},
+        # one training batch after another, and the weights they lead to
+        {"name": "train steps", "kind": "train", "batch": 4096, "steps": 8},
+        # scoring that pool with one network
+        {"name": "score pool", "kind": "score", "rows": 230453, "batch": 4096},
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.choice(["vote", "vote", "vote", "batch", "extract", "refine", "features",
+                       "train", "score"])
+    if kind == "train":
+        return {"kind": kind, "batch": _log_int(rng, 64, 8192), "steps": rng.randint(1, 8)}
+    if kind == "score":
+        return {"kind": kind, "rows": _log_int(rng, 100, 230000),
+                "batch": rng.choice([1024, 4096, 16384])}
+    if kind == "batch":
+        c = {"kind": kind, "chips": rng.randint(1, 5), "first": rng.randint(5, 58)}
+        while c["chips"] > 1 and work(c)["flops"] > 3.0e12:
+            c["chips"] -= 1
+        return c
+    c = {"kind": kind, "style": rng.choice(["wide", "fast"]), "epochs": rng.randint(40, 120)}
+    c["noise"] = _log_int(rng, 5e4, 3e5) // c["epochs"]
+    if kind == "vote":
+        form = rng.choice(["epochs", "detections", "weighted_epochs", "weighted_detections",
+                           "sort"])
+        if form == "sort":
+            c.update(style="fast", path="sort", v_block=_log_int(rng, 32, 512))
+        elif form != "epochs" or rng.random() < 0.3:
+            c.update(style="faint", mode=form)
+        if rng.random() < 0.3:
+            c.update(order="by_count", top_k=rng.randint(1, 2000))
+    elif kind == "refine":
+        c["starts"] = rng.choice([30, 100, 500])
+    elif kind == "features":
+        # slow movers; the threshold rule at the pool's size in noise stacks, one below
+        c.update(style="wide", half_height=_log_int(rng, 10, 110), pool=_log_int(rng, 1e3, 2e5))
+        bins = 2048 * 4096 / 16.0
+        c["n_pool"] = max(2, sas.threshold_n_min(
+            c["epochs"], c["noise"] / bins, 381 * (2 * c["half_height"] + 1) * bins,
+            c["pool"]) - 1)
+    return c
+
+
+# --------------------------------------------------------------------------- inputs
+
+def _catalog(case, seed):
+    style = case["style"]
+    if style == "tiny":
+        return _first(synth.make_tiny(seed), _n(case))
+    make = {"wide": synth.make_wide, "fast": synth.make_fast, "faint": synth.make_faint}[style]
+    return _first(make(seed, n_epochs=case["epochs"], noise_per_epoch=case["noise"]), _n(case))
+
+
+def _first(wl, n):
+    """The first n of a catalog's shuffled detections (their number otherwise
+    depends on the seed)."""
+    for k in ("x_q8", "y_q8", "epoch", "snr"):
+        setattr(wl, k, getattr(wl, k)[:n])
+    return wl
+
+
+def _n(case):
+    return 2000 if case["style"] == "tiny" else case["epochs"] * case["noise"]
+
+
+def _pool_velocities(case):
+    """Box of trial velocities of the features case, 1 px/h apart, rows of vy."""
+    h = case["half_height"]
+    vy, vx = np.mgrid[-h:h + 1, -400:-19]
+    return np.stack([vx.ravel(), vy.ravel()], axis=1).astype(np.int32) * 256
+
+
+def _velocities(case, wl):
+    if case["kind"] == "features":
+        return _pool_velocities(case)
+    v = sas.grid_from_spec(wl.grid, wl.binw_q8, wl.span_q16)
+    if case.get("v_block"):  # consecutive velocities of the grid
+        k = min(case["v_block"], len(v))
+        v = v[(len(v) - k) // 2:(len(v) - k) // 2 + k]  # those about v = 0
+    return v
+
+
+def _threshold(case, wl, v):
+    """N_min, and the typical weight of a weighted search."""
+    mode = case.get("mode", "epochs")
+    if case["kind"] == "features":
+        return case["n_pool"], 0
+    if case["style"] == "tiny":
+        return wl.n_min, 0
+    if case["style"] == "wide":
+        return int(round(0.25 * case["epochs"])), 0
+    area = float(wl.width_px * wl.height_px)
+    mu = case["noise"] * wl.bin_px ** 2 / area
+    n_min = sas.threshold_n_min(case["epochs"], mu, len(v) * area / wl.bin_px ** 2,
+                                mode="detections" if mode.endswith("detections") else "epochs")
+    if not mode.startswith("weighted"):
+        return n_min, 0
+    return 22 * n_min, 22  # the mean weight of noise above SNR 3
+
+
+def _plan(case, wl, v):
+    n_min, w_hint = _threshold(case, wl, v)
+    n = _n(case)
+    mode, path = case.get("mode", "epochs"), case.get("path", "auto")
+    tun = None
+    if path == "auto" and mode == "epochs" and case["kind"] != "features":
+        tun = autotune.cached(autotune.shape_class(v, wl.t_q16, wl.binw_q8, n_min, wl.extent_q8,
+                                                   n))
+    tun = dict(tun or {}, n_det_hint=n)
+    if w_hint:
+        tun["weight_hint"] = w_hint
+    return sas.Plan(v, wl.t_q16, wl.binw_q8, n_min, wl.extent_q8, mode=mode,
+                    count_sat=255 if wl.count_dtype == "u8" else 65535, path=path, tuning=tun)
+
+
+def _search(case, seed):
+    wl = _catalog(case, seed)
+    v = _velocities(case, wl)
+    plan = _plan(case, wl, v)
+    s = sas.Search(plan, wl.n, cand_cap=1 << 22 if case["kind"] == "features" else CAND_CAP)
+    w = synth.likelihood_weights(wl.snr) if plan.weighted else None
+    return {"kind": case["kind"], "case": case, "wl": wl, "plan": plan, "s": s,
+            "cat": s.upload(wl.x_q8, wl.y_q8, wl.epoch, w),
+            "out": np.zeros(CAND_CAP, dtype=sas.CAND_DTYPE)}
+
+
+def _network_inputs(case, seed, rows):
+    """Weights, standardisation, feature-like rows and labels."""
+    rng = np.random.default_rng(seed)
+    p = np.zeros(sas.MLP_PARAMS, dtype=np.float32)
+    p[0:4096] = rng.uniform(-1, 1, 4096) * math.sqrt(6.0 / 32)
+    p[4096:4224] = rng.normal(0, 0.05, 128)
+    p[4224:20608] = rng.uniform(-1, 1, 16384) * math.sqrt(6.0 / 128)
+    p[20608:20736] = rng.normal(0, 0.05, 128)
+    p[20736:20864] = rng.uniform(-1, 1, 128) * math.sqrt(6.0 / 128)
+    mean = rng.uniform(-0.5, 1.0, 32).astype(np.float32)
+    std = rng.uniform(0.05, 1.5, 32).astype(np.float32)
+    std[rng.integers(0, 32)] = 0.0  # a constant feature
+    g = torch.Generator(device="cuda").manual_seed(int(seed))
+    x = torch.randn(rows, 32, device="cuda", generator=g)
+    x = x * torch.as_tensor(std).cuda() + torch.as_tensor(mean).cuda()
+    y = (torch.rand(rows, device="cuda", generator=g) < 0.05).float()
+    return p, mean, std, x.contiguous(), y
+
+
+TRAIN = {"pos_weight": 19.0, "lr": 1e-3, "betas": (0.9, 0.999), "eps": 1e-8,
+         "weight_decay": 0.01}
+
+
+def prepare(case, seed):
+    kind = case["kind"]
+    if kind in ("train", "score"):
+        rows = case["batch"] * case["steps"] if kind == "train" else case["rows"]
+        p, mean, std, x, y = _network_inputs(case, seed, rows)
+        net = sas.MLP(max_batch=case["batch"])
+        net.set_norm(mean, std)
+        net.set_params(p)
+        return {"kind": kind, "case": case, "net": net, "x": x, "y": y}
+    if kind == "batch":
+        chips = []
+        for q in synth.night_chip_params(4, 64)[case["first"]:case["first"] + case["chips"]]:
+            wl = _first(synth.make_night_chip(dict(q, seed=1000 * seed + q["chip"]), 0),
+                        q["n_det"])
+            v = sas.grid_from_spec(wl.grid, wl.binw_q8, wl.span_q16)
+            c = {"kind": "vote", "style": q["style"], "epochs": q["n_epochs"],
+                 "noise": q["n_det"] // q["n_epochs"]}
+            x, y, e = (torch.as_tensor(a).cuda() for a in (wl.x_q8, wl.y_q8, wl.epoch))
+            chips.append((_plan(c, wl, v), x, y, e))
+        return {"kind": kind, "case": case, "b": sas.Batch(chips, CAND_CAP),
+                "out": [np.zeros(CAND_CAP, dtype=sas.CAND_DTYPE) for _ in chips]}
+    st = _search(case, seed)
+    if kind == "vote":
+        return st
+    # the later steps start from a finished vote
+    s, cat = st["s"], st["cat"]
+    s.vote(*cat)
+    recs = s.peaks()
+    if kind == "features":
+        # the pool in canonical order (the vote appends it in no fixed order), cut
+        # to the size the program takes on (from the start again if it is shorter)
+        recs = np.resize(recs, case["pool"])
+        s.cand[:len(recs)].copy_(torch.as_tensor(recs.view(np.int32).reshape(-1, 4)))
+        s.res[0] = len(recs)
+        st["snr"] = torch.as_tensor(st["wl"].snr).cuda()
+        st["spacing"] = sas.grid_spacing(st["wl"].binw_q8, st["wl"].span_q16)
+    if kind == "refine":
+        clusters, owner = s.extract(st["wl"].n)
+        order = np.argsort(owner, kind="stable")
+        own = owner[order]
+        cut = np.searchsorted(own, np.arange(len(clusters) + 1))
+        st["groups"] = [order[a:b] for a, b in zip(cut[:-1], cut[1:])]
+        st["starts"] = synth.mcd_starts(7, case["starts"])
+        st["refined"] = np.zeros(1 << 12, dtype=sas.REFINED_DTYPE)
+        st["sets"] = np.zeros((2, 1 << 18), dtype=np.int32)
+    return st
+
+
+def _records(r):
+    return {k: r[k] for k in FIELDS}
+
+
+def run(st):
+    """One pass.  Lists land in arrays the program keeps; what lies beyond
+    their length is zero."""
+    kind, case = st["kind"], st["case"]
+    if kind == "vote":
+        s = st["s"]
+        s.vote(*st["cat"])
+        r = sas.peaks(s.cand, s.res, case.get("order", "canonical"), case.get("top_k", 0),
+                      out=st["out"])
+        return {"n": len(r), "list": _records(st["out"])}
+    if kind == "batch":
+        b = st["b"]
+        b.vote()
+        n = [len(sas.peaks(b.cand[k], b.res[k], out=out)) for k, out in enumerate(st["out"])]
+        return {"n": n, "lists": [_records(out) for out in st["out"]]}
+    if kind == "extract":
+        clusters, owner = st["s"].extract(st["wl"].n)
+        st["out"][:len(clusters)] = clusters
+        return {"n": len(clusters), "clusters": _records(st["out"]), "owner": owner}
+    if kind == "refine":
+        recs, gathered, subsets = st["s"].refine(*st["cat"], st["groups"], st["starts"])
+        out = st["refined"]
+        out[:len(recs)] = recs
+        for row, parts in zip(st["sets"], (gathered, subsets)):
+            np.concatenate(parts, out=row[:sum(map(len, parts))])
+        return dict({k: out[k] for k in out.dtype.names}, n=len(recs), sets=st["sets"])
+    if kind == "features":
+        recs, feat = st["s"].features(st["wl"].n, st["snr"], st["spacing"])
+        return {"pool": _records(recs), "features": feat}
+    if kind == "score":
+        return st["net"].forward(st["x"])
+    B = case["batch"]
+    for k in range(case["steps"]):
+        loss = st["net"].train_step(st["x"][k * B:(k + 1) * B], st["y"][k * B:(k + 1) * B],
+                                    **TRAIN)
+    return {"loss": loss, "params": st["net"].params()}
+
+
+# --------------------------------------------------------------------------- work
+
+def work(case):
+    """Bytes: inputs read and outputs written once.  flops: operations the
+    method cannot do without (votes: 6 integer operations each)."""
+    kind = case["kind"]
+    if kind == "train":
+        rows = case["batch"] * case["steps"]
+        return {"bytes": rows * 33 * 4 + case["steps"] * 20865 * 4 * 6.0,
+                "flops": rows * 6.0 * (32 * 128 + 128 * 128 + 128)}
+    if kind == "score":
+        return {"bytes": case["rows"] * 33 * 4.0,
+                "flops": case["rows"] * 2.0 * (32 * 128 + 128 * 128 + 128)}
+    n_v = {"tiny": 441, "wide": 84351, "fast": 1229685, "faint": 17700}
+    if kind == "batch":
+        qs = synth.night_chip_params(4, 64)[case["first"]:case["first"] + case["chips"]]
+        return {"bytes": float(sum(9 * q["n_det"] + 8 * n_v[q["style"]] for q in qs)),
+                "flops": float(sum(6 * q["n_det"] * n_v[q["style"]] for q in qs))}
+    n = _n(case)
+    if kind == "vote":
+        k = min(case.get("v_block", 1 << 30), n_v[case["style"]])
+        return {"bytes": 9.0 * n + 8.0 * k, "flops": 6.0 * n * k}
+    if kind == "extract":
+        # about 3000 stacks of 40 detections: each list and each owner once
+        return {"bytes": 12.0 * n + 3000 * (16 + 40 * 12.0), "flops": 3000 * 40 * 6.0}
+    if kind == "refine":
+        # about 175 clusters of 35 points, 2.35 rounds; per start two passes of
+        # distances and moments over the points
+        return {"bytes": 13.0 * n + 175 * (72 + 35 * 12.0),
+                "flops": 175 * 2.35 * case["starts"] * 2 * 35 * 40.0}
+    # features: the catalog with its SNR, 16 B in and 128 B out per candidate
+    return {"bytes": 13.0 * n + case["pool"] * 144.0,
+            "flops": case["pool"] * case["n_pool"] * 60.0}
+
+
+# --------------------------------------------------------------------------- exact
+
+def _exact_network(case, seed):
+    train = case["kind"] == "train"
+    B = case["batch"]
+    p0, mean, std, x, y = _network_inputs(case, seed, B * case["steps"] if train
+                                          else case["rows"])
+    sd = torch.as_tensor(np.where(std == 0, 1.0, std.astype(np.float64))).cuda()
+    a = (x.double() - torch.as_tensor(mean).cuda().double()) / sd
+    p = torch.as_tensor(p0).cuda().double()
+
+    def logits(p, a):
+        h = torch.relu(a @ p[0:4096].view(32, 128) + p[4096:4224])
+        h = torch.relu(h @ p[4224:20608].view(128, 128) + p[20608:20736])
+        return h @ p[20736:20864] + p[20864]
+
+    if not train:
+        return logits(p, a)
+    m, v = torch.zeros_like(p), torch.zeros_like(p)
+    b1, b2 = TRAIN["betas"]
+    for k in range(case["steps"]):
+        q = p.detach().requires_grad_(True)
+        loss = torch.nn.functional.binary_cross_entropy_with_logits(
+            logits(q, a[k * B:(k + 1) * B]), y[k * B:(k + 1) * B].double(),
+            pos_weight=torch.tensor(TRAIN["pos_weight"], device="cuda", dtype=torch.float64))
+        g, = torch.autograd.grad(loss, q)
+        m = b1 * m + (1 - b1) * g
+        v = b2 * v + (1 - b2) * g * g
+        step = (m / (1 - b1 ** (k + 1))) / ((v / (1 - b2 ** (k + 1))).sqrt() + TRAIN["eps"])
+        p = p - TRAIN["lr"] * (step + TRAIN["weight_decay"] * p)
+    return {"loss": loss.detach().reshape(1), "params": p}
+
+
+def _exact_features(case, seed):
+    """Vote and features of the pool in torch: integers for the bins, FP64
+    for the features."""
+    wl = _catalog(case, seed)
+    v = _pool_velocities(case)
+    b, E, n_pool = wl.binw_q8, wl.n_epochs, case["n_pool"]
+    dev = "cuda"
+    x, y = (torch.as_tensor(q.astype(np.int64)).to(dev) for q in (wl.x_q8, wl.y_q8))
+    e = torch.as_tensor(wl.epoch.astype(np.int64)).to(dev)
+    t = torch.as_tensor(wl.t_q16).to(dev)
+    dt = t - t[torch.unique(e)].min()
+    d = dt[e]
+    D = int(t.max() - t.min())
+    vt = torch.as_tensor(v.astype(np.int64)).to(dev)
+    kb = 16 + int(math.log2(b))
+    # bins reach max |v| D beyond the chip on either side
+    ox, oy = (int(q) * D // (b << 16) + 2 for q in np.abs(v).max(axis=0))
+    nx, ny = (wl.width_px * 256) // b + 2 * ox + 1, (wl.height_px * 256) // b + 2 * oy + 1
+    cv, cb, pc, pd = [], [], [], []
+    n_c, V = 0, 16
+    for k0 in range(0, len(v), V):
+        vs = vt[k0:k0 + V]
+        bx = (((x << 16)[None] - vs[:, :1] * d) >> kb) + ox
+        by = (((y << 16)[None] - vs[:, 1:] * d) >> kb) + oy
+        cell = ((torch.arange(len(vs), device=dev)[:, None] * ny + by) * nx + bx).reshape(-1)
+        cnt = torch.zeros(len(vs) * ny * nx, dtype=torch.int32, device=dev)
+        cnt.scatter_add_(0, cell, torch.ones_like(cell, dtype=torch.int32))
+        hot = (cnt >= n_pool).nonzero().reshape(-1)
+        idx = torch.full_like(cnt, -1)
+        idx[hot] = torch.arange(len(hot), device=dev, dtype=torch.int32)
+        got = idx[cell]
+        at = (got >= 0).nonzero().reshape(-1)
+        cv.append(k0 + hot // (ny * nx))
+        cb.append(hot % (ny * nx))
+        pc.append(got[at].long() + n_c)
+        pd.append(at % len(x))
+        n_c += len(hot)
+    cv, cb, pc, pd = (torch.cat(q) for q in (cv, cb, pc, pd))
+    # distinct epochs; stacks of fewer than n_pool leave the list
+    seen = torch.zeros(n_c * E, dtype=torch.bool, device=dev)
+    seen[pc * E + e[pd]] = True
+    seen = seen.view(n_c, E)
+    keep = seen.sum(1) >= n_pool
+    new = torch.cumsum(keep.long(), 0) - 1
+    on = keep[pc]
+    pc, pd, cv, cb, seen = new[pc[on]], pd[on], cv[keep], cb[keep], seen[keep]
+    # the pool: the first of them in the order they were found in, (v_idx, by, bx)
+    K = min(case["pool"], len(cv))
+    on = pc < K
+    pc, pd, cv, cb, seen = pc[on], pd[on], cv[:K], cb[:K], seen[:K]
+    cx, cy = cb % nx - ox, cb // nx - oy
+    vx, vy = vt[cv, 0], vt[cv, 1]
+
+    def tot(q):
+        return torch.zeros(K, dtype=torch.float64, device=dev).scatter_add_(0, pc, q)
+
+    one = torch.ones(len(pc), dtype=torch.float64, device=dev)
+    rx = ((x[pd] << 16) - vx[pc] * d[pd]).double() / (65536.0 * b) - cx[pc] - 0.5
+    ry = ((y[pd] << 16) - vy[pc] * d[pd]).double() / (65536.0 * b) - cy[pc] - 0.5
+    tau, snr = d[pd].double() / D, torch.as_tensor(wl.snr).to(dev).double()[pd]
+    n, c = tot(one), seen.sum(1).double()
+    f = torch.zeros(K, 32, dtype=torch.float64, device=dev)
+    f[:, 0], f[:, 1] = c / E, n / E
+    far = torch.where(seen, dt.double()[None], torch.inf)
+    f[:, 2] = far.amin(1) / D
+    f[:, 3] = (torch.where(seen, dt.double()[None], -torch.inf).amax(1)) / D - f[:, 2]
+    run_, best = torch.zeros(K, device=dev), torch.zeros(K, device=dev)
+    for k in range(E):
+        run_ = torch.where(seen[:, k], run_ + 1, 0)
+        best = torch.maximum(best, run_)
+    f[:, 4] = best.double() / E
+    vmax = float(np.sqrt((v.astype(np.float64) ** 2).sum(1)).max())
+    f[:, 5], f[:, 6] = vx / vmax, vy / vmax
+    f[:, 7] = torch.hypot(vx.double(), vy.double()) / vmax
+    f[:, 8], f[:, 11] = tot(snr) / E, tot(snr) / n - 3.0
+    mx, my, mt = tot(rx) / n, tot(ry) / n, tot(tau) / n
+    ex, ey, et = rx - mx[pc], ry - my[pc], tau - mt[pc]
+    f[:, 12], f[:, 13] = mx, my
+    f[:, 14], f[:, 15] = (tot(ex * ex) / n).sqrt(), (tot(ey * ey) / n).sqrt()
+    stt = tot(et * et)
+    f[:, 16], f[:, 17] = tot(et * ex) / stt, tot(et * ey) / stt  # n_pool > 1 epochs: stt > 0
+    sse = tot((ex - f[pc, 16] * et) ** 2) + tot((ey - f[pc, 17] * et) ** 2)
+    f[:, 31] = (sse / (2 * n)).sqrt()
+    sl = torch.clamp(4 * d[pd] // D, max=3)
+    for k in range(4):
+        w = (sl == k).double()
+        m = tot(w)
+        f[:, 18 + 2 * k] = tot(w * rx) / m.clamp(min=1)
+        f[:, 19 + 2 * k] = tot(w * ry) / m.clamp(min=1)
+        f[:, 26 + k] = m / n
+    f[:, 30] = (n - c) / n
+    # neighbours in velocity index and bin: the velocities lie on the lattice
+    ix, iy = vx // 256 + 1024, vy // 256 + 1024
+    key = ((ix * 2048 + iy) * 32768 + cx + 16384) * 32768 + cy + 16384
+    srt, order = torch.sort(key)
+    cnt = torch.zeros(K, dtype=torch.float64, device=dev)
+    top = torch.zeros(K, dtype=torch.float64, device=dev)
+    for q in range(81):
+        if q == 40:
+            continue
+        step = ((q % 3 - 1) * 2048 + (q // 3) % 3 - 1) * 32768 + (q // 9) % 3 - 1
+        want = key + step * 32768 + q // 27 - 1
+        at = torch.searchsorted(srt, want).clamp(max=K - 1)
+        hit = srt[at] == want
+        cnt += hit
+        top = torch.maximum(top, torch.where(hit, c[order[at]], 0.0))
+    f[:, 9] = cnt / 80.0
+    f[:, 10] = torch.where(cnt > 0, top / c, 0.0)
+    f = f[torch.arange(case["pool"], device=dev) % K]
+    return {"pool": {k: None for k in FIELDS}, "features": f}
+
+
+def exact(case, seed):
+    if case["kind"] in ("train", "score"):
+        return _exact_network(case, seed)
+    if case["kind"] == "features":
+        return _exact_features(case, seed)
+    # votes and extraction return whole numbers; the fits of the refinement
+    # are 64-bit sums over point sets that their own roundings select
+    return None
