@@ -47,7 +47,7 @@ def listed():
         {"name": "sort path vote", "kind": "vote", "style": "fast", "epochs": 60, "noise": 3000,
          "path": "sort", "v_block": 512},
         # the first chips of the night, both styles, one launch per kernel class
-        {"name": "night batch", "kind": "batch", "chips": 5, "first": 0},
+        {"name": "night batch", "kind": "batch", "chips": 6, "first": 0},
         # Step 3 over the stacks of a wide chip
         {"name": "wide extract", "kind": "extract", "style": "wide", "epochs": 100,
          "noise": 3000},
@@ -78,7 +78,10 @@ def draw(rng):
                 "batch": rng.choice([1024, 4096, 16384])}
     if kind == "batch":
         c = {"kind": kind, "chips": rng.randint(1, 5), "first": rng.randint(5, 58)}
-        while c["chips"] > 1 and work(c)["flops"] > 3.0e12:
+        # at most two fast-style chips: they take most of a night's time
+        night = synth.night_chip_params(4, 64)
+        while c["chips"] > 1 and (work(c)["flops"] > 3.0e12 or sum(
+                q["style"] == "fast" for q in night[c["first"]:c["first"] + c["chips"]]) > 2):
             c["chips"] -= 1
         return c
     c = {"kind": kind, "style": rng.choice(["wide", "fast"]), "epochs": rng.randint(40, 120)}
