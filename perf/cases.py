@@ -26,7 +26,7 @@ import torch
 from paper_2509_26279_amd import autotune, sas, synth
 
 FIELDS = ("v_idx", "bx", "by", "count", "flags")
-CAND_CAP = 1 << 16  # candidates a program keeps room for, per catalog
+CAND_CAP = 1 << 18  # candidates a program keeps room for, per catalog
 
 
 def listed():
@@ -92,7 +92,8 @@ def draw(rng):
         if form == "sort":
             c.update(style="fast", path="sort", v_block=_log_int(rng, 32, 512))
         elif form != "epochs" or rng.random() < 0.3:
-            c.update(style="faint", mode=form)
+            c.update(style="faint", mode=form, epochs=rng.randint(40, 80))
+            c["noise"] = _log_int(rng, 5e4, 3e5) // c["epochs"]
         if rng.random() < 0.3:
             c.update(order="by_count", top_k=rng.randint(1, 2000))
     elif kind == "refine":
@@ -161,7 +162,7 @@ def _threshold(case, wl, v):
                                 mode="detections" if mode.endswith("detections") else "epochs")
     if not mode.startswith("weighted"):
         return n_min, 0
-    return 22 * n_min, 22  # the mean weight of noise above SNR 3
+    return 24 * n_min, 22  # noise above SNR 3 weighs 22 on average
 
 
 def _plan(case, wl, v):
