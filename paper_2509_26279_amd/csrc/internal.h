@@ -219,32 +219,36 @@ constexpr int kMlpOffB3 = kMlpOffW3 + kMlpHidden;
 constexpr int kMlpParams = kMlpOffB3 + 1;  // 20865
 constexpr int kMlpSplitK = 512;            // batch rows per weight-gradient partial
 
+// Partial weight gradients of one chunk: W1, W2 and W3.
+constexpr int kMlpPart = kMlpIn * kMlpHidden + kMlpHidden * kMlpHidden + kMlpHidden;
+
 struct MlpWeights {        // bf16 working copies of the weights
-    uint16_t *w1;          // [32][128]
-    uint16_t *w2;          // [128][128]
-    uint16_t *w3;          // [128][16], column 0 = W3, the rest 0
-    float *b3pad;          // [16], element 0 = b3, the rest 0
+    uint16_t *w1;          // [32][128] in fragment order (mlp.hip)
+    uint16_t *w2, *w2t;    // [128][128] and its transpose, in fragment order
+    uint16_t *w3;          // [128]
 };
 
 struct MlpBuffers {
-    float *p, *m, *v, *grad;   // FP32 master parameters, AdamW moments, gradient
+    float *p, *m, *v;          // FP32 master parameters, AdamW moments
     MlpWeights w;
     float *mu, *sd;            // [32] input standardisation
-    uint16_t *a0;              // [max_batch][32]
-    uint16_t *h1, *h2;         // [max_batch][128]
-    uint16_t *d1, *d2;         // [max_batch][128]
-    float *z16;                // [max_batch][16], column 0 = logits
-    uint16_t *g3;              // [max_batch][16]
+    // a training batch, rows up to a multiple of 32, in fragment order over the rows
+    uint16_t *a0;              // 32 columns
+    uint16_t *h1, *h2;         // 128 columns
+    uint16_t *d1, *d2;         // 128 columns
+    uint16_t *g3;              // [rows] logit gradients
     float *row_loss;           // [max_batch]
-    float *part;               // [max_batch / kMlpSplitK + 1][128][128]
+    float *part;               // [max_batch / kMlpSplitK + 1][kMlpPart]
+    float *bsum;               // [257] column sums of d1, d2 and g3
 };
 
-hipError_t mlp_forward(const MlpBuffers &b, const float *x, int64_t n, hipStream_t s);
 hipError_t mlp_logits(const MlpBuffers &b, const float *x, int64_t n, float *out, hipStream_t s);
 hipError_t mlp_grad(const MlpBuffers &b, const float *x, const float *y, int64_t B, float pw,
                     float *loss, float *grad, hipStream_t s);
-hipError_t mlp_adamw(const MlpBuffers &b, const float *grad, float lr, float b1, float b2,
-                     float eps, float wd, float c1, float c2, hipStream_t s);
+// One AdamW step; c1, c2: the moments' bias corrections.
+hipError_t mlp_step(const MlpBuffers &b, const float *x, const float *y, int64_t B, float pw,
+                    float *loss, float lr, float b1, float b2, float eps, float wd, float c1,
+                    float c2, hipStream_t s);
 hipError_t mlp_refresh(const MlpBuffers &b, hipStream_t s);
 
 // groups: lane groups G (1, 2 or 4); segments hold 64 / G velocities.

@@ -10,338 +10,603 @@
 // the batch in two stages (per-chunk partials, then a fixed-order sum), so
 // the result is the same on every run.  AdamW keeps FP32 master weights and
 // refreshes the bf16 working copies.
+//
+// The network is 20865 parameters: the time of a pass is launches and trips
+// to memory, not products.  So a pass over the rows is one kernel that keeps
+// the weights of a wave in registers and the activations in registers and
+// LDS: k_mlp_forward reads x and writes logits; a training step is
+// k_mlp_rows (forward, loss and backward of the rows, activations stored for
+// the weight gradients), k_mlp_wgrad (all partial products and column sums)
+// and k_mlp_update (fixed-order sums and AdamW).
+// As 25 launches of one 64 x 64 tiled product, element-wise passes and
+// reductions, a step on 4096 rows took 284 us and 2.3e5 logits 2350 us; now
+// 19 us (8.8 us k_mlp_rows, 6.1 us k_mlp_wgrad, 3.3 us k_mlp_update) and
+// 21 us.  A step is bound by the latency of its three launches, the logits
+// by the LDS reads of the fragments and their products (30 MB of input at
+// 1.4 TB/s, 0.45 PFLOP/s); results are bit for bit those of the older form.
+//
+// Matrix fragments.  A lane of the 16 x 16 x 32 product holds, of either
+// operand, 8 consecutive k (8 (lane / 16) + j) of one row or column
+// (lane % 16); of the result, rows 4 (lane / 16) + i of column lane % 16.
+// The working copies of the weights and the stored activations are kept in
+// fragment order ([tile][lane][8]), so that every load is 16 bytes a lane
+// and contiguous over the wave.  The products over k of every output run
+// in steps of 32 in ascending k.
+#include <type_traits>
+
 #include "internal.h"
 
 namespace sas {
 namespace {
 
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+// rows of the caller's matrix: 4-byte aligned (global loads of any width are)
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
 
-__device__ inline uint16_t f2bf(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return 0x7fc0;  // NaN
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
+constexpr int H = kMlpHidden;
+constexpr int NT = H / 16;       // 16-column tiles of a hidden layer
+constexpr int KT = H / 32;       // steps of 32 over a hidden layer
+constexpr int MT = 256;          // threads: 4 waves, each 32 columns of a hidden layer
+constexpr int MWAVES = MT / 64;
+constexpr int LD = H + 8;        // LDS row of a hidden layer, in bf16 (16-byte multiple;
+                                 // rows 4 banks apart)
+constexpr int LD0 = kMlpIn + 8;  // LDS row of the inputs
+
+__device__ inline __bf16 to_bf(float f) { return (__bf16)f; }
+__device__ inline v8bf load8(const uint16_t *p) { return *(const v8bf *)p; }
+__device__ inline v4f mma(v8bf a, v8bf b, v4f c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
-__device__ inline float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
+
+// Place of element (k, n) of a K x 128 matrix in fragment order.
+__host__ __device__ inline int frag_index(int k, int n) {
+    return (((k >> 5) * NT + (n >> 4)) * 64 + ((k & 31) >> 3) * 16 + (n & 15)) * 8 + (k & 7);
+}
 
 // Store parameter i (packed index) into the bf16 working copies.
-__device__ inline void mlp_store_working(const MlpWeights &w, int64_t i, float v) {
+__device__ inline void mlp_store_working(const MlpWeights &w, int i, float v) {
+    const uint16_t q = __builtin_bit_cast(uint16_t, to_bf(v));
     if (i < kMlpOffB1) {
-        w.w1[i] = f2bf(v);
+        w.w1[frag_index(i / H, i % H)] = q;
     } else if (i >= kMlpOffW2 && i < kMlpOffB2) {
-        w.w2[i - kMlpOffW2] = f2bf(v);
+        const int k = (i - kMlpOffW2) / H, n = (i - kMlpOffW2) % H;
+        w.w2[frag_index(k, n)] = q;
+        w.w2t[frag_index(n, k)] = q;
     } else if (i >= kMlpOffW3 && i < kMlpOffB3) {
-        w.w3[(i - kMlpOffW3) * 16] = f2bf(v);
-    } else if (i == kMlpOffB3) {
-        w.b3pad[0] = v;
+        w.w3[i - kMlpOffW3] = q;
     }
 }
 
-enum Epi : int {
-    kEpiBiasReluBf16 = 0,  // C = q(relu(acc + bias[n]))
-    kEpiBiasF32 = 1,       // C = acc + bias[n]
-    kEpiMaskBf16 = 2,      // C = q(acc [mask[m][n] > 0])
-    kEpiPartialF32 = 3,    // C[kz] = acc (split over K)
+// Weights of wave w: columns 32 w .. 32 w + 31 of the hidden layers, W3 whole.
+struct FwdWeights {
+    v8bf w1[2], w2[KT][2], w3[KT];
+    float b1[2], b2[2], b3;
+    __device__ FwdWeights(const MlpBuffers &b, int wave, int lane) {
+        const int r16 = lane & 15, q4 = lane >> 4;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int nt = 2 * wave + t;
+            w1[t] = load8(b.w.w1 + (nt * 64 + lane) * 8);
+#pragma unroll
+            for (int k = 0; k < KT; ++k) w2[k][t] = load8(b.w.w2 + ((k * NT + nt) * 64 + lane) * 8);
+            b1[t] = b.p[kMlpOffB1 + 16 * nt + r16];
+            b2[t] = b.p[kMlpOffB2 + 16 * nt + r16];
+        }
+        const v8bf zero = {};
+#pragma unroll
+        for (int k = 0; k < KT; ++k) {  // column 0 of a 16-column tile, the rest 0
+            const v8bf c = load8(b.w.w3 + 32 * k + 8 * q4);
+            w3[k] = r16 == 0 ? c : zero;
+        }
+        b3 = b.p[kMlpOffB3];
+    }
 };
 
-struct Gemm {
-    const uint16_t *A;
-    int64_t sam, sak;  // A[m][k] = A[m sam + k sak]
-    const uint16_t *B;
-    int64_t sbk, sbn;  // B[k][n] = B[k sbk + n sbn]
-    int M, N, K, k_chunk;
-    const float *bias;
-    const uint16_t *mask;
-    int64_t smm;
-    void *C;
-    int64_t scm;
-};
-
-constexpr int GT = 256;  // 4 waves, each a 32 x 32 quarter of the 64 x 64 tile
-
-constexpr int GK = 32;   // K of one v_mfma_f32_16x16x32_bf16
-
-template <int EPI>
-__global__ void __launch_bounds__(GT) k_gemm(Gemm g) {
-    __shared__ uint16_t As[64][GK + 2];
-    __shared__ uint16_t Bs[GK][64 + 2];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-    const int kb = blockIdx.z * g.k_chunk, ke = min(g.K, kb + g.k_chunk);
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-    const int r16 = lane & 15, q4 = lane >> 4;
-    v4f acc[2][2];
+// Standardised inputs of row m as the lane's fragment (zero past the end).
+struct Norm {
+    float mu[8], sd[8];
+    __device__ Norm(const MlpBuffers &b, int lane) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = (v4f){0.f, 0.f, 0.f, 0.f};
-    for (int k0 = kb; k0 < ke; k0 += GK) {
-        for (int q = tid; q < 64 * GK; q += GT) {
-            const int r = q / GK, kk = q % GK, m = m0 + r, k = k0 + kk;
-            As[r][kk] = (m < g.M && k < ke) ? g.A[(int64_t)m * g.sam + (int64_t)k * g.sak] : 0;
+        for (int j = 0; j < 8; ++j) {
+            mu[j] = b.mu[8 * (lane >> 4) + j];
+            const float s = b.sd[8 * (lane >> 4) + j];
+            sd[j] = s == 0.0f ? 1.0f : s;
         }
-        for (int q = tid; q < GK * 64; q += GT) {
-            const int kk = q >> 6, cc = q & 63, k = k0 + kk, n = n0 + cc;
-            Bs[kk][cc] = (k < ke && n < g.N) ? g.B[(int64_t)k * g.sbk + (int64_t)n * g.sbn] : 0;
-        }
-        __syncthreads();
-        // operands of a 16 x 16 x 32 product: lane holds row (or column)
-        // lane % 16 at k = 8 (lane / 16) + j, j < 8
+    }
+    __device__ v8bf row(const float *x, int64_t m, int64_t n, int lane) const {
+        v8bf a = {};
+        if (m < n) {
+            const float *p = x + m * kMlpIn + 8 * (lane >> 4);
+            const v4f_any u = *(const v4f_any *)p, v = *(const v4f_any *)(p + 4);
 #pragma unroll
-        for (int ti = 0; ti < 2; ++ti) {
-            v8bf a;
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                a[j] = __builtin_bit_cast(__bf16, As[wm + 16 * ti + r16][8 * q4 + j]);
-#pragma unroll
-            for (int tj = 0; tj < 2; ++tj) {
-                v8bf b;
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    b[j] = __builtin_bit_cast(__bf16, Bs[8 * q4 + j][wn + 16 * tj + r16]);
-                acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[ti][tj], 0, 0, 0);
+            for (int j = 0; j < 4; ++j) {
+                a[j] = to_bf((u[j] - mu[j]) / sd[j]);
+                a[4 + j] = to_bf((v[j] - mu[4 + j]) / sd[4 + j]);
             }
         }
-        __syncthreads();
+        return a;
     }
-    // result layout of a 16 x 16 tile: lane holds rows 4 (lane / 16) + i, column lane % 16
+};
+
+// Hidden-layer epilogue of a 16-row tile: q(relu(acc + bias)) of the lane's
+// 4 rows into LDS and back to the caller.
+__device__ inline v4bf relu_store(v4f acc, float bias, __bf16 *tile, int q4, int col) {
+    v4bf h;
 #pragma unroll
-    for (int ti = 0; ti < 2; ++ti)
+    for (int i = 0; i < 4; ++i) {
+        h[i] = to_bf(fmaxf(acc[i] + bias, 0.0f));
+        tile[(4 * q4 + i) * LD + col] = h[i];
+    }
+    return h;
+}
+
+// Logits of rows [0, n).  A workgroup takes 16 R rows at a time; its 4 waves
+// split the columns of the hidden layers.  R = 4 (large n): the weights and
+// each A fragment serve 4 times the products, and each wave standardises and
+// finishes one 16-row tile; R = 1 (small n): 4 times as many workgroups.
+template <int R>
+__global__ void __launch_bounds__(MT) k_mlp_forward(MlpBuffers b, const float *__restrict__ x,
+                                                    int64_t n, float *__restrict__ out) {
+    __shared__ __attribute__((aligned(16))) __bf16 a0s[16 * R * LD0];
+    __shared__ __attribute__((aligned(16))) __bf16 h1s[16 * R * LD], h2s[16 * R * LD];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r16 = lane & 15, q4 = lane >> 4;
+    const FwdWeights w(b, wave, lane);
+    const Norm norm(b, lane);
+    const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
+    const int64_t tiles = (n + 16 * R - 1) / (16 * R);
+    for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+        const int64_t m0 = t * (16 * R);
+        v8bf a[R];
+        if (R == 1) {  // every wave standardises the tile
+            a[0] = norm.row(x, m0 + r16, n, lane);
+        } else {       // wave r standardises row tile r
+            *(v8bf *)(a0s + (16 * wave + r16) * LD0 + 8 * q4) =
+                norm.row(x, m0 + 16 * wave + r16, n, lane);
+            __syncthreads();
 #pragma unroll
-        for (int tj = 0; tj < 2; ++tj)
+            for (int r = 0; r < R; ++r) a[r] = *(const v8bf *)(a0s + (16 * r + r16) * LD0 + 8 * q4);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                relu_store(mma(a[r], w.w1[c], zero4), w.b1[c], h1s + 16 * r * LD, q4,
+                           32 * wave + 16 * c + r16);
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            v4f acc[2] = {zero4, zero4};
+#pragma unroll
+            for (int k = 0; k < KT; ++k) {
+                const v8bf f = *(const v8bf *)(h1s + (16 * r + r16) * LD + 32 * k + 8 * q4);
+                acc[0] = mma(f, w.w2[k][0], acc[0]);
+                acc[1] = mma(f, w.w2[k][1], acc[1]);
+            }
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                relu_store(acc[c], w.b2[c], h2s + 16 * r * LD, q4, 32 * wave + 16 * c + r16);
+        }
+        __syncthreads();
+        if (R == MWAVES || wave == 0) {
+            const int r = R == MWAVES ? wave : 0;
+            v4f z = zero4;
+#pragma unroll
+            for (int k = 0; k < KT; ++k)
+                z = mma(*(const v8bf *)(h2s + (16 * r + r16) * LD + 32 * k + 8 * q4), w.w3[k], z);
+            if (r16 == 0)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int64_t m = m0 + 16 * r + 4 * q4 + i;
+                    if (m < n) out[m] = z[i] + w.b3;
+                }
+        }
+        // the next tile writes h1s (R = 4: a0s) after every wave has read it, and
+        // h2s after the barrier that follows h1s
+    }
+}
+
+// Offset of the lane's 4 rows of a result tile (16-row tile rt, column tile
+// ct of nct) in an activation stored in fragment order over its rows:
+// [row / 32][ct][(row % 32) / 8 * 16 + column][row % 8].
+__device__ inline int64_t act_offset(int64_t rt, int nct, int ct, int lane) {
+    const int q4 = lane >> 4;
+    return ((rt >> 1) * nct + ct) * 512 +
+           ((2 * (int)(rt & 1) + (q4 >> 1)) * 16 + (lane & 15)) * 8 + 4 * (q4 & 1);
+}
+
+// Forward, loss and backward of 16 rows per workgroup and pass, with the
+// activations and their gradients stored for k_mlp_wgrad.  Rows past the
+// batch (up to a multiple of 32) are stored as zeros.
+__global__ void __launch_bounds__(MT) k_mlp_rows(MlpBuffers b, const float *__restrict__ x,
+                                                 const float *__restrict__ y, int64_t B,
+                                                 float pw) {
+    __shared__ __attribute__((aligned(16))) __bf16 a0s[16 * LD0], h1s[16 * LD], h2s[16 * LD],
+        d2s[16 * LD];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r16 = lane & 15, q4 = lane >> 4;
+    const FwdWeights w(b, wave, lane);
+    const Norm norm(b, lane);
+    v8bf w3r[2], w2t[KT][2];  // W3 as one row (k = 0), W2 transposed
+    const v8bf zero8 = {};
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const int nt = 2 * wave + c;
+        w3r[c] = zero8;
+        if (q4 == 0) w3r[c][0] = __builtin_bit_cast(__bf16, b.w.w3[16 * nt + r16]);
+#pragma unroll
+        for (int k = 0; k < KT; ++k) w2t[k][c] = load8(b.w.w2t + ((k * NT + nt) * 64 + lane) * 8);
+    }
+    const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
+    const int64_t tiles = 2 * ((B + 31) / 32);
+    for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+        const int64_t m0 = t * 16;
+        const v8bf a = norm.row(x, m0 + r16, B, lane);
+        if (wave == 0) *(v8bf *)(a0s + r16 * LD0 + 8 * q4) = a;
+        bool in[4];  // the lane's result rows are rows of the batch
+#pragma unroll
+        for (int i = 0; i < 4; ++i) in[i] = m0 + 4 * q4 + i < B;
+        const __bf16 zb = to_bf(0.0f);
+        v4bf h1[2], h2[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int col = 32 * wave + 16 * c + r16;
+            h1[c] = relu_store(mma(a, w.w1[c], zero4), w.b1[c], h1s, q4, col);
+            v4bf s = h1[c];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] = in[i] ? s[i] : zb;
+            *(v4bf *)(b.h1 + act_offset(t, NT, 2 * wave + c, lane)) = s;
+        }
+        __syncthreads();
+        if (wave < kMlpIn / 16) {  // the inputs by column
+            v4bf s;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] = a0s[(4 * q4 + i) * LD0 + 16 * wave + r16];
+            *(v4bf *)(b.a0 + act_offset(t, kMlpIn / 16, wave, lane)) = s;
+        }
+        v4f acc[2] = {zero4, zero4};
+#pragma unroll
+        for (int k = 0; k < KT; ++k) {
+            const v8bf f = *(const v8bf *)(h1s + r16 * LD + 32 * k + 8 * q4);
+            acc[0] = mma(f, w.w2[k][0], acc[0]);
+            acc[1] = mma(f, w.w2[k][1], acc[1]);
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            h2[c] = relu_store(acc[c], w.b2[c], h2s, q4, 32 * wave + 16 * c + r16);
+            v4bf s = h2[c];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] = in[i] ? s[i] : zb;
+            *(v4bf *)(b.h2 + act_offset(t, NT, 2 * wave + c, lane)) = s;
+        }
+        __syncthreads();
+        v4f z = zero4;  // every wave: column 0 holds the logits, less b3
+#pragma unroll
+        for (int k = 0; k < KT; ++k)
+            z = mma(*(const v8bf *)(h2s + r16 * LD + 32 * k + 8 * q4), w.w3[k], z);
+        // loss and logit gradient of row r16, by every lane of the row
+        float zr = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float v = __shfl(z[i], 16 * (r16 >> 2), 64);
+            zr = (r16 & 3) == i ? v : zr;
+        }
+        zr += w.b3;
+        const int64_t m = m0 + r16;
+        __bf16 g = zb;
+        if (m < B) {
+            const float yi = y[m];
+            const float sp_pos = fmaxf(zr, 0.0f) + log1pf(expf(-fabsf(zr)));   // softplus(z)
+            const float sp_neg = fmaxf(-zr, 0.0f) + log1pf(expf(-fabsf(zr)));  // softplus(-z)
+            const float sig = 1.0f / (1.0f + expf(-zr));
+            g = to_bf((sig * (pw * yi + 1.0f - yi) - pw * yi) / (float)B);
+            if (wave == 0 && q4 == 0) b.row_loss[m] = pw * yi * sp_neg + (1.0f - yi) * sp_pos;
+        }
+        if (wave == 0 && q4 == 0) b.g3[m] = __builtin_bit_cast(uint16_t, g);
+        v8bf ga = zero8;
+        if (q4 == 0) ga[0] = g;
+        // d2 = q((g3 w3^T) [h2 > 0])
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const v4f d = mma(ga, w3r[c], zero4);
+            v4bf s;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int m = m0 + wm + 16 * ti + 4 * q4 + i, n = n0 + wn + 16 * tj + r16;
-                if (m >= g.M || n >= g.N) continue;
-                const float v = acc[ti][tj][i];
-                const int64_t o = (int64_t)m * g.scm + n;
-                if (EPI == kEpiBiasReluBf16) {
-                    ((uint16_t *)g.C)[o] = f2bf(fmaxf(v + g.bias[n], 0.0f));
-                } else if (EPI == kEpiBiasF32) {
-                    ((float *)g.C)[o] = v + g.bias[n];
-                } else if (EPI == kEpiMaskBf16) {
-                    const float h = bf2f(g.mask[(int64_t)m * g.smm + n]);
-                    ((uint16_t *)g.C)[o] = f2bf(h > 0.0f ? v : 0.0f);
-                } else {
-                    ((float *)g.C)[(int64_t)blockIdx.z * g.M * g.scm + o] = v;
-                }
+                s[i] = to_bf((float)h2[c][i] > 0.0f ? d[i] : 0.0f);
+                d2s[(4 * q4 + i) * LD + 32 * wave + 16 * c + r16] = s[i];
             }
-}
-
-// a0 = q((x - mu) / sd) for rows [0, n) of x (row-major, 32 features)
-__global__ void k_norm_cast(const float *__restrict__ x, int64_t n, const float *__restrict__ mu,
-                            const float *__restrict__ sd, uint16_t *__restrict__ a0) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n * 32) return;
-    const int k = (int)(i & 31);
-    const float s = sd[k] == 0.0f ? 1.0f : sd[k];
-    a0[i] = f2bf((x[i] - mu[k]) / s);
-}
-
-// Per-row loss and logit gradient; g3 is [B][16] with column 0 the gradient.
-__global__ void k_loss(const float *__restrict__ z16, const float *__restrict__ y, int64_t B,
-                       float pw, uint16_t *__restrict__ g3, float *__restrict__ row_loss) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= B) return;
-    const float z = z16[i * 16], yi = y[i];
-    const float sp_pos = fmaxf(z, 0.0f) + log1pf(expf(-fabsf(z)));    // softplus(z)
-    const float sp_neg = fmaxf(-z, 0.0f) + log1pf(expf(-fabsf(z)));   // softplus(-z)
-    row_loss[i] = pw * yi * sp_neg + (1.0f - yi) * sp_pos;
-    const float sig = 1.0f / (1.0f + expf(-z));
-    const float dz = (sig * (pw * yi + 1.0f - yi) - pw * yi) / (float)B;
+            *(v4bf *)(b.d2 + act_offset(t, NT, 2 * wave + c, lane)) = s;
+        }
+        __syncthreads();
+        // d1 = q((d2 W2^T) [h1 > 0])
+        acc[0] = zero4;
+        acc[1] = zero4;
 #pragma unroll
-    for (int c = 0; c < 16; ++c) g3[i * 16 + c] = c == 0 ? f2bf(dz) : (uint16_t)0;
-}
-
-constexpr int RT = 256;
-
-// out[c] = sum over rows r of in[r][c] (bf16 matrix, row stride ld), in a
-// fixed order: thread t sums rows t, t + RT, ...; then a fixed tree.
-__global__ void __launch_bounds__(RT) k_colsum_bf16(const uint16_t *__restrict__ in, int64_t rows,
-                                                    int64_t ld, float *__restrict__ out) {
-    __shared__ float red[RT];
-    const int c = blockIdx.x;
-    float s = 0.0f;
-    for (int64_t r = threadIdx.x; r < rows; r += RT) s += bf2f(in[r * ld + c]);
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int h = RT / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-        __syncthreads();
+        for (int k = 0; k < KT; ++k) {
+            const v8bf f = *(const v8bf *)(d2s + r16 * LD + 32 * k + 8 * q4);
+            acc[0] = mma(f, w2t[k][0], acc[0]);
+            acc[1] = mma(f, w2t[k][1], acc[1]);
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            v4bf s;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] = to_bf((float)h1[c][i] > 0.0f ? acc[c][i] : 0.0f);
+            *(v4bf *)(b.d1 + act_offset(t, NT, 2 * wave + c, lane)) = s;
+        }
+        // the next tile writes h1s and a0s, last read before the second barrier
+        // above, and h2s and d2s after two barriers more
     }
-    if (threadIdx.x == 0) out[c] = red[0];
 }
 
-__global__ void __launch_bounds__(RT) k_sum_f32(const float *__restrict__ in, int64_t n,
-                                                float scale, float *__restrict__ out) {
-    __shared__ float red[RT];
-    float s = 0.0f;
-    for (int64_t r = threadIdx.x; r < n; r += RT) s += in[r];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int h = RT / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-        __syncthreads();
+// Partial weight gradients of one chunk of kMlpSplitK rows: [W1 | W2 | W3].
+constexpr int kPartW2 = kMlpIn * H, kPartW3 = kPartW2 + H * H;
+static_assert(kMlpPart == kPartW3 + H, "partials of W1, W2 and W3");
+// Tasks of a chunk, one wave each: 16 x 32 blocks of dW2 and dW1, 32 of dW3.
+constexpr int kTasksW2 = NT * (NT / 2), kTasksW1 = (kMlpIn / 16) * (NT / 2), kTasksW3 = NT / 2;
+constexpr int kChunkTasks = kTasksW2 + kTasksW1 + kTasksW3;
+constexpr int kSumTasks = (2 * H + 2) / 2 + 1;  // column sums, two a wave, and the loss
+
+// f over the row blocks [rb0, rb1): blocks of kInFlight, then single ones.  A
+// wave issues the loads of kInFlight row blocks before it uses the first:
+// its tasks are serial chains, and the rows were written by other XCDs, so
+// every load is a trip past the L2.  With the compiler's order of loads
+// k_mlp_wgrad took 12.9 us on 4096 rows, now 6.1 us.
+constexpr int kInFlight = 8;
+template <class F>
+__device__ __attribute__((always_inline)) inline void for_row_blocks(int64_t rb0, int64_t rb1,
+                                                                     const F &f) {
+    int64_t rb = rb0;
+    for (; rb + kInFlight <= rb1; rb += kInFlight) f(std::integral_constant<int, kInFlight>{});
+    for (; rb < rb1; ++rb) f(std::integral_constant<int, 1>{});
+}
+
+// Two 16 x 16 blocks A^T B of row blocks [rb0, rb1): operands in fragment order.
+__device__ inline void partial_pair(const uint16_t *A, int nca, int ca, const uint16_t *Bm,
+                                    int ncb, int cb, int64_t rb0, int64_t rb1, float *out, int ldo,
+                                    int lane) {
+    v4f acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    const uint16_t *pa = A + (rb0 * nca + ca) * 512 + lane * 8;
+    const uint16_t *pb = Bm + (rb0 * ncb + cb) * 512 + lane * 8;
+    for_row_blocks(rb0, rb1, [&](auto u) __attribute__((always_inline)) {
+        constexpr int U = decltype(u)::value;
+        v8bf fa[U], f0[U], f1[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            fa[k] = load8(pa + k * nca * 512);
+            f0[k] = load8(pb + k * ncb * 512);
+            f1[k] = load8(pb + k * ncb * 512 + 512);
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            acc[0] = mma(fa[k], f0[k], acc[0]);
+            acc[1] = mma(fa[k], f1[k], acc[1]);
+        }
+        pa += U * nca * 512;
+        pb += U * ncb * 512;
+    });
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            out[(int64_t)(16 * ca + 4 * (lane >> 4) + i) * ldo + 16 * (cb + c) + (lane & 15)] =
+                acc[c][i];
+}
+
+// Every reduction over the rows, one task a wave: the partial weight
+// gradients of each chunk of kMlpSplitK rows, the column sums and the loss.
+// The sums keep one fixed order: residue r of the rows modulo 256 is summed
+// over its rows, then the 256 residues by a halving tree.
+__global__ void __launch_bounds__(MT) k_mlp_wgrad(MlpBuffers b, int64_t B, int nz,
+                                                  float *__restrict__ loss) {
+    const int lane = threadIdx.x & 63;
+    const int64_t task = (int64_t)blockIdx.x * MWAVES + (threadIdx.x >> 6);
+    const int64_t nb = (B + 31) / 32;  // row blocks of 32
+    if (task < kSumTasks) {
+        if (task == kSumTasks - 1) {  // mean loss; lane: residues 4 lane + j
+            float s[4] = {0.f, 0.f, 0.f, 0.f};
+            const float *p = b.row_loss + 4 * lane;
+            const int64_t full = max((B - 4 * lane) >> 2 << 2, (int64_t)0);  // whole quads
+            const int64_t n = (full + 255) / 256;
+            for_row_blocks(0, n, [&](auto uu) __attribute__((always_inline)) {
+                constexpr int U = decltype(uu)::value;
+                v4f v[U];
+#pragma unroll
+                for (int k = 0; k < U; ++k) v[k] = *(const v4f *)(p + 256 * k);
+#pragma unroll
+                for (int k = 0; k < U; ++k)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) s[j] += v[k][j];
+                p += 256 * U;
+            });
+            for (int j = 0; j < 3; ++j)  // the rows of a last partial quad
+                if (4 * lane + 256 * n + j < B) s[j] += p[j];
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) s[j] += __shfl_down(s[j], o, 64);
+            if (lane == 0) *loss = ((s[0] + s[2]) + (s[1] + s[3])) * (1.0f / (float)B);
+            return;
+        }
+        // columns 2 task and 2 task + 1 of [d1 | d2 | g3]; half a wave each, lane
+        // u of it: residues 8 u + j
+        const int col = 2 * (int)task + (lane >> 5), u = lane & 31;
+        float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (col <= 2 * H) {
+            // rows r .. r + 7 of the column, then 256 rows on (8 row blocks)
+            const int c = col & (H - 1);
+            const uint16_t *p = b.g3 + 8 * u;
+            int64_t step = 256;
+            if (col < 2 * H) {
+                p = (col < H ? b.d1 : b.d2) + ((int64_t)(u >> 2) * NT + (c >> 4)) * 512 +
+                    ((u & 3) * 16 + (c & 15)) * 8;
+                step = 8 * NT * 512;
+            }
+            const int64_t n = (32 * nb - 8 * u + 255) / 256;  // steps that hold rows
+            for_row_blocks(0, max(n, (int64_t)0), [&](auto uu) __attribute__((always_inline)) {
+                constexpr int U = decltype(uu)::value;
+                v8bf v[U];
+#pragma unroll
+                for (int k = 0; k < U; ++k) v[k] = load8(p + k * step);
+#pragma unroll
+                for (int k = 0; k < U; ++k)
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) s[j] += (float)v[k][j];
+                p += U * step;
+            });
+        }
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) s[j] += __shfl_down(s[j], o, 32);
+#pragma unroll
+        for (int o = 4; o > 0; o >>= 1)
+#pragma unroll
+            for (int j = 0; j < o; ++j) s[j] += s[j + o];
+        if (u == 0 && col <= 2 * H) b.bsum[col] = s[0];
+        return;
     }
-    if (threadIdx.x == 0) *out = red[0] * scale;
+    const int64_t q = task - kSumTasks, z = q / kChunkTasks;
+    if (z >= nz) return;
+    int k = (int)(q - z * kChunkTasks);
+    const int64_t rb0 = z * (kMlpSplitK / 32), rb1 = min(nb, rb0 + kMlpSplitK / 32);
+    float *part = b.part + z * kMlpPart;
+    if (k < kTasksW2) {
+        partial_pair(b.h1, NT, k / (NT / 2), b.d2, NT, 2 * (k % (NT / 2)), rb0, rb1,
+                     part + kPartW2, H, lane);
+        return;
+    }
+    k -= kTasksW2;
+    if (k < kTasksW1) {
+        partial_pair(b.a0, kMlpIn / 16, k / (NT / 2), b.d1, NT, 2 * (k % (NT / 2)), rb0, rb1, part,
+                     H, lane);
+        return;
+    }
+    k -= kTasksW1;
+    // dW3: two 16-row blocks of h2^T g3, in column 0
+    const v8bf zero8 = {};
+    v4f acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    const uint16_t *pg = b.g3 + rb0 * 32 + 8 * (lane >> 4);
+    const uint16_t *ph = b.h2 + (rb0 * NT + 2 * k) * 512 + lane * 8;
+    for_row_blocks(rb0, rb1, [&](auto u) __attribute__((always_inline)) {
+        constexpr int U = decltype(u)::value;
+        v8bf g[U], f0[U], f1[U];
+#pragma unroll
+        for (int r = 0; r < U; ++r) {
+            g[r] = load8(pg + r * 32);
+            f0[r] = load8(ph + r * NT * 512);
+            f1[r] = load8(ph + r * NT * 512 + 512);
+        }
+#pragma unroll
+        for (int r = 0; r < U; ++r) {
+            const v8bf f = (lane & 15) == 0 ? g[r] : zero8;
+            acc[0] = mma(f0[r], f, acc[0]);
+            acc[1] = mma(f1[r], f, acc[1]);
+        }
+        pg += U * 32;
+        ph += U * NT * 512;
+    });
+    if ((lane & 15) == 0)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                part[kPartW3 + 16 * (2 * k + c) + 4 * (lane >> 4) + i] = acc[c][i];
 }
 
-// out[j] = sum over kz of part[kz][j] (j < n), kz in order; column col of
-// a [rows][ld] partial when pick >= 0 (out[j] = sum part[kz][j * ld + pick]).
-__global__ void k_reduce_partials(const float *__restrict__ part, int nz, int64_t stride,
-                                  int64_t n, int64_t ld, int pick, float *__restrict__ out) {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
-    const int64_t o = pick >= 0 ? j * ld + pick : j;
+// Gradient of parameter i: its partials in chunk order, or its column sum.
+__device__ inline float gradient_of(const MlpBuffers &b, int i, int nz) {
+    if (i >= kMlpOffB1 && i < kMlpOffW2) return b.bsum[i - kMlpOffB1];
+    if (i >= kMlpOffB2 && i < kMlpOffW3) return b.bsum[H + i - kMlpOffB2];
+    if (i == kMlpOffB3) return b.bsum[2 * H];
+    const int o = i < kMlpOffB1   ? i
+                  : i < kMlpOffB2 ? kPartW2 + i - kMlpOffW2
+                                  : kPartW3 + i - kMlpOffW3;
     float s = 0.0f;
-    for (int z = 0; z < nz; ++z) s += part[(int64_t)z * stride + o];
-    out[j] = s;
+#pragma unroll 8
+    for (int z = 0; z < nz; ++z) s += b.part[(int64_t)z * kMlpPart + o];
+    return s;
 }
 
-// AdamW over the packed FP32 parameters; refreshes the bf16 working copies.
-__global__ void k_adamw(float *__restrict__ p, float *__restrict__ m, float *__restrict__ v,
-                        const float *__restrict__ g, int64_t n, float lr, float b1, float b2,
-                        float eps, float wd, float c1, float c2, MlpWeights w) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float pi = p[i] - lr * ((mi * c1) / (sqrtf(vi * c2) + eps) + wd * p[i]);
-    p[i] = pi;
-    mlp_store_working(w, i, pi);
+__global__ void k_mlp_gradient(MlpBuffers b, int nz, float *__restrict__ grad) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < kMlpParams) grad[i] = gradient_of(b, i, nz);
 }
 
-__global__ void k_refresh(const float *__restrict__ p, int64_t n, MlpWeights w) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) mlp_store_working(w, i, p[i]);
+// Gradient and AdamW over the packed FP32 parameters; refreshes the bf16
+// working copies.
+__global__ void k_mlp_update(MlpBuffers b, int nz, float lr, float b1, float b2, float eps,
+                             float wd, float c1, float c2) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= kMlpParams) return;
+    const float gi = gradient_of(b, i, nz);
+    const float mi = b1 * b.m[i] + (1.0f - b1) * gi;
+    const float vi = b2 * b.v[i] + (1.0f - b2) * gi * gi;
+    b.m[i] = mi;
+    b.v[i] = vi;
+    const float p0 = b.p[i];
+    const float pi = p0 - lr * ((mi * c1) / (sqrtf(vi * c2) + eps) + wd * p0);
+    b.p[i] = pi;
+    mlp_store_working(b.w, i, pi);
 }
 
-__global__ void k_pick_col0(const float *__restrict__ z16, int64_t n, float *__restrict__ out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = z16[i * 16];
+__global__ void k_refresh(MlpBuffers b) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < kMlpParams) mlp_store_working(b.w, i, b.p[i]);
 }
 
 inline unsigned nblk(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 
-template <int EPI>
-hipError_t gemm(const Gemm &g, int nz, hipStream_t s) {
-    const dim3 grid((unsigned)((g.N + 63) / 64), (unsigned)((g.M + 63) / 64), (unsigned)nz);
-    hipLaunchKernelGGL(k_gemm<EPI>, grid, dim3(GT), 0, s, g);
-    return hipGetLastError();
-}
+constexpr int64_t kMaxRowBlocks = 2048;  // workgroups of a pass over rows (they stride)
 
-Gemm mk(const uint16_t *A, int64_t sam, int64_t sak, const uint16_t *B, int64_t sbk, int64_t sbn,
-        int M, int N, int K, void *C, int64_t scm) {
-    Gemm g{};
-    g.A = A;
-    g.sam = sam;
-    g.sak = sak;
-    g.B = B;
-    g.sbk = sbk;
-    g.sbn = sbn;
-    g.M = M;
-    g.N = N;
-    g.K = K;
-    g.k_chunk = K;
-    g.C = C;
-    g.scm = scm;
-    return g;
+hipError_t launch_rows(const MlpBuffers &b, const float *x, const float *y, int64_t B, float pw,
+                       float *loss, hipStream_t s) {
+    const unsigned grid = (unsigned)min((int64_t)nblk(B, 32) * 2, kMaxRowBlocks);
+    hipLaunchKernelGGL(k_mlp_rows, dim3(grid), dim3(MT), 0, s, b, x, y, B, pw);
+    const int nz = (int)nblk(B, kMlpSplitK);
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3(nblk((int64_t)nz * kChunkTasks + kSumTasks, MWAVES)),
+                       dim3(MT), 0, s, b, B, nz, loss);
+    return hipGetLastError();
 }
 
 }  // namespace
 
-// Forward of rows [0, n) (n <= the buffers' batch): a0, h1, h2, z16.
-hipError_t mlp_forward(const MlpBuffers &b, const float *x, int64_t n, hipStream_t s) {
-    hipLaunchKernelGGL(k_norm_cast, dim3(nblk(n * 32, 256)), dim3(256), 0, s, x, n, b.mu, b.sd,
-                       b.a0);
-    Gemm g = mk(b.a0, kMlpIn, 1, b.w.w1, kMlpHidden, 1, (int)n, kMlpHidden, kMlpIn, b.h1,
-                kMlpHidden);
-    g.bias = b.p + kMlpOffB1;
-    hipError_t e = gemm<kEpiBiasReluBf16>(g, 1, s);
-    if (e != hipSuccess) return e;
-    g = mk(b.h1, kMlpHidden, 1, b.w.w2, kMlpHidden, 1, (int)n, kMlpHidden, kMlpHidden, b.h2,
-           kMlpHidden);
-    g.bias = b.p + kMlpOffB2;
-    if ((e = gemm<kEpiBiasReluBf16>(g, 1, s)) != hipSuccess) return e;
-    g = mk(b.h2, kMlpHidden, 1, b.w.w3, 16, 1, (int)n, 16, kMlpHidden, b.z16, 16);
-    g.bias = b.w.b3pad;
-    return gemm<kEpiBiasF32>(g, 1, s);
-}
-
 hipError_t mlp_logits(const MlpBuffers &b, const float *x, int64_t n, float *out, hipStream_t s) {
-    hipError_t e = mlp_forward(b, x, n, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_pick_col0, dim3(nblk(n, 256)), dim3(256), 0, s, b.z16, n, out);
+    // 64-row workgroups once there is one for every CU: up to 3e4 rows either
+    // form takes the 8.7 us of a launch; 65536 rows 8.8 us against 15.9 us,
+    // 2.3e5 rows 21 us against 46 us
+    if (n >= 64 * 256)
+        hipLaunchKernelGGL(k_mlp_forward<4>, dim3((unsigned)min((int64_t)(n + 63) / 64, (int64_t)768)),
+                           dim3(MT), 0, s, b, x, n, out);
+    else
+        hipLaunchKernelGGL(k_mlp_forward<1>, dim3(nblk(n, 16)), dim3(MT), 0, s, b, x, n, out);
     return hipGetLastError();
 }
 
 // Loss (mean) and gradient (packed like the parameters) of a batch of B rows.
 hipError_t mlp_grad(const MlpBuffers &b, const float *x, const float *y, int64_t B, float pw,
                     float *loss, float *grad, hipStream_t s) {
-    hipError_t e = mlp_forward(b, x, B, s);
+    hipError_t e = launch_rows(b, x, y, B, pw, loss, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_loss, dim3(nblk(B, 256)), dim3(256), 0, s, b.z16, y, B, pw, b.g3,
-                       b.row_loss);
-    hipLaunchKernelGGL(k_sum_f32, dim3(1), dim3(RT), 0, s, b.row_loss, B, 1.0f / (float)B, loss);
-    const int chunk = kMlpSplitK;
-    const int nz = (int)((B + chunk - 1) / chunk);
-    // dW3 = h2^T g3 (column 0 of a 128 x 16 product)
-    Gemm g = mk(b.h2, 1, kMlpHidden, b.g3, 16, 1, kMlpHidden, 16, (int)B, b.part, 16);
-    g.k_chunk = chunk;
-    if ((e = gemm<kEpiPartialF32>(g, nz, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_reduce_partials, dim3(nblk(kMlpHidden, 256)), dim3(256), 0, s, b.part, nz,
-                       (int64_t)kMlpHidden * 16, (int64_t)kMlpHidden, (int64_t)16, 0,
-                       grad + kMlpOffW3);
-    hipLaunchKernelGGL(k_colsum_bf16, dim3(1), dim3(RT), 0, s, b.g3, B, (int64_t)16,
-                       grad + kMlpOffB3);
-    // d2 = q((g3 q(W3)^T) [h2 > 0])
-    g = mk(b.g3, 16, 1, b.w.w3, 1, 16, (int)B, kMlpHidden, 16, b.d2, kMlpHidden);
-    g.mask = b.h2;
-    g.smm = kMlpHidden;
-    if ((e = gemm<kEpiMaskBf16>(g, 1, s)) != hipSuccess) return e;
-    // dW2 = h1^T d2, db2
-    g = mk(b.h1, 1, kMlpHidden, b.d2, kMlpHidden, 1, kMlpHidden, kMlpHidden, (int)B, b.part,
-           kMlpHidden);
-    g.k_chunk = chunk;
-    if ((e = gemm<kEpiPartialF32>(g, nz, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_reduce_partials, dim3(nblk(kMlpHidden * kMlpHidden, 256)), dim3(256), 0,
-                       s, b.part, nz, (int64_t)kMlpHidden * kMlpHidden,
-                       (int64_t)kMlpHidden * kMlpHidden, (int64_t)0, -1, grad + kMlpOffW2);
-    hipLaunchKernelGGL(k_colsum_bf16, dim3(kMlpHidden), dim3(RT), 0, s, b.d2, B,
-                       (int64_t)kMlpHidden, grad + kMlpOffB2);
-    // d1 = q((d2 q(W2)^T) [h1 > 0])
-    g = mk(b.d2, kMlpHidden, 1, b.w.w2, 1, kMlpHidden, (int)B, kMlpHidden, kMlpHidden, b.d1,
-           kMlpHidden);
-    g.mask = b.h1;
-    g.smm = kMlpHidden;
-    if ((e = gemm<kEpiMaskBf16>(g, 1, s)) != hipSuccess) return e;
-    // dW1 = a0^T d1, db1
-    g = mk(b.a0, 1, kMlpIn, b.d1, kMlpHidden, 1, kMlpIn, kMlpHidden, (int)B, b.part, kMlpHidden);
-    g.k_chunk = chunk;
-    if ((e = gemm<kEpiPartialF32>(g, nz, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_reduce_partials, dim3(nblk(kMlpIn * kMlpHidden, 256)), dim3(256), 0, s,
-                       b.part, nz, (int64_t)kMlpIn * kMlpHidden, (int64_t)kMlpIn * kMlpHidden,
-                       (int64_t)0, -1, grad + kMlpOffW1);
-    hipLaunchKernelGGL(k_colsum_bf16, dim3(kMlpHidden), dim3(RT), 0, s, b.d1, B,
-                       (int64_t)kMlpHidden, grad + kMlpOffB1);
+    hipLaunchKernelGGL(k_mlp_gradient, dim3(nblk(kMlpParams, 256)), dim3(256), 0, s, b,
+                       (int)nblk(B, kMlpSplitK), grad);
     return hipGetLastError();
 }
 
-hipError_t mlp_adamw(const MlpBuffers &b, const float *grad, float lr, float b1, float b2,
-                     float eps, float wd, float c1, float c2, hipStream_t s) {
-    hipLaunchKernelGGL(k_adamw, dim3(nblk(kMlpParams, 256)), dim3(256), 0, s, b.p, b.m, b.v, grad,
-                       (int64_t)kMlpParams, lr, b1, b2, eps, wd, c1, c2, b.w);
+hipError_t mlp_step(const MlpBuffers &b, const float *x, const float *y, int64_t B, float pw,
+                    float *loss, float lr, float b1, float b2, float eps, float wd, float c1,
+                    float c2, hipStream_t s) {
+    hipError_t e = launch_rows(b, x, y, B, pw, loss, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_mlp_update, dim3(nblk(kMlpParams, 256)), dim3(256), 0, s, b,
+                       (int)nblk(B, kMlpSplitK), lr, b1, b2, eps, wd, c1, c2);
     return hipGetLastError();
 }
 
 hipError_t mlp_refresh(const MlpBuffers &b, hipStream_t s) {
-    hipLaunchKernelGGL(k_refresh, dim3(nblk(kMlpParams, 256)), dim3(256), 0, s, b.p,
-                       (int64_t)kMlpParams, b.w);
+    hipLaunchKernelGGL(k_refresh, dim3(nblk(kMlpParams, 256)), dim3(256), 0, s, b);
     return hipGetLastError();
 }
 

@@ -71,19 +71,19 @@ sas_status sas_mlp_create(int64_t max_batch, uint64_t seed, sas_mlp **out) {
     std::unique_ptr<sas_mlp> m(new sas_mlp());
     m->max_batch = max_batch;
     m->seed = seed;
-    const size_t B = (size_t)max_batch, H = kMlpHidden;
+    const size_t B = (size_t)(max_batch + 31) / 32 * 32, H = kMlpHidden;
     const size_t nz = (size_t)((max_batch + kMlpSplitK - 1) / kMlpSplitK);
     MlpBuffers &b = m->b;
     bool ok = dalloc(m.get(), &b.p, kMlpParams) && dalloc(m.get(), &b.m, kMlpParams) &&
-              dalloc(m.get(), &b.v, kMlpParams) && dalloc(m.get(), &b.grad, kMlpParams) &&
+              dalloc(m.get(), &b.v, kMlpParams) &&
               dalloc(m.get(), &b.w.w1, kMlpIn * H) && dalloc(m.get(), &b.w.w2, H * H) &&
-              dalloc(m.get(), &b.w.w3, H * 16) && dalloc(m.get(), &b.w.b3pad, 16) &&
+              dalloc(m.get(), &b.w.w2t, H * H) && dalloc(m.get(), &b.w.w3, H) &&
               dalloc(m.get(), &b.mu, kMlpIn) && dalloc(m.get(), &b.sd, kMlpIn) &&
               dalloc(m.get(), &b.a0, B * kMlpIn) && dalloc(m.get(), &b.h1, B * H) &&
               dalloc(m.get(), &b.h2, B * H) && dalloc(m.get(), &b.d1, B * H) &&
-              dalloc(m.get(), &b.d2, B * H) && dalloc(m.get(), &b.z16, B * 16) &&
-              dalloc(m.get(), &b.g3, B * 16) && dalloc(m.get(), &b.row_loss, B) &&
-              dalloc(m.get(), &b.part, nz * H * H);
+              dalloc(m.get(), &b.d2, B * H) && dalloc(m.get(), &b.g3, B) &&
+              dalloc(m.get(), &b.row_loss, B) && dalloc(m.get(), &b.part, nz * kMlpPart) &&
+              dalloc(m.get(), &b.bsum, 2 * H + 1);
     if (!ok) {
         for (void *a : m->allocs) hipFree(a);
         return mfail(SAS_E_NOMEM, "sas_mlp_create: device memory");
@@ -223,11 +223,10 @@ sas_status sas_mlp_forward(const sas_mlp *m, const float *x_dev, int64_t n, floa
                            void *stream) {
     if (!m || n < 0 || (n > 0 && (!x_dev || !logits_dev)))
         return mfail(SAS_E_INVALID, "sas_mlp_forward: bad argument");
-    for (int64_t r0 = 0; r0 < n; r0 += m->max_batch) {
-        const int64_t k = std::min(m->max_batch, n - r0);
-        hipError_t e = mlp_logits(m->b, x_dev + r0 * kMlpIn, k, logits_dev + r0, (hipStream_t)stream);
-        if (e != hipSuccess) return mfail(SAS_E_DEVICE, std::string("sas_mlp_forward: ") + hipGetErrorString(e));
-    }
+    if (n == 0) return SAS_OK;
+    // one pass over any number of rows: it keeps nothing outside registers and LDS
+    hipError_t e = mlp_logits(m->b, x_dev, n, logits_dev, (hipStream_t)stream);
+    if (e != hipSuccess) return mfail(SAS_E_DEVICE, std::string("sas_mlp_forward: ") + hipGetErrorString(e));
     return SAS_OK;
 }
 
@@ -247,13 +246,13 @@ sas_status sas_mlp_train_step(sas_mlp *m, const float *x_dev, const float *y_dev
     if (!m || batch < 1 || batch > m->max_batch || !x_dev || !y_dev || !loss_dev)
         return mfail(SAS_E_INVALID, "sas_mlp_train_step: bad argument (batch in [1, max_batch])");
     hipStream_t s = (hipStream_t)stream;
-    hipError_t e = mlp_grad(m->b, x_dev, y_dev, batch, pos_weight, loss_dev, m->b.grad, s);
+    const int64_t step = m->step + 1;
+    const double c1 = 1.0 / (1.0 - std::pow((double)beta1, (double)step));
+    const double c2 = 1.0 / (1.0 - std::pow((double)beta2, (double)step));
+    hipError_t e = mlp_step(m->b, x_dev, y_dev, batch, pos_weight, loss_dev, lr, beta1, beta2, eps,
+                            weight_decay, (float)c1, (float)c2, s);
     if (e != hipSuccess) return mfail(SAS_E_DEVICE, std::string("sas_mlp_train_step: ") + hipGetErrorString(e));
-    m->step += 1;
-    const double c1 = 1.0 / (1.0 - std::pow((double)beta1, (double)m->step));
-    const double c2 = 1.0 / (1.0 - std::pow((double)beta2, (double)m->step));
-    e = mlp_adamw(m->b, m->b.grad, lr, beta1, beta2, eps, weight_decay, (float)c1, (float)c2, s);
-    if (e != hipSuccess) return mfail(SAS_E_DEVICE, std::string("sas_mlp_train_step: ") + hipGetErrorString(e));
+    m->step = step;
     return SAS_OK;
 }
 
