@@ -13,10 +13,25 @@
 // stops changing.
 //
 // One workgroup per cluster (grid-stride over clusters).  The point set
-// (at most kMaxPoints) lives in LDS as t (h since t0), x, y (px) in FP64;
-// the eight waves take the starts; a C-step ranks the distances exactly
-// (each point counts the points before it, ties to the lower position), so
-// the chosen subset does not depend on any reduction order.
+// (at most kMaxPoints) lives in LDS as t (h since t0), x, y (px) in FP64.
+// The starts of FAST-MCD are independent, and their C-steps are nearly all
+// the arithmetic.  A start takes one row of 16 lanes (4 starts a wave, 64 a
+// workgroup; a whole wave above 128 points); a lane holds every 16th (64th)
+// point in registers.  The sums cross the row by data-parallel primitive
+// moves, the six or three divisions of a C-step are made by six or three
+// lanes at once, and the h closest points come from a bisection on the upper
+// 32 bits of the distances (ordered as integers), which ends as soon as a
+// bound separates h points: about 12 passes of two instructions a point.
+// Points whose upper bits tie across that bound are taken in the exact order
+// (distance, position), so the subset is that of a full sort.  The sums keep
+// the order of a butterfly over 64 lanes for every L, so a fit's bits do not
+// depend on the form.  The kernel is bound by vector instructions (about 800
+// a C-step of 4 starts at 64 points, half of them FP64) and by the rounds of
+// the slowest cluster, which follow one another.
+//   With one start a wave, ranks by comparing all pairs through LDS and
+// reductions by LDS permutes, the 160 clusters of a fast chip (500 starts)
+// took 8.0 ms, now 0.64 ms (1.5 ms before rounds that repeat were
+// recognised).
 //
 // Rules shared with the reference definition: a point set is ordered by
 // catalog index; h = (n + 4) / 2; a start whose 4 points repeat, or whose
@@ -30,11 +45,11 @@
 namespace sas {
 namespace {
 
-constexpr int RT = 512;             // threads per cluster workgroup
+constexpr int RT = 1024;            // threads per cluster workgroup
 constexpr int RW = RT / 64;
 constexpr int kMaxPoints = 512;     // points of one set held in LDS
 constexpr int kMaskWords = kMaxPoints / 32;
-constexpr int kPtsPerLane = kMaxPoints / 64;  // the wave's points per lane, at most
+constexpr int kRowLanes = 16;
 constexpr int kBest = 10;
 constexpr int kMaxCsteps = 30;
 constexpr int kMaxRounds = 10;
@@ -55,7 +70,37 @@ __device__ inline bool degenerate(const double *s) {
     return det3(s) <= kDegenerate * s[0] * s[3] * s[5];
 }
 
-// Inverse of the symmetric 3x3 matrix s (same layout), by cofactors.
+// Moves within a row of 16 lanes.
+template <int CTRL>
+__device__ inline int32_t dpp(int32_t v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false);
+}
+template <int CTRL>
+__device__ inline double dpp(double v) {
+    return __hiloint2double(dpp<CTRL>(__double2hiint(v)), dpp<CTRL>(__double2loint(v)));
+}
+constexpr int kRor8 = 0x128, kRor4 = 0x124, kXor2 = 0x4e, kXor1 = 0xb1;  // 0x4e: quad 2,3,0,1
+constexpr int kBcast = 0x150;                                            // row broadcast of lane n
+// Sum over the row, in every lane: lanes l and l ^ 8 are added, then ^ 4, 2, 1
+// (after the first step the values repeat with period 8, so a rotation by 4
+// brings lane l ^ 4's).
+template <class T>
+__device__ inline T row_sum(T v) {
+    v += dpp<kRor8>(v);
+    v += dpp<kRor4>(v);
+    v += dpp<kXor2>(v);
+    return v + dpp<kXor1>(v);
+}
+__device__ inline uint32_t row_min(uint32_t v) {
+    v = min(v, (uint32_t)dpp<kRor8>((int32_t)v));
+    v = min(v, (uint32_t)dpp<kRor4>((int32_t)v));
+    v = min(v, (uint32_t)dpp<kXor2>((int32_t)v));
+    return min(v, (uint32_t)dpp<kXor1>((int32_t)v));
+}
+__device__ inline uint32_t row_max(uint32_t v) { return ~row_min(~v); }
+
+// Inverse of the symmetric 3x3 matrix s (same layout), by cofactors; lane q
+// of the row divides the q-th.
 __device__ inline void inv3(const double *s, double *v) {
     const double c00 = s[3] * s[5] - s[4] * s[4];
     const double c01 = s[2] * s[4] - s[1] * s[5];
@@ -64,26 +109,30 @@ __device__ inline void inv3(const double *s, double *v) {
     const double c12 = s[1] * s[2] - s[0] * s[4];
     const double c22 = s[0] * s[3] - s[1] * s[1];
     const double d = s[0] * c00 + s[1] * c01 + s[2] * c02;
-    v[0] = c00 / d;
-    v[1] = c01 / d;
-    v[2] = c02 / d;
-    v[3] = c11 / d;
-    v[4] = c12 / d;
-    v[5] = c22 / d;
-}
-
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    const int q = __lane_id() & (kRowLanes - 1);
+    double c = c00;
+    c = q == 1 ? c01 : c;
+    c = q == 2 ? c02 : c;
+    c = q == 3 ? c11 : c;
+    c = q == 4 ? c12 : c;
+    c = q == 5 ? c22 : c;
+    c /= d;
+    v[0] = dpp<kBcast + 0>(c);
+    v[1] = dpp<kBcast + 1>(c);
+    v[2] = dpp<kBcast + 2>(c);
+    v[3] = dpp<kBcast + 3>(c);
+    v[4] = dpp<kBcast + 4>(c);
+    v[5] = dpp<kBcast + 5>(c);
 }
 
 struct Shared {
     double zt[kMaxPoints], zx[kMaxPoints], zy[kMaxPoints];
-    double d2[RW][kMaxPoints];
     double dets[kMaxRefineStarts];
-    int32_t cur[kMaxPoints];  // catalog indices of the current set, ascending
-    int32_t nxt[kMaxPoints];  // gathered set
+    // round r fits set r - 1 and gathers set r (catalog indices, ascending)
+    int32_t sets[kMaxRounds + 1][kMaxPoints];
+    int32_t n_set[kMaxRounds + 1];
+    sas_refined fit[kMaxRounds];               // of round r at r - 1
+    uint32_t subset[kMaxRounds][kMaskWords];   // its MCD subset of set r - 1
     int32_t tmp[kMaxPoints];
     uint32_t mask[kBest][kMaskWords];
     Cov cov[kBest];
@@ -92,132 +141,222 @@ struct Shared {
     int32_t n_top, n_nxt, overflow;
 };
 
-// Mean and covariance of the points whose flag is set (lane-held flags of
-// points lane + 64 k), by the wave; all lanes get the result.
-template <int KPL>
-__device__ Cov wave_moments(const Shared &sh, int n, const bool *in, int cnt) {
-    const int lane = __lane_id();
-    Cov c;
-    double a0 = 0, a1 = 0, a2 = 0;
-#pragma unroll
-    for (int k = 0; k < KPL; ++k) {
-        const int i = lane + 64 * k;
-        if (i < n && in[k]) {
-            a0 += sh.zt[i];
-            a1 += sh.zx[i];
-            a2 += sh.zy[i];
-        }
+// A start's lanes: L = 16 (a row) or 64 (the wave).
+template <int L, class T>
+__device__ inline T lanes_sum(T v) {
+    if (L == 64) {
+        v += __shfl_xor(v, 32, 64);
+        v += __shfl_xor(v, 16, 64);
     }
-    c.mu[0] = wave_sum(a0) / cnt;
-    c.mu[1] = wave_sum(a1) / cnt;
-    c.mu[2] = wave_sum(a2) / cnt;
-    double s[6] = {0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int k = 0; k < KPL; ++k) {
-        const int i = lane + 64 * k;
-        if (i < n && in[k]) {
-            const double dt = sh.zt[i] - c.mu[0], dx = sh.zx[i] - c.mu[1], dy = sh.zy[i] - c.mu[2];
-            s[0] += dt * dt;
-            s[1] += dt * dx;
-            s[2] += dt * dy;
-            s[3] += dx * dx;
-            s[4] += dx * dy;
-            s[5] += dy * dy;
-        }
+    return row_sum(v);
+}
+template <int L>
+__device__ inline uint32_t lanes_min(uint32_t v) {
+    v = row_min(v);
+    if (L == 64) {
+        v = min(v, (uint32_t)__shfl_xor((int32_t)v, 16, 64));
+        v = min(v, (uint32_t)__shfl_xor((int32_t)v, 32, 64));
     }
-#pragma unroll
-    for (int q = 0; q < 6; ++q) c.s[q] = wave_sum(s[q]) / cnt;
-    return c;
+    return v;
 }
 
-// One C-step by the wave: distances from (mu, S^-1) into its d2 row, then
-// in[k] = point lane + 64 k is among the h closest (ties to the lower
-// position).  Returns whether the subset changed.
-template <int KPL>
-__device__ bool c_step(Shared &sh, int n, int h, const Cov &c, bool *in) {
-    const int lane = __lane_id(), wave = threadIdx.x >> 6;
+// The lane's points i = r + L k, k < P, with r = lane % L (L P >= n).
+template <int L, int P>
+struct Points {
+    int n, r;
+    double t[P], x[P], y[P];
+    __device__ Points(const Shared &sh, int n_) : n(n_), r(__lane_id() & (L - 1)) {
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            t[k] = sh.zt[r + L * k];
+            x[k] = sh.zx[r + L * k];
+            y[k] = sh.zy[r + L * k];
+        }
+    }
+};
+
+// Partial sums of a lane of A, combined as a butterfly over 64 lanes with
+// every 64th point each would: sums over every 64th point, then halves 32 and
+// 16 apart (L = 16: within the lane), then the row.
+template <int A>
+__device__ __attribute__((always_inline)) inline double fold(const double *a) {
+    return A == 1 ? a[0] : A == 2 ? a[0] + a[1] : (a[0] + a[2]) + (a[1] + a[3]);
+}
+
+// Mean and covariance of the points whose bit is set in `in`, cnt of them;
+// every lane of the start gets the result.
+template <int L, int P>
+__device__ __attribute__((always_inline)) inline void moments(const Points<L, P> &pt, uint32_t in,
+                                                              int cnt, Cov &c) {
+    constexpr int A = L == 64 ? 1 : P < 4 ? P : 4;
+    const int q = __lane_id() & (kRowLanes - 1);
+    const double n = (double)cnt;
+    double a0[A] = {}, a1[A] = {}, a2[A] = {};
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        const bool on = (in >> k) & 1u;
+        a0[k % A] += on ? pt.t[k] : 0.0;
+        a1[k % A] += on ? pt.x[k] : 0.0;
+        a2[k % A] += on ? pt.y[k] : 0.0;
+    }
+    const double m0 = lanes_sum<L>(fold<A>(a0)), m1 = lanes_sum<L>(fold<A>(a1)),
+                 m2 = lanes_sum<L>(fold<A>(a2));
+    double m = m0;
+    m = q == 1 ? m1 : m;
+    m = q == 2 ? m2 : m;
+    m /= n;
+    c.mu[0] = dpp<kBcast + 0>(m);
+    c.mu[1] = dpp<kBcast + 1>(m);
+    c.mu[2] = dpp<kBcast + 2>(m);
+    double s[6][A] = {};
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        const bool on = (in >> k) & 1u;
+        const double dt = on ? pt.t[k] - c.mu[0] : 0.0, dx = on ? pt.x[k] - c.mu[1] : 0.0,
+                     dy = on ? pt.y[k] - c.mu[2] : 0.0;
+        s[0][k % A] += dt * dt;
+        s[1][k % A] += dt * dx;
+        s[2][k % A] += dt * dy;
+        s[3][k % A] += dx * dx;
+        s[4][k % A] += dx * dy;
+        s[5][k % A] += dy * dy;
+    }
+    double v = 0.0;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        const double w = lanes_sum<L>(fold<A>(s[j]));
+        v = q == j ? w : v;
+    }
+    v /= n;
+    c.s[0] = dpp<kBcast + 0>(v);
+    c.s[1] = dpp<kBcast + 1>(v);
+    c.s[2] = dpp<kBcast + 2>(v);
+    c.s[3] = dpp<kBcast + 3>(v);
+    c.s[4] = dpp<kBcast + 4>(v);
+    c.s[5] = dpp<kBcast + 5>(v);
+}
+
+// The h points closest to c.mu in the metric of the inverse of c.s (ties to
+// the lower position), as bits of the lane's points.  Starts with live =
+// false get no meaningful result.  All lanes of the wave call.
+template <int L, int P>
+__device__ __attribute__((always_inline)) inline uint32_t c_step(const Points<L, P> &pt, int h,
+                                                                 const Cov &c, bool live) {
     double v[6];
     inv3(c.s, v);
-    double *d2 = sh.d2[wave];
+    const auto dist = [&](int k) __attribute__((always_inline)) {
+        const double a = pt.t[k] - c.mu[0], b = pt.x[k] - c.mu[1], e = pt.y[k] - c.mu[2];
+        // + 0.0: a zero distance has one sign
+        return a * (v[0] * a + v[1] * b + v[2] * e) + b * (v[1] * a + v[3] * b + v[4] * e) +
+               e * (v[2] * a + v[4] * b + v[5] * e) + 0.0;
+    };
+    // upper halves of the distances, as integers in the same order; points
+    // past the set above every bound
+    uint32_t key[P], lo = 0xffffffffu, hi = 0;
 #pragma unroll
-    for (int k = 0; k < KPL; ++k) {
-        const int i = lane + 64 * k;
-        if (i < n) {
-            const double a = sh.zt[i] - c.mu[0], b = sh.zx[i] - c.mu[1], e = sh.zy[i] - c.mu[2];
-            d2[i] = a * (v[0] * a + v[1] * b + v[2] * e) + b * (v[1] * a + v[3] * b + v[4] * e) +
-                    e * (v[2] * a + v[4] * b + v[5] * e);
-        }
+    for (int k = 0; k < P; ++k) {
+        const int32_t w = __double2hiint(dist(k));
+        const bool on = pt.r + L * k < pt.n;
+        key[k] = on ? (uint32_t)w ^ ((uint32_t)(w >> 31) | 0x80000000u) : 0xffffffffu;
+        lo = min(lo, key[k]);
+        hi = max(hi, on ? key[k] : 0u);
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    int rank[KPL];
-    double mine[KPL];
+    // bisection: fewer than h keys below lo, at least h below hi; a start ends
+    // at a bound with exactly h below it, or with hi = lo + 1 (a tie)
+    lo = lanes_min<L>(lo);
+    hi = ~lanes_min<L>(~hi) + 1;
+    uint32_t bound = 0;
+    bool done = !live;
+    for (;;) {
+        const bool on = !done && hi - lo > 1u;
+        if (!__any(on)) break;
+        const uint32_t mid = lo + ((hi - lo) >> 1);
+        int32_t below = 0;
 #pragma unroll
-    for (int k = 0; k < KPL; ++k) {
-        rank[k] = 0;
-        mine[k] = (lane + 64 * k < n) ? d2[lane + 64 * k] : 0.0;
-    }
-    // blocks of U distances loaded before they are compared (the loads of a
-    // block are in flight together; fewer when each lane holds many points)
-    constexpr int U = KPL <= 2 ? 8 : 2;
-    int j = 0;
-    for (; j + U <= n; j += U) {
-        double dj[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) dj[u] = d2[j + u];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int k = 0; k < KPL; ++k) {
-                const int i = lane + 64 * k;
-                rank[k] += (dj[u] < mine[k] || (dj[u] == mine[k] && j + u < i)) ? 1 : 0;
+        for (int k = 0; k < P; ++k) below += key[k] < mid ? 1 : 0;
+        below = lanes_sum<L>(below);
+        if (on) {
+            if (below == h) {
+                bound = mid;
+                done = true;
+            } else if (below < h) {
+                lo = mid;
+            } else {
+                hi = mid;
             }
-    }
-    for (; j < n; ++j) {
-        const double dj = d2[j];
-#pragma unroll
-        for (int k = 0; k < KPL; ++k) {
-            const int i = lane + 64 * k;
-            rank[k] += (dj < mine[k] || (dj == mine[k] && j < i)) ? 1 : 0;
         }
     }
-    bool changed = false;
+    uint32_t in = 0;
+    const uint32_t cut = done ? bound : lo;
 #pragma unroll
-    for (int k = 0; k < KPL; ++k) {
-        const bool nin = lane + 64 * k < n && rank[k] < h;
-        changed |= nin != in[k];
-        in[k] = nin;
+    for (int k = 0; k < P; ++k) in |= key[k] < cut ? 1u << k : 0u;
+    if (__any(!done)) {
+        // points tied at lo: the first ones by (distance, position)
+        uint32_t tied = 0;
+        int32_t need = 0;
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            tied |= !done && key[k] == lo && pt.r + L * k < pt.n ? 1u << k : 0u;
+            need += key[k] < lo ? 1 : 0;
+        }
+        need = h - lanes_sum<L>(need);
+        need = done ? 0 : need;
+        constexpr int32_t kNone = kMaxPoints;
+        while (__any(need > 0)) {
+            double bd = 0.0;
+            int32_t bi = kNone;
+#pragma unroll
+            for (int k = 0; k < P; ++k) {
+                const double d = dist(k);
+                if (((tied >> k) & 1u) && (bi == kNone || d < bd)) {
+                    bd = d;
+                    bi = pt.r + L * k;
+                }
+            }
+#pragma unroll
+            for (int o = L / 2; o > 0; o >>= 1) {
+                const double od = __shfl_xor(bd, o, 64);
+                const int32_t oi = __shfl_xor(bi, o, 64);
+                if (oi != kNone && (bi == kNone || od < bd || (od == bd && oi < bi))) {
+                    bd = od;
+                    bi = oi;
+                }
+            }
+            if (bi == kNone) {
+                need = 0;  // not reached: a start holds more tied points than it needs
+            } else if (need > 0) {
+                --need;
+                if (bi % L == pt.r) {
+                    in |= 1u << (bi / L);
+                    tied &= ~(1u << (bi / L));
+                }
+            }
+        }
     }
-    __builtin_amdgcn_wave_barrier();  // d2 is read before the next step writes it
-    return __any(changed);
+    return in;
 }
 
-// The first two C-steps of start s (both phases take this same path); the
-// subset flags and its moments on return.  False when the start is dropped.
-template <int KPL>
-__device__ bool start_steps(Shared &sh, int n, int h, const uint32_t *starts, int s, bool *in,
-                            Cov &c) {
-    const int lane = __lane_id();
-    int j[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) j[q] = (int)(starts[4 * s + q] % (uint32_t)n);
-    for (int a = 0; a < 4; ++a)
-        for (int b = a + 1; b < 4; ++b)
-            if (j[a] == j[b]) return false;
-    // mean and covariance of the 4 points (every lane computes them)
+// Mean and covariance of the 4 points of start s, by every lane of the start.
+// False when the start is dropped.
+__device__ __attribute__((always_inline)) inline bool start_cov(const Shared &sh, int n,
+                                                                const uint32_t *starts, int s,
+                                                                Cov &c) {
+    const int32_t jq = (int32_t)(starts[4 * s + (__lane_id() & 3)] % (uint32_t)n);
+    const int j[4] = {dpp<0x00>(jq), dpp<0x55>(jq), dpp<0xaa>(jq), dpp<0xff>(jq)};  // of the quad
     double mu[3] = {0, 0, 0};
+#pragma unroll
     for (int q = 0; q < 4; ++q) {
         mu[0] += sh.zt[j[q]];
         mu[1] += sh.zx[j[q]];
         mu[2] += sh.zy[j[q]];
     }
-    Cov c0;
-    for (int r = 0; r < 3; ++r) c0.mu[r] = mu[r] / 4;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) c.mu[r] = mu[r] / 4;
     double s6[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const double dt = sh.zt[j[q]] - c0.mu[0], dx = sh.zx[j[q]] - c0.mu[1],
-                     dy = sh.zy[j[q]] - c0.mu[2];
+        const double dt = sh.zt[j[q]] - c.mu[0], dx = sh.zx[j[q]] - c.mu[1],
+                     dy = sh.zy[j[q]] - c.mu[2];
         s6[0] += dt * dt;
         s6[1] += dt * dx;
         s6[2] += dt * dy;
@@ -225,100 +364,129 @@ __device__ bool start_steps(Shared &sh, int n, int h, const uint32_t *starts, in
         s6[4] += dx * dy;
         s6[5] += dy * dy;
     }
-    for (int q = 0; q < 6; ++q) c0.s[q] = s6[q] / 4;
-    if (degenerate(c0.s)) return false;
 #pragma unroll
-    for (int k = 0; k < KPL; ++k) in[k] = false;
-    c_step<KPL>(sh, n, h, c0, in);  // 4 points -> h points
-    c = wave_moments<KPL>(sh, n, in, h);
-    if (!degenerate(c.s) && c_step<KPL>(sh, n, h, c, in)) c = wave_moments<KPL>(sh, n, in, h);
-    (void)lane;
-    return true;
+    for (int q = 0; q < 6; ++q) c.s[q] = s6[q] / 4;
+    return j[0] != j[1] && j[0] != j[2] && j[0] != j[3] && j[1] != j[2] && j[1] != j[3] &&
+           j[2] != j[3] && !degenerate(c.s);
 }
 
-// Ascending sort of a[0, m) (distinct or not) into out by rank counting.
-__device__ void sort_into(const int32_t *a, int m, int32_t *out) {
+// Ascending sort of a[0, m) (distinct or not) into out by rank counting.  a
+// is padded to a multiple of 4; ends with a barrier.
+__device__ void sort_into(int32_t *a, int m, int32_t *out) {
+    const int m4 = (m + 3) & ~3;
+    if ((int)threadIdx.x < m4 - m) a[m + threadIdx.x] = INT32_MAX;  // above every index
+    __syncthreads();
     for (int i = threadIdx.x; i < m; i += RT) {
         const int32_t v = a[i];
         int r = 0;
-        for (int j = 0; j < m; ++j) r += (a[j] < v || (a[j] == v && j < i)) ? 1 : 0;
+        for (int j = 0; j < m4; j += 4) {
+            const int4 w = *(const int4 *)(a + j);
+            r += (w.x < v || (w.x == v && j < i)) ? 1 : 0;
+            r += (w.y < v || (w.y == v && j + 1 < i)) ? 1 : 0;
+            r += (w.z < v || (w.z == v && j + 2 < i)) ? 1 : 0;
+            r += (w.w < v || (w.w == v && j + 3 < i)) ? 1 : 0;
+        }
         out[r] = v;
     }
+    __syncthreads();
 }
 
-// FAST-MCD on the n points in LDS (KPL >= ceil(n / 64) points per lane):
-// the first stage scores every start by the determinant after two C-steps,
-// the kBest lowest (ties to the earlier start) are iterated until the subset
-// holds; their subsets, moments and determinants are left in sh.
-template <int KPL>
-__device__ void mcd_stages(Shared &sh, const RefineArgs &a, int n, int h) {
-    const int tid = threadIdx.x, lane = __lane_id(), wave = tid >> 6;
-    (void)tid;
-    // FAST-MCD, first stage: two C-steps from every start
-    for (int s = wave; s < a.n_starts; s += RW) {
-        bool in[KPL];
-        Cov cv;
-        const bool ok = start_steps<KPL>(sh, n, h, a.starts, s, in, cv);
-        if (lane == 0) sh.dets[s] = ok ? det3(cv.s) : INFINITY;
-    }
-    __syncthreads();
-    if (wave == 0) {  // the kBest lowest (det, start)
-        int nt = 0;
-        double last_d = -INFINITY;
-        int last_s = -1;
-        for (; nt < kBest; ++nt) {
-            double bd = INFINITY;
-            int bs = -1;
-            for (int s = lane; s < a.n_starts; s += 64) {
-                const double d = sh.dets[s];
-                const bool after = d > last_d || (d == last_d && s > last_s);
-                if (after && d != INFINITY && (d < bd || (d == bd && s < bs) || bs < 0)) {
-                    bd = d;
-                    bs = s;
-                }
+// The kBest lowest (determinant, start) of sh.dets, by one wave.
+__device__ void best_starts(Shared &sh, int n_starts) {
+    const int lane = __lane_id();
+    constexpr int kHeld = kMaxRefineStarts / 64;
+    double d[kHeld];
+#pragma unroll
+    for (int k = 0; k < kHeld; ++k)
+        d[k] = lane + 64 * k < n_starts ? sh.dets[lane + 64 * k] : INFINITY;
+    int nt = 0;
+#pragma unroll 1
+    for (; nt < kBest; ++nt) {
+        double bd = INFINITY;  // of equal determinants the earlier start
+        int bs = kMaxRefineStarts;
+#pragma unroll
+        for (int k = 0; k < kHeld; ++k)
+            if (d[k] < bd) {
+                bd = d[k];
+                bs = lane + 64 * k;
             }
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                const double od = __shfl_xor(bd, o, 64);
-                const int os = __shfl_xor(bs, o, 64);
-                if (os >= 0 && (bs < 0 || od < bd || (od == bd && os < bs))) {
-                    bd = od;
-                    bs = os;
-                }
+        for (int o = 32; o > 0; o >>= 1) {
+            const double od = __shfl_xor(bd, o, 64);
+            const int os = __shfl_xor(bs, o, 64);
+            if (od < bd || (od == bd && os < bs)) {
+                bd = od;
+                bs = os;
             }
-            if (bs < 0) break;
-            if (lane == 0) sh.top[nt] = bs;
-            last_d = bd;
-            last_s = bs;
         }
-        if (lane == 0) sh.n_top = nt;
+        if (bs == kMaxRefineStarts) break;
+        if (lane == 0) sh.top[nt] = bs;
+#pragma unroll
+        for (int k = 0; k < kHeld; ++k)
+            if (lane + 64 * k == bs) d[k] = INFINITY;
     }
-    __syncthreads();
-    const int n_top = sh.n_top;
-    // second stage: the best starts iterated until the subset holds
-    for (int k = wave; k < n_top; k += RW) {
-        bool in[KPL];
-        Cov cv;
-        start_steps<KPL>(sh, n, h, a.starts, sh.top[k], in, cv);
-        for (int it = 0; it < kMaxCsteps; ++it) {
-            if (degenerate(cv.s)) break;
-            if (!c_step<KPL>(sh, n, h, cv, in)) break;
-            cv = wave_moments<KPL>(sh, n, in, h);
+    if (lane == 0) sh.n_top = nt;
+}
+
+// One stage of FAST-MCD on the n points in LDS (L P >= n).  Stage 0 scores
+// every start by the determinant after two C-steps; stage 1 iterates the
+// kBest lowest (sh.top; ties to the earlier start) until the subset holds,
+// from the start again and one a wave, and leaves their subsets, moments and
+// determinants in sh.
+template <int L, int P>
+__device__ __attribute__((always_inline)) inline void mcd_stage(Shared &sh, const RefineArgs &a,
+                                                                int n, int h, int stage) {
+    const int lane = __lane_id(), wave = threadIdx.x >> 6;
+    constexpr int kStarts = 64 / L;  // starts a wave works on at once
+    const Points<L, P> pt(sh, n);
+    const int n_tasks = stage ? sh.n_top : a.n_starts;
+    const int per_wave = stage ? 1 : kStarts;
+    for (int t0 = wave * per_wave; t0 < n_tasks; t0 += RW * per_wave) {
+        // the last start again past the end
+        const int t = stage ? t0 : min(t0 + lane / L, n_tasks - 1);
+        const int s = stage ? sh.top[t] : t;
+        Cov c;
+        const bool ok = start_cov(sh, n, a.starts, s, c);
+        // the 4 points' step, the second, and kMaxCsteps more in stage 1; a
+        // degenerate covariance or an unchanged subset ends a start
+        uint32_t in = 0;
+        bool on = ok;
+        const int steps = stage ? 2 + kMaxCsteps : 2;
+#pragma unroll 1
+        for (int it = 0; it < steps; ++it) {
+            if (it) on = on && !degenerate(c.s);
+            if (!__any(on)) break;
+            const uint32_t next = c_step<L, P>(pt, h, c, on);
+            if (it) {
+                const uint64_t moved = __ballot(next != in);
+                on = on && (L == 64 ? moved : (moved >> (lane & ~(L - 1))) & 0xffffu) != 0;
+            }
+            if (!__any(on)) break;
+            in = on ? next : in;
+            // the same moments again for starts that have ended
+            moments<L, P>(pt, in, h, c);
+        }
+        if (stage == 0) {
+            if (pt.r == 0) sh.dets[s] = ok ? det3(c.s) : INFINITY;
+            continue;
         }
 #pragma unroll
-        for (int q = 0; q < kPtsPerLane; ++q) {
-            const uint64_t b = q < KPL ? __ballot(in[q < KPL ? q : 0]) : 0;
+        for (int k = 0; k < kMaxPoints / L; k += L == 64 ? 1 : 2) {
+            uint64_t w = k < P ? __ballot((in >> k) & 1u) : 0;
+            if (L == 16) {  // the wave's rows are alike
+                const uint64_t w1 = k + 1 < P ? __ballot((in >> (k + 1)) & 1u) : 0;
+                w = (w & 0xffffu) | (w1 & 0xffffu) << 16;
+            }
             if (lane == 0) {
-                sh.mask[k][2 * q] = (uint32_t)b;
-                sh.mask[k][2 * q + 1] = (uint32_t)(b >> 32);
+                sh.mask[t][L * k / 32] = (uint32_t)w;
+                if (L == 64) sh.mask[t][2 * k + 1] = (uint32_t)(w >> 32);
             }
         }
         if (lane == 0) {
-            sh.cov[k] = cv;
-            sh.cdet[k] = det3(cv.s);
+            sh.cov[t] = c;
+            sh.cdet[t] = det3(c.s);
         }
     }
-    __syncthreads();
 }
 
 __device__ inline bool cell_span(int64_t lo, int64_t hi, int32_t f0, int32_t f1, int cl, int *c0,
@@ -331,22 +499,21 @@ __device__ inline bool cell_span(int64_t lo, int64_t hi, int32_t f0, int32_t f1,
 
 __global__ void __launch_bounds__(RT) k_refine_clusters(RefineArgs a) {
     __shared__ Shared sh;
-    const int tid = threadIdx.x, lane = __lane_id(), wave = tid >> 6;
+    const int tid = threadIdx.x;
     const PreparedCatalog &c = a.cat;
     const double r2max = a.radius_px * a.radius_px;
     for (int64_t cl = blockIdx.x; cl < a.n_clusters; cl += gridDim.x) {
         const int32_t f = a.first[cl], m0 = a.first[cl + 1] - f;
-        sas_refined res{};
-        res.status = SAS_REFINE_TOO_SMALL;
+        int status = SAS_REFINE_TOO_SMALL;
         int n = m0;
         __syncthreads();  // the previous cluster is done with the shared state
         if (tid == 0) sh.overflow = 0;
         __syncthreads();
         if (f < 0 || m0 < 0 || (int64_t)f + m0 > a.n_members) {
-            res.status = SAS_REFINE_BAD_INPUT;
+            status = SAS_REFINE_BAD_INPUT;
             n = -1;
         } else if (m0 > kMaxPoints) {
-            res.status = SAS_REFINE_TOO_LARGE;
+            status = SAS_REFINE_TOO_LARGE;
             n = -1;
         } else {
             for (int i = tid; i < m0; i += RT) {
@@ -356,88 +523,104 @@ __global__ void __launch_bounds__(RT) k_refine_clusters(RefineArgs a) {
             }
             __syncthreads();
             if (sh.overflow) {
-                res.status = SAS_REFINE_BAD_INPUT;
+                status = SAS_REFINE_BAD_INPUT;
                 n = -1;
             } else {
-                sort_into(sh.tmp, m0, sh.cur);
+                sort_into(sh.tmp, m0, sh.sets[0]);
+                if (tid == 0) sh.n_set[0] = m0;
             }
         }
-        int32_t n_g = 0;  // gathered by the last fit
+        int32_t n_g = 0;   // gathered by the last fit
+        int rounds = 0;    // fits made
+        int last = 0;      // the round whose fit stands (rounds, or its like in a cycle)
+        int out_set = 0;   // the set reported as gathered
         for (int rnd = 1; n >= 0 && rnd <= kMaxRounds; ++rnd) {
             __syncthreads();
             if (n < kMinPoints) {
-                res.status = SAS_REFINE_TOO_SMALL;
+                status = SAS_REFINE_TOO_SMALL;
                 break;
             }
+            const int32_t *set = sh.sets[rnd - 1];
             for (int i = tid; i < n; i += RT) {
-                const int32_t q = sh.cur[i];
+                const int32_t q = set[i];
                 sh.zt[i] = (double)c.dt[a.epoch[q]] / 65536.0;
                 sh.zx[i] = (double)a.x[q] / 256.0;
                 sh.zy[i] = (double)a.y[q] / 256.0;
             }
             const int h = (n + 4) / 2;
             __syncthreads();
-            switch ((n + 63) >> 6) {
-            case 1: mcd_stages<1>(sh, a, n, h); break;
-            case 2: mcd_stages<2>(sh, a, n, h); break;
-            case 3:
-            case 4: mcd_stages<4>(sh, a, n, h); break;
-            default: mcd_stages<8>(sh, a, n, h); break;
+            // the smallest form that holds the set: a lane's work is per point held
+#pragma unroll 1
+            for (int stage = 0; stage < 2; ++stage) {
+                if (n <= 32)
+                    mcd_stage<16, 2>(sh, a, n, h, stage);
+                else if (n <= 64)
+                    mcd_stage<16, 4>(sh, a, n, h, stage);
+                else if (n <= 128)
+                    mcd_stage<16, 8>(sh, a, n, h, stage);
+                else if (n <= 256)
+                    mcd_stage<64, 4>(sh, a, n, h, stage);
+                else
+                    mcd_stage<64, 8>(sh, a, n, h, stage);
+                __syncthreads();
+                if (stage == 0) {
+                    if (tid < 64) best_starts(sh, a.n_starts);
+                    __syncthreads();
+                }
             }
             const int n_top = sh.n_top;
             if (n_top == 0) {
-                res.status = SAS_REFINE_NO_START;
+                status = SAS_REFINE_NO_START;
                 break;
             }
-            __syncthreads();
             int best = 0;
             for (int k = 1; k < n_top; ++k)
                 if (sh.cdet[k] < sh.cdet[best]) best = k;
-            const Cov cv = sh.cov[best];
-            // the regression of Sec. 2 from the MCD mean and covariance
-            const double bx = cv.s[1] / cv.s[0], by = cv.s[2] / cv.s[0];
-            const double cx = cv.mu[1] - bx * cv.mu[0], cy = cv.mu[2] - by * cv.mu[0];
-            res.vx = bx;
-            res.vy = by;
-            res.x0 = cx;
-            res.y0 = cy;
-            res.sxx = cv.s[3] - bx * bx * cv.s[0];
-            res.sxy = cv.s[4] - bx * by * cv.s[0];
-            res.syy = cv.s[5] - by * by * cv.s[0];
-            res.n_points = h;
-            res.rounds = rnd;
-            if (a.subset && cl < a.subset_clusters) {  // the MCD subset (catalog indices)
-                for (int i = tid; i < n; i += RT)
-                    if ((sh.mask[best][i >> 5] >> (i & 31)) & 1u) {
-                        int r = 0;
-                        for (int j = 0; j < i; ++j) r += (sh.mask[best][j >> 5] >> (j & 31)) & 1u;
-                        a.subset[cl * (int64_t)kMaxPoints + r] = sh.cur[i];
-                    }
+            double bx, by, cx, cy;
+            {
+                const Cov &cv = sh.cov[best];
+                // the regression of Sec. 2 from the MCD mean and covariance
+                bx = cv.s[1] / cv.s[0];
+                by = cv.s[2] / cv.s[0];
+                cx = cv.mu[1] - bx * cv.mu[0];
+                cy = cv.mu[2] - by * cv.mu[0];
+                if (tid == 0) {
+                    sas_refined &r = sh.fit[rnd - 1];
+                    r.vx = bx;
+                    r.vy = by;
+                    r.x0 = cx;
+                    r.y0 = cy;
+                    r.sxx = cv.s[3] - bx * bx * cv.s[0];
+                    r.sxy = cv.s[4] - bx * by * cv.s[0];
+                    r.syy = cv.s[5] - by * by * cv.s[0];
+                    r.n_points = h;
+                    sh.n_nxt = 0;
+                }
+                if (tid < kMaskWords) sh.subset[rnd - 1][tid] = sh.mask[best][tid];
             }
-            // Step 5: the catalog detections within the radius of c + B t
-            if (tid == 0) {
-                sh.n_nxt = 0;
-                sh.overflow = 0;
-            }
+            rounds = last = rnd;
             __syncthreads();
-            for (int e = tid; e < c.n_epochs; e += RT) {
-                const int32_t d = c.dt[e];
-                if (d < 0) continue;
+            // Step 5: the catalog detections within the radius of c + B t, kGatherRows
+            // threads an epoch, each every kGatherRows-th index row
+            constexpr int kGatherRows = RT / kMaxEpochs;
+            {
+                const int e = tid / kGatherRows;
+                const int32_t d = e < c.n_epochs ? c.dt[e] : -1;
                 const double t = (double)d / 65536.0;
                 const double px = cx + bx * t, py = cy + by * t;
                 const double lo_x = (px - a.radius_px) * 256.0, hi_x = (px + a.radius_px) * 256.0;
                 const double lo_y = (py - a.radius_px) * 256.0, hi_y = (py + a.radius_px) * 256.0;
-                if (!(hi_x >= -2147483648.0 && lo_x < 2147483647.0 && hi_y >= -2147483648.0 &&
-                      lo_y < 2147483647.0))
-                    continue;
-                const int64_t xlo = (int64_t)floor(lo_x), xhi = (int64_t)floor(hi_x) + 2;
-                const int64_t ylo = (int64_t)floor(lo_y), yhi = (int64_t)floor(hi_y) + 2;
-                int cx0, cx1, cy0, cy1;
-                if (!cell_span(xlo, xhi, c.x0, c.x1, c.cell_log2, &cx0, &cx1) ||
-                    !cell_span(ylo, yhi, c.y0, c.y1, c.cell_log2, &cy0, &cy1))
-                    continue;
-                for (int cy = cy0; cy <= cy1; ++cy) {
-                    const int64_t base = ((int64_t)e * c.ncy + cy) * c.ncx;
+                int cx0 = 0, cx1 = 0, cy0 = 0, cy1 = -1;
+                if (d >= 0 && hi_x >= -2147483648.0 && lo_x < 2147483647.0 &&
+                    hi_y >= -2147483648.0 && lo_y < 2147483647.0) {
+                    const int64_t xlo = (int64_t)floor(lo_x), xhi = (int64_t)floor(hi_x) + 2;
+                    const int64_t ylo = (int64_t)floor(lo_y), yhi = (int64_t)floor(hi_y) + 2;
+                    if (!cell_span(xlo, xhi, c.x0, c.x1, c.cell_log2, &cx0, &cx1) ||
+                        !cell_span(ylo, yhi, c.y0, c.y1, c.cell_log2, &cy0, &cy1))
+                        cy1 = cy0 - 1;  // the window misses the footprint
+                }
+                for (int cy2 = cy0 + tid % kGatherRows; cy2 <= cy1; cy2 += kGatherRows) {
+                    const int64_t base = ((int64_t)e * c.ncy + cy2) * c.ncx;
                     const int32_t j1 = c.off[base + cx1 + 1];
                     for (int32_t j = c.off[base + cx0]; j < j1; ++j) {
                         const int2 p = c.sxy[j];
@@ -453,34 +636,64 @@ __global__ void __launch_bounds__(RT) k_refine_clusters(RefineArgs a) {
             __syncthreads();
             n_g = sh.n_nxt;
             if (n_g > kMaxPoints) {
-                res.status = SAS_REFINE_TOO_LARGE;
-                break;
+                status = SAS_REFINE_TOO_LARGE;
+                break;  // out_set: the set just fitted
             }
-            sort_into(sh.tmp, n_g, sh.nxt);
-            __syncthreads();
-            // Step 6: stop when the gathered set is the set just fitted
-            bool same = n_g == n;
-            if (same) {
+            sort_into(sh.tmp, n_g, sh.sets[rnd]);
+            if (tid == 0) sh.n_set[rnd] = n_g;
+            out_set = rnd;
+            // Step 6: stop when the gathered set is the set just fitted.  A fit
+            // depends on its set alone, so when the gathered set was fitted in an
+            // earlier round q the rounds from q on repeat: the last round is like
+            // the round of the cycle in its place.  (Three to eight of the fast
+            // chip's 160 clusters end at the round limit, all in a cycle of two;
+            // the others take two to four rounds.)
+            int q = rnd;
+            for (; q >= 1; --q) {
+                if (sh.n_set[q - 1] != n_g) continue;  // block uniform
                 int diff = 0;
-                for (int i = tid; i < n; i += RT) diff |= sh.nxt[i] != sh.cur[i];
-                same = __syncthreads_or(diff) == 0;
+                for (int i = tid; i < n_g; i += RT) diff |= sh.sets[rnd][i] != sh.sets[q - 1][i];
+                if (__syncthreads_or(diff) == 0) break;
             }
-            __syncthreads();
-            for (int i = tid; i < n_g; i += RT) sh.cur[i] = sh.nxt[i];
-            n = n_g;
-            if (same) {
-                res.status = SAS_REFINE_CONVERGED;
+            if (q == rnd) {
+                status = SAS_REFINE_CONVERGED;
                 break;
             }
-            res.status = SAS_REFINE_MAX_ROUNDS;
+            status = SAS_REFINE_MAX_ROUNDS;
+            if (q >= 1) {
+                last = q + (kMaxRounds - q) % (rnd + 1 - q);
+                rounds = kMaxRounds;
+                out_set = last;
+                __syncthreads();  // n_set[rnd] is written
+                n_g = sh.n_set[last];
+                break;
+            }
+            n = n_g;
         }
         __syncthreads();
-        res.n_gathered = n_g;
-        if (res.rounds > 0 && a.gathered) {
-            const int m = min(n_g, min(kMaxPoints, a.gather_cap));
-            for (int i = tid; i < m; i += RT) a.gathered[cl * (int64_t)a.gather_cap + i] = sh.cur[i];
+        if (last > 0 && a.subset && cl < a.subset_clusters) {  // the MCD subset (catalog indices)
+            const uint32_t *mask = sh.subset[last - 1];
+            for (int i = tid; i < sh.n_set[last - 1]; i += RT) {
+                const uint32_t w = mask[i >> 5];
+                if (!((w >> (i & 31)) & 1u)) continue;
+                int r = __popc(w & ((1u << (i & 31)) - 1u));
+                for (int j = 0; j < i >> 5; ++j) r += __popc(mask[j]);
+                a.subset[cl * (int64_t)kMaxPoints + r] = sh.sets[last - 1][i];
+            }
         }
-        if (tid == 0) a.out[cl] = res;
+        if (last > 0 && a.gathered) {
+            const int m = min(n_g, min(kMaxPoints, a.gather_cap));
+            for (int i = tid; i < m; i += RT)
+                a.gathered[cl * (int64_t)a.gather_cap + i] = sh.sets[out_set][i];
+        }
+        if (tid == 0) {
+            sas_refined res{};
+            if (last > 0) res = sh.fit[last - 1];
+            res.n_gathered = n_g;
+            res.rounds = rounds;
+            res.status = status;
+            a.out[cl] = res;
+        }
     }
 }
 
