@@ -546,7 +546,7 @@ sas_status sas_extract_scratch_size(int64_t n, int64_t n_cand, int64_t member_ca
  *               neighbours when those indices and their bins differ by at
  *               most 1 per component.  0 leaves features 9 and 10 at zero.
  *   scratch:    device memory of sas_features_scratch_size(n_cand) bytes or
- *               more (neighbour keys and their sort); unused when
+ *               more (a table of neighbour keys); unused when
  *               spacing_q8 is 0 (may then be NULL).
  *   feat_dev:   device [n_cand][32] float, row-major.
  * Asynchronous, no allocation.  Errors: SAS_E_INVALID (n_cand >= 2^31,

@@ -1380,21 +1380,16 @@ sas_status sas_vote_batch(const sas_batch *b, void *stream) {
 
 namespace {
 
-struct FeatScratch {
-    size_t keys, keys_alt, hist, hist_blocksum, total;
-};
+// Neighbour table of sas_features: a power of two of slots, at least two a
+// candidate (open addressing at most half full).
+int feat_table_log2(int64_t n_cand) {
+    int l = 8;
+    while (((int64_t)1 << l) < 2 * n_cand) ++l;
+    return l;
+}
 
-FeatScratch feat_scratch_layout(int64_t n_cand) {
-    FeatScratch L{};
-    const int64_t tiles = (n_cand + kSortKeysPerTile - 1) / kSortKeysPerTile;
-    const int64_t hist = 256 * tiles;
-    size_t o = 0;
-    L.keys = o; o = align_up(o + sizeof(uint64_t) * n_cand);
-    L.keys_alt = o; o = align_up(o + sizeof(uint64_t) * n_cand);
-    L.hist = o; o = align_up(o + sizeof(int32_t) * hist);
-    L.hist_blocksum = o; o = align_up(o + sizeof(int32_t) * ((hist + kScanTile - 1) / kScanTile));
-    L.total = o;
-    return L;
+size_t feat_scratch_bytes(int64_t n_cand) {
+    return sizeof(uint64_t) << feat_table_log2(n_cand);
 }
 
 constexpr int64_t kMaxFeatureCands = (int64_t)1 << 31;
@@ -1404,7 +1399,7 @@ constexpr int64_t kMaxFeatureCands = (int64_t)1 << 31;
 extern "C" sas_status sas_features_scratch_size(int64_t n_cand, size_t *bytes) {
     if (!bytes || n_cand < 0 || n_cand >= kMaxFeatureCands)
         return fail(SAS_E_INVALID, "sas_features_scratch_size: bad argument");
-    *bytes = feat_scratch_layout(n_cand).total;
+    *bytes = feat_scratch_bytes(n_cand);
     return SAS_OK;
 }
 
@@ -1422,8 +1417,7 @@ extern "C" sas_status sas_features(const sas_plan *p, const void *workspace, siz
     const WsLayout L = ws_layout(p, n);
     if (!workspace || ws_bytes < L.total)
         return fail(SAS_E_WORKSPACE, "sas_features: workspace smaller than sas_vote_workspace_size()");
-    const FeatScratch S = feat_scratch_layout(n_cand);
-    if (spacing_q8 > 0 && n_cand > 0 && (!scratch || scratch_bytes < S.total))
+    if (spacing_q8 > 0 && n_cand > 0 && (!scratch || scratch_bytes < feat_scratch_bytes(n_cand)))
         return fail(SAS_E_WORKSPACE, "sas_features: scratch smaller than sas_features_scratch_size()");
     if (n_cand == 0 || n == 0) return SAS_OK;
     char *w = (char *)workspace;
@@ -1439,13 +1433,8 @@ extern "C" sas_status sas_features(const sas_plan *p, const void *workspace, siz
     a.n_cand = n_cand;
     a.feat = feat_dev;
     a.spacing = spacing_q8;
-    if (spacing_q8 > 0) {
-        char *s = (char *)scratch;
-        a.keys = (uint64_t *)(s + S.keys);
-        a.keys_alt = (uint64_t *)(s + S.keys_alt);
-        a.hist = (int32_t *)(s + S.hist);
-        a.hist_blocksum = (int32_t *)(s + S.hist_blocksum);
-    }
+    a.table = (uint64_t *)scratch;
+    a.table_log2 = feat_table_log2(n_cand);
     hipError_t e = launch_features(a, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "sas_features: launch");
     return SAS_OK;

@@ -162,10 +162,10 @@ struct FeatureArgs {
     int64_t n_cand;
     float *feat;               // [n_cand][kFeatures]
     int32_t spacing;           // lattice spacing of the grid (0: no neighbour features)
-    uint64_t *keys, *keys_alt; // [n_cand] neighbour keys (scratch)
-    int32_t *hist, *hist_blocksum;
+    uint64_t *table;           // [2^table_log2] hash table of the neighbour keys (scratch)
+    int table_log2;
 };
-// Neighbour keys of the candidates, their sort, then the features.
+// Table of the candidates' neighbour keys, then the features.
 hipError_t launch_features(const FeatureArgs &a, hipStream_t stream);
 
 // ---- greedy cluster extraction (Step 3)
