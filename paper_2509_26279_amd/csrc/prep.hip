@@ -181,6 +181,97 @@ __global__ void k_prep_scatter(const int32_t *__restrict__ x, const int32_t *__r
     sidx[pos] = (int32_t)i;  // position in the caller's catalog (candidate features)
 }
 
+// The whole preparation of a small catalog in one workgroup: counts in LDS,
+// the lanes' cells and ranks in registers.  A small search is the latency of
+// its launches: on the 2000 detections and 5120 cells of the tiny workload the
+// eight kernels of the general path ran 28 us and left gaps of as much again;
+// this one runs 7.8 us.
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallPerThread = 8;
+constexpr int64_t kSmallDet = (int64_t)kSmallThreads * kSmallPerThread;
+constexpr int64_t kSmallCount = 12288;  // cells, and one (48 KB of LDS)
+
+__global__ void __launch_bounds__(kSmallThreads)
+k_prep_small(const int32_t *__restrict__ x, const int32_t *__restrict__ y,
+             const uint8_t *__restrict__ epoch, const uint8_t *__restrict__ weight, int32_t n,
+             const int64_t *__restrict__ t, int32_t n_epochs, int32_t ncx, int32_t ncy,
+             int32_t cell_log2, int32_t x0, int32_t x1, int32_t y0, int32_t y1, PrepBuffers pb,
+             sas_vote_result *res) {
+    __shared__ int32_t count[kSmallCount];
+    __shared__ int32_t present[kMaxEpochs];
+    __shared__ long long red[kMaxEpochs];
+    __shared__ int32_t status;
+    const int tid = threadIdx.x;
+    const int n_count = n_epochs * ncx * ncy + 1;
+    for (int i = tid; i < n_count; i += kSmallThreads) count[i] = 0;
+    if (tid < kMaxEpochs) present[tid] = 0;
+    if (tid == 0) status = 0;
+    __syncthreads();
+    int32_t cell[kSmallPerThread], rank[kSmallPerThread];
+    int2 at[kSmallPerThread];
+#pragma unroll
+    for (int k = 0; k < kSmallPerThread; ++k) {
+        const int i = k * kSmallThreads + tid;
+        cell[k] = -1;
+        if (i >= n) continue;
+        const int e = epoch[i];
+        const int32_t xi = x[i], yi = y[i];
+        if (e >= n_epochs) {
+            atomicOr(&status, SAS_DATA_BAD_EPOCH);
+        } else if (xi < x0 || xi >= x1 || yi < y0 || yi >= y1) {
+            atomicOr(&status, SAS_DATA_OUTSIDE);
+        } else {
+            cell[k] = (e * ncy + ((yi - y0) >> cell_log2)) * ncx + ((xi - x0) >> cell_log2);
+            rank[k] = atomicAdd(&count[cell[k]], 1);
+            present[e] = 1;
+            at[k] = make_int2(weight ? (int32_t)(((uint32_t)xi << 8) | weight[i]) : xi, yi);
+        }
+    }
+    __syncthreads();
+    // offsets: each thread scans a stretch of the counts
+    const int per = (n_count + kSmallThreads - 1) / kSmallThreads;
+    const int i0 = min(tid * per, n_count), i1 = min(i0 + per, n_count);
+    int32_t s = 0, total;
+    for (int i = i0; i < i1; ++i) s += count[i];
+    int32_t run = block_exclusive_scan(s, &total);
+    for (int i = i0; i < i1; ++i) {
+        const int32_t v = count[i];
+        count[i] = run;
+        run += v;
+    }
+    // reference epoch
+    if (tid < kMaxEpochs)
+        red[tid] = tid < n_epochs && present[tid] ? (long long)t[tid] : LLONG_MAX;
+    __syncthreads();
+    for (int h = kMaxEpochs / 2; h > 0; h >>= 1) {
+        if (tid < h) red[tid] = red[tid] < red[tid + h] ? red[tid] : red[tid + h];
+        __syncthreads();
+    }
+    if (tid < n_epochs)
+        pb.dt[tid] = present[tid] && red[0] != LLONG_MAX ? (int32_t)(t[tid] - red[0]) : -1;
+    for (int i = tid; i < n_count; i += kSmallThreads) pb.count[i] = count[i];
+    const int total_t = n_epochs * (ncx + 1) * ncy;
+    for (int i = tid; i < total_t; i += kSmallThreads) {
+        const int cy = i % ncy, rest = i / ncy;
+        const int cx = rest % (ncx + 1), e = rest / (ncx + 1);
+        pb.offT[i] = count[(e * ncy + cy) * ncx + cx];
+    }
+#pragma unroll
+    for (int k = 0; k < kSmallPerThread; ++k) {
+        if (cell[k] < 0) continue;
+        const int32_t pos = count[cell[k]] + rank[k];
+        pb.sxy[pos] = at[k];
+        pb.sidx[pos] = k * kSmallThreads + tid;
+    }
+    if (tid < kXcds) pb.item_queue[tid] = 0;
+    if (tid == 0) {
+        res->n_cand = 0;
+        res->status = status;
+        res->n_spilled = 0;
+        *pb.refine_count = 0;
+    }
+}
+
 inline unsigned blocks_for(int64_t n, int threads) {
     return (unsigned)((n + threads - 1) / threads);
 }
@@ -204,6 +295,12 @@ hipError_t launch_prep(const int32_t *x, const int32_t *y, const uint8_t *epoch,
                        int32_t cell_log2, const int32_t ext[4], int64_t n_cells,
                        const PrepBuffers &pb, sas_vote_result *res, hipStream_t stream) {
     const int64_t n_count = n_cells + 1;
+    if (n <= kSmallDet && n_count <= kSmallCount) {
+        hipLaunchKernelGGL(k_prep_small, dim3(1), dim3(kSmallThreads), 0, stream, x, y, epoch,
+                           weight, (int32_t)n, t_dev, n_epochs, ncx, ncy, cell_log2, ext[0],
+                           ext[1], ext[2], ext[3], pb, res);
+        return hipGetLastError();
+    }
     unsigned zb = blocks_for(n_count, 256);
     if (zb > 4096) zb = 4096;
     hipLaunchKernelGGL(k_prep_zero, dim3(zb), dim3(256), 0, stream, pb.count, n_count,

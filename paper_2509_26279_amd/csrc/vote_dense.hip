@@ -859,7 +859,12 @@ __device__ void vote_item(const DenseArgs &a, Shared &sh, uint4 *smem4, int32_t 
 
 // Dynamic LDS: histogram [HY][HX][NV] words, then the stage (int2, or one
 // packed word per detection), one part of stage_cap / NW detections per wave.
-template <int MODE, int G, bool PK>
+// EACH: launched with a workgroup for every kept item, which it takes by its
+// own index.  The tickets of the other form past the ends of eight ranges, one
+// trip to memory after the other, took 7.5 of the 81 us of the tiny search; a
+// switch inside one kernel would cost the large ones registers (1 % of a
+// weighted vote).
+template <int MODE, int G, bool PK, bool EACH>
 __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<G, PK>))) k_vote_dense(DenseArgs a) {
     extern __shared__ uint4 smem4[];
     __shared__ Shared sh;
@@ -887,18 +892,26 @@ __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(kWavesPe
     // ticket each, then helps with the other ranges in turn.  Every ticket
     // below a range's size is one item, taken once; every workgroup ends after
     // one ticket past the end of each range.
-    const int x0 = blockIdx.x % kXcds;
-    for (int k = 0; k < kXcds; ++k) {
-        const int x = (x0 + k) % kXcds;
-        const int64_t lo = x * n_walk / kXcds, n_x = (x + 1) * n_walk / kXcds - lo;
-        for (;;) {
-            __syncthreads();  // every thread has read the previous ticket
-            if (tid == 0) sh.ticket = atomicAdd(&a.item_queue[x], 1ull);
-            __syncthreads();
-            const int64_t t = (int64_t)sh.ticket;  // block uniform
-            if (t >= n_x) break;
-            const int32_t *it = a.items + 4 * (lo + t);
+    if constexpr (EACH) {
+        // few items: no queues
+        for (int64_t q = blockIdx.x; q < n_walk; q += gridDim.x) {
+            const int32_t *it = a.items + 4 * q;
             vote_item<MODE, G, PK>(a, sh, smem4, it[0], it[1], it[2], it[3], tseq);
+        }
+    } else {
+        const int x0 = blockIdx.x % kXcds;
+        for (int k = 0; k < kXcds; ++k) {
+            const int x = (x0 + k) % kXcds;
+            const int64_t lo = x * n_walk / kXcds, n_x = (x + 1) * n_walk / kXcds - lo;
+            for (;;) {
+                __syncthreads();  // every thread has read the previous ticket
+                if (tid == 0) sh.ticket = atomicAdd(&a.item_queue[x], 1ull);
+                __syncthreads();
+                const int64_t t = (int64_t)sh.ticket;  // block uniform
+                if (t >= n_x) break;
+                const int32_t *it = a.items + 4 * (lo + t);
+                vote_item<MODE, G, PK>(a, sh, smem4, it[0], it[1], it[2], it[3], tseq);
+            }
         }
     }
     __syncthreads();
@@ -1115,18 +1128,27 @@ int64_t resident_grid(size_t lds, int64_t kept) {
     return std::min<int64_t>(std::max<int64_t>(kept, 1), (int64_t)n_cu * per_cu);
 }
 
-template <int MODE, int G, bool PK>
-hipError_t launch_mg(const DenseArgs &a, size_t lds, hipStream_t stream, hipEvent_t ev0,
-                     hipEvent_t ev1) {
+template <int MODE, int G, bool PK, bool EACH>
+hipError_t launch_vote(const DenseArgs &a, int64_t grid, size_t lds, hipStream_t stream,
+                       hipEvent_t ev0, hipEvent_t ev1) {
     static size_t lds_set = 0;  // dynamic LDS limit raised so far for this kernel
-    hipError_t e = set_lds_limit((const void *)k_vote_dense<MODE, G, PK>, lds, &lds_set);
+    hipError_t e = set_lds_limit((const void *)k_vote_dense<MODE, G, PK, EACH>, lds, &lds_set);
     if (e != hipSuccess) return e;
-    const dim3 grid((unsigned)resident_grid<G, PK>(lds, a.n_items_kept)), block(T);
     if (ev0 && (e = hipEventRecord(ev0, stream)) != hipSuccess) return e;
-    hipLaunchKernelGGL((k_vote_dense<MODE, G, PK>), grid, block, lds, stream, a);
+    hipLaunchKernelGGL((k_vote_dense<MODE, G, PK, EACH>), dim3((unsigned)grid), dim3(T), lds,
+                       stream, a);
     if (ev1 && (e = hipEventRecord(ev1, stream)) != hipSuccess) return e;
     if (refined_mode<MODE>()) return launch_refine(a, stream);
     return hipGetLastError();
+}
+
+template <int MODE, int G, bool PK>
+hipError_t launch_mg(const DenseArgs &a, size_t lds, hipStream_t stream, hipEvent_t ev0,
+                     hipEvent_t ev1) {
+    const int64_t grid = resident_grid<G, PK>(lds, a.n_items_kept);
+    return grid >= a.n_items_kept
+               ? launch_vote<MODE, G, PK, true>(a, grid, lds, stream, ev0, ev1)
+               : launch_vote<MODE, G, PK, false>(a, grid, lds, stream, ev0, ev1);
 }
 
 template <int MODE, bool PK>
