@@ -153,7 +153,8 @@ typedef struct {
 
 #define SAS_PATH_AUTO 0
 #define SAS_PATH_DENSE 1   /* LDS-resident count tiles (velocity block x spatial tile) */
-#define SAS_PATH_SORT 2    /* sort-by-bin-key in HBM */
+#define SAS_PATH_SORT 2    /* sort-by-bin-key in HBM; whole-band LDS counts where a velocity's
+                              bins are few enough and sort_vblock is not given */
 
 /* Launch shape of the dense path; zeros select the built-in defaults. */
 typedef struct {
@@ -166,7 +167,7 @@ typedef struct {
     int32_t stage_cap;          /* detections staged in LDS at a time (larger windows are
                                    processed in chunks) */
     int32_t cell_log2;          /* log2 of the window-index cell size in Q8 px */
-    int32_t sort_vblock;        /* velocities per sort-path block */
+    int32_t sort_vblock;        /* velocities per sort-path block (given: always the sort) */
     int32_t n_det_hint;         /* expected detections per catalog: chooses the cell size */
     int32_t coarse_log2;        /* histogram cells of 2^m x 2^m bins, m in [0, 3]; -1: single
                                    bins; 0: chosen from n_det_hint */

@@ -132,6 +132,8 @@ struct sas_plan {
     std::vector<SortBlock> sort_blocks;
     int64_t sort_max_nv = 0;
     int32_t sort_vblock = 0;
+    int64_t n_bands = 0;        // band items (0: a velocity's bins are too many for them)
+    int32_t *d_bands = nullptr;
     int32_t *d_sort_vel = nullptr, *d_sort_vidx = nullptr;
     hipEvent_t probe[2] = {nullptr, nullptr};
     unsigned long long *counter = nullptr;  // device: LDS atomic vote instructions (probe)
@@ -848,7 +850,12 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
 
     // Sort path: blocks of consecutive segments, up to sort_vblock velocities,
     // each with the bin extent every (velocity, detection) of it can reach.
-    std::vector<int32_t> sort_vel, sort_vidx;
+    std::vector<int32_t> sort_vel, sort_vidx, bands;
+    // Band items replace the sort where every velocity's bin rows fit LDS and its
+    // bins at most kMaxBands items (each reads about its share of the catalog, but
+    // walks every epoch); an explicit sort_vblock asks for the sort.
+    constexpr int64_t kMaxBands = 32;
+    bool banded = tu.sort_vblock <= 0;
     if (p->path == SAS_PATH_SORT) {
         int64_t vb = tu.sort_vblock;
         if (vb <= 0)
@@ -900,6 +907,14 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
                 if (bx0 <= -((int64_t)1 << 31) || bx1 >= ((int64_t)1 << 31) ||
                     by0 <= -((int64_t)1 << 31) || by1 >= ((int64_t)1 << 31))
                     return fail(SAS_E_UNSUPPORTED, "sas_plan_create: sort-path bins exceed 32 bits");
+                const int64_t nbx = a1 - a0 + 1, nby = c1 - c0 + 1;
+                const int64_t rows = nbx <= kBandBins ? std::min<int64_t>(kBandBins / nbx, nby) : 0;
+                banded = banded && rows > 0 && (nby + rows - 1) / rows <= kMaxBands &&
+                         (int64_t)bands.size() / 5 < ((int64_t)1 << 30);
+                for (int64_t r = 0; banded && r < nby; r += rows)
+                    bands.insert(bands.end(), {(int32_t)sort_vidx.size(), (int32_t)a0, (int32_t)nbx,
+                                               (int32_t)(c0 + r),
+                                               (int32_t)std::min<int64_t>(rows, nby - r)});
                 sort_vel.push_back(u);
                 sort_vel.push_back(w);
                 sort_vidx.push_back(vi);
@@ -912,6 +927,8 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
             return fail(SAS_E_UNSUPPORTED, "sas_plan_create: sort keys exceed 64 bits; lower "
                                            "sort_vblock");
         p->sort_vblock = (int32_t)vb;
+        if (!banded) bands.clear();
+        p->n_bands = (int64_t)bands.size() / 5;
     }
 
     std::vector<int32_t> vel(V, V + 2 * n_v);
@@ -930,6 +947,7 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
     if ((st = upload(p.get(), &p->d_t, p->t)) != SAS_OK) goto fail_free;
     if ((st = upload(p.get(), &p->d_sort_vel, sort_vel)) != SAS_OK) goto fail_free;
     if ((st = upload(p.get(), &p->d_sort_vidx, sort_vidx)) != SAS_OK) goto fail_free;
+    if ((st = upload(p.get(), &p->d_bands, bands)) != SAS_OK) goto fail_free;
     *plan_out = p.release();
     return SAS_OK;
 fail_free:
@@ -1035,6 +1053,7 @@ sas_status vote_impl(const sas_plan *p, const int32_t *x_q8, const int32_t *y_q8
         sa.mode_epochs = p->mode == SAS_MODE_EPOCHS ? 1 : 0;
         sa.vel = p->d_sort_vel;
         sa.v_idx = p->d_sort_vidx;
+        sa.cat = dense_args(p, L, w, pb, nullptr, 0, nullptr).cat;
         sa.keys = (uint64_t *)(w + L.keys);
         sa.keys_alt = (uint64_t *)(w + L.keys_alt);
         sa.hist = (int32_t *)(w + L.hist);
@@ -1046,9 +1065,20 @@ sas_status vote_impl(const sas_plan *p, const int32_t *x_q8, const int32_t *y_q8
             e = hipEventRecord(p->probe[0], s);
             if (e != hipSuccess) return hip_fail(e, "sas_vote: probe");
         }
-        for (const SortBlock &b : p->sort_blocks) {
-            e = launch_vote_sort_block(sa, b, s);
-            if (e != hipSuccess) return hip_fail(e, "sas_vote: sort-path launch");
+        // Band items read the catalog once, and in EPOCHS mode once more for every
+        // kBandMasks / ceil(E / 32) bins that hold N_min detections.  Also where
+        // every occupied bin does (up to 64 readings) they beat the sort: 512
+        // velocities and 1.8e5 detections, thresholds 1 / 8 / 23: 6.8 / 3.0 / 0.16 ms
+        // against 22.6 / 12.7 / 5.3 ms at 60 epochs, 12.4 / 4.5 / 0.34 against
+        // 26.2 / 18.8 / 6.3 ms at 256.
+        if (p->n_bands > 0) {
+            e = launch_band_vote(sa, p->d_bands, p->n_bands, s);
+            if (e != hipSuccess) return hip_fail(e, "sas_vote: band launch");
+        } else {
+            for (const SortBlock &b : p->sort_blocks) {
+                e = launch_vote_sort_block(sa, b, s);
+                if (e != hipSuccess) return hip_fail(e, "sas_vote: sort-path launch");
+            }
         }
         if (p->probe[1]) {
             e = hipEventRecord(p->probe[1], s);

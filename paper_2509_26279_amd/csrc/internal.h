@@ -122,6 +122,7 @@ struct SortBlock {
 };
 
 struct SortArgs {
+    PreparedCatalog cat;      // window index of the catalog (band items)
     const int32_t *x, *y;
     const uint8_t *epoch;
     int64_t n;
@@ -137,6 +138,13 @@ struct SortArgs {
     int64_t cand_cap;
     sas_vote_result *res;
 };
+
+// Band items of the sort path: [n][5] velocity (block order), first bin and
+// bins in x, first bin row and rows.
+constexpr int kBandBins = 16384;   // bins of an item (64 KB of LDS)
+constexpr int kBandMasks = 2048;   // words of epoch masks
+hipError_t launch_band_vote(const SortArgs &a, const int32_t *items, int64_t n_items,
+                            hipStream_t stream);
 
 constexpr int kSortKeysPerTile = 4096;  // radix tile: 256 threads x 16 keys
 
