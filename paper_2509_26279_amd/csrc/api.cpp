@@ -1487,15 +1487,16 @@ extern "C" sas_status sas_features(const sas_plan *p, const void *workspace, siz
 namespace {
 
 struct ExtractScratch {
-    size_t first, blocksum, member, member_epoch, member_cell, inv_first, inv_blocksum,
-        inv_cursor, inv, count, dirty, live, open, best, slot, taken, perm, counters, total;
+    size_t first, len, n_members, member, member_epoch, member_cell, inv_first, inv_blocksum,
+        inv_cursor, inv, count, dirty, died, open, best, taken, perm, counters, total;
 };
 
 ExtractScratch extract_layout(int64_t n, int64_t n_cand, int64_t member_cap) {
     ExtractScratch L{};
     size_t o = 0;
-    L.first = o; o = align_up(o + sizeof(int32_t) * (n_cand + 1));
-    L.blocksum = o; o = align_up(o + sizeof(int32_t) * ((n_cand + 1 + kScanTile - 1) / kScanTile));
+    L.first = o; o = align_up(o + sizeof(int32_t) * n_cand);
+    L.len = o; o = align_up(o + sizeof(int32_t) * n_cand);
+    L.n_members = o; o = align_up(o + sizeof(unsigned long long));
     L.member = o; o = align_up(o + sizeof(int32_t) * member_cap);
     L.member_epoch = o; o = align_up(o + member_cap);
     L.member_cell = o; o = align_up(o + sizeof(int32_t) * member_cap);
@@ -1505,11 +1506,10 @@ ExtractScratch extract_layout(int64_t n, int64_t n_cand, int64_t member_cap) {
     L.inv = o; o = align_up(o + sizeof(int32_t) * member_cap);
     L.count = o; o = align_up(o + sizeof(int32_t) * n_cand);
     L.dirty = o; o = align_up(o + sizeof(uint32_t) * n_cand);
-    L.live = o; o = align_up(o + n);
+    L.died = o; o = align_up(o + n);
     L.open = o; o = align_up(o + n_cand);
     L.best = o; o = align_up(o + sizeof(int32_t) * n);
-    L.slot = o; o = align_up(o + sizeof(int32_t) * n_cand);
-    L.taken = o; o = align_up(o + sizeof(int32_t) * n_cand);
+    L.taken = o; o = align_up(o + sizeof(int4) * n_cand);
     L.perm = o; o = align_up(o + sizeof(int32_t) * n_cand);
     L.counters = o; o = align_up(o + sizeof(int32_t) * kExtractCounters);
     L.total = o;
@@ -1566,7 +1566,8 @@ extern "C" sas_status sas_extract_clusters(const sas_plan *p, const void *worksp
     a.n_cand = n_cand;
     a.n = n;
     a.first = (int32_t *)(s + S.first);
-    a.scan_blocksum = (int32_t *)(s + S.blocksum);
+    a.len = (int32_t *)(s + S.len);
+    a.n_members = (unsigned long long *)(s + S.n_members);
     a.member = (int32_t *)(s + S.member);
     a.member_epoch = (uint8_t *)(s + S.member_epoch);
     a.member_cell = (int32_t *)(s + S.member_cell);
@@ -1577,11 +1578,10 @@ extern "C" sas_status sas_extract_clusters(const sas_plan *p, const void *worksp
     a.inv = (int32_t *)(s + S.inv);
     a.count = (int32_t *)(s + S.count);
     a.dirty = (uint32_t *)(s + S.dirty);
-    a.live = (uint8_t *)(s + S.live);
+    a.died = (uint8_t *)(s + S.died);
     a.open = (uint8_t *)(s + S.open);
     a.best = (int32_t *)(s + S.best);
-    a.slot = (int32_t *)(s + S.slot);
-    a.taken = (int32_t *)(s + S.taken);
+    a.taken = (int4 *)(s + S.taken);
     a.perm = (int32_t *)(s + S.perm);
     a.counters = (int32_t *)(s + S.counters);
     a.clusters = clusters_dev;

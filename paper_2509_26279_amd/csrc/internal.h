@@ -108,8 +108,10 @@ hipError_t launch_prep(const int32_t *x, const int32_t *y, const uint8_t *epoch,
                        int32_t cell_log2, const int32_t ext[4], int64_t n_cells,
                        const PrepBuffers &pb, sas_vote_result *res, hipStream_t stream);
 
-// Exclusive scan of n int32 in place (blocksum: (n + kScanTile - 1) / kScanTile).
-hipError_t launch_scan_exclusive(int32_t *data, int64_t n, int32_t *blocksum, hipStream_t stream);
+// Exclusive scan of n int32 in place (blocksum: (n + kScanTile - 1) / kScanTile);
+// skipped on the device when *when is 0 (when may be null).
+hipError_t launch_scan_exclusive(int32_t *data, int64_t n, int32_t *blocksum, hipStream_t stream,
+                                 const int32_t *when = nullptr);
 
 // Sort-by-bin-key path.  A sort block is a run of velocities whose keys are
 // generated, radix sorted and counted together.
@@ -185,8 +187,8 @@ struct ExtractArgs {
     const sas_candidate *cand;  // the cells the vote reported
     int64_t n_cand;
     int64_t n;                 // detections
-    int32_t *first;            // [n_cand + 1] contributor counts, then offsets
-    int32_t *scan_blocksum;
+    int32_t *first, *len;      // [n_cand] first entry and length of each cell's list
+    unsigned long long *n_members;  // total length of the lists
     int32_t *member;           // [member_cap] sorted positions of the contributors
     uint8_t *member_epoch;     // [member_cap] their epochs
     int32_t *member_cell;      // [member_cap] the cell of each entry
@@ -197,13 +199,13 @@ struct ExtractArgs {
     int32_t *inv;              // [member_cap] the cells, grouped by detection
     int32_t *count;            // [n_cand] current count of each cell
     uint32_t *dirty;           // [n_cand] queued for a recount
-    uint8_t *live;             // [n] by sorted position: not yet in a cluster
-    uint8_t *open;             // [n_cand] 0 closed, 1 open, 2 taken in this round
+    uint8_t *died;             // [n] by sorted position: 0 live, r taken in round r, 255 after
+    uint8_t *open;             // [n_cand] 0 closed, 1 open
     int32_t *best;             // [n] by sorted position: the best open cell holding it, -1
-    int32_t *slot;             // [n_cand] provisional cluster of a cell taken in a round
-    int32_t *taken;            // [n_cand] the cell of each cluster, by provisional index
+    int4 *taken;               // [n_cand] by provisional cluster: count, v_idx, by, bx of its cell
     int32_t *perm;             // [n_cand] provisional index -> extraction order
-    int32_t *counters;         // [2 + kExtractRounds + 1] taken so far, total, open after round r
+    int32_t *counters;         // [2 + kExtractRounds + 1] taken so far, total, open left after
+                               // round r
     int32_t rounds;            // parallel rounds before the sequential finish (<= kExtractRounds)
     sas_candidate *clusters;   // [cluster_cap] in extraction order
     int64_t cluster_cap;

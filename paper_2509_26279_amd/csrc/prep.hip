@@ -96,7 +96,8 @@ __global__ void k_prep_count(const int32_t *__restrict__ x, const int32_t *__res
 
 // Per-tile exclusive scan in place; tile totals to blocksum.
 __global__ void __launch_bounds__(kScanThreads)
-k_scan_tiles(int32_t *data, int64_t n, int32_t *blocksum) {
+k_scan_tiles(int32_t *data, int64_t n, int32_t *blocksum, const int32_t *when) {
+    if (when && *when == 0) return;
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPerThread;
     int32_t v[kScanPerThread];
     int32_t s = 0;
@@ -117,7 +118,8 @@ k_scan_tiles(int32_t *data, int64_t n, int32_t *blocksum) {
 
 // Exclusive scan of the tile totals (one block, any count).
 __global__ void __launch_bounds__(kScanThreads)
-k_scan_blocksums(int32_t *blocksum, int64_t nb) {
+k_scan_blocksums(int32_t *blocksum, int64_t nb, const int32_t *when) {
+    if (when && *when == 0) return;
     int32_t carry = 0;
     for (int64_t start = 0; start < nb; start += kScanThreads) {
         const int64_t i = start + threadIdx.x;
@@ -130,7 +132,9 @@ k_scan_blocksums(int32_t *blocksum, int64_t nb) {
     }
 }
 
-__global__ void k_scan_add(int32_t *data, int64_t n, const int32_t *blocksum) {
+__global__ void k_scan_add(int32_t *data, int64_t n, const int32_t *blocksum,
+                           const int32_t *when) {
+    if (when && *when == 0) return;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) data[i] += blocksum[i / kScanTile];
 }
@@ -278,14 +282,18 @@ inline unsigned blocks_for(int64_t n, int threads) {
 
 }  // namespace
 
-hipError_t launch_scan_exclusive(int32_t *data, int64_t n, int32_t *blocksum, hipStream_t stream) {
+hipError_t launch_scan_exclusive(int32_t *data, int64_t n, int32_t *blocksum, hipStream_t stream,
+                                 const int32_t *when) {
     if (n <= 0) return hipSuccess;
     const int64_t nb = (n + kScanTile - 1) / kScanTile;
     hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)nb), dim3(kScanThreads), 0, stream, data, n,
-                       blocksum);
-    hipLaunchKernelGGL(k_scan_blocksums, dim3(1), dim3(kScanThreads), 0, stream, blocksum, nb);
-    hipLaunchKernelGGL(k_scan_add, dim3(blocks_for(n, 256)), dim3(256), 0, stream, data, n,
-                       blocksum);
+                       blocksum, when);
+    if (nb > 1) {
+        hipLaunchKernelGGL(k_scan_blocksums, dim3(1), dim3(kScanThreads), 0, stream, blocksum, nb,
+                           when);
+        hipLaunchKernelGGL(k_scan_add, dim3(blocks_for(n, 256)), dim3(256), 0, stream, data, n,
+                           blocksum, when);
+    }
     return hipGetLastError();
 }
 
@@ -310,12 +318,8 @@ hipError_t launch_prep(const int32_t *x, const int32_t *y, const uint8_t *epoch,
                            epoch, n, n_epochs, ncx, ncy, cell_log2, ext[0], ext[1], ext[2],
                            ext[3], pb.count, pb.cellid, pb.rank, pb.present, res);
     }
-    const int64_t nb = (n_count + kScanTile - 1) / kScanTile;
-    hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)nb), dim3(kScanThreads), 0, stream, pb.count,
-                       n_count, pb.blocksum);
-    hipLaunchKernelGGL(k_scan_blocksums, dim3(1), dim3(kScanThreads), 0, stream, pb.blocksum, nb);
-    hipLaunchKernelGGL(k_scan_add, dim3(blocks_for(n_count, 256)), dim3(256), 0, stream,
-                       pb.count, n_count, pb.blocksum);
+    const hipError_t e = launch_scan_exclusive(pb.count, n_count, pb.blocksum, stream, nullptr);
+    if (e != hipSuccess) return e;
     {
         const int64_t total = (int64_t)n_epochs * (ncx + 1) * ncy;
         unsigned tb = blocks_for(total, 256);
