@@ -166,7 +166,8 @@ typedef struct {
                                    instruction for 64 / G velocities */
     int32_t stage_cap;          /* detections staged in LDS at a time (larger windows are
                                    processed in chunks) */
-    int32_t cell_log2;          /* log2 of the window-index cell size in Q8 px */
+    int32_t cell_log2;          /* log2 of the window-index cell width in Q8 px (the cells grow
+                                   higher than wide when a window has too many rows of them) */
     int32_t sort_vblock;        /* velocities per sort-path block (given: always the sort) */
     int32_t n_det_hint;         /* expected detections per catalog: chooses the cell size */
     int32_t coarse_log2;        /* histogram cells of 2^m x 2^m bins, m in [0, 3]; -1: single
@@ -240,7 +241,7 @@ typedef struct {
     int32_t path;
     int32_t tile_x, tile_y;
     int32_t vblock_x, vblock_y;
-    int32_t cell_log2;
+    int32_t cell_log2;     /* log2 of the window-index cell height in Q8 px */
     int32_t coarse_log2;   /* histogram cells of 2^m x 2^m bins */
     int32_t mode_variant;  /* 0 epoch masks, 1 detection counts, 2 counts + refinement,
                               3 weight sums, 4 weight sums + refinement */

@@ -112,7 +112,7 @@ struct sas_plan {
     int32_t ext[4] = {0, 0, 0, 0};
     int64_t n_v = 0;
     int dense_mode = 0;
-    int32_t tile_x = 16, tile_y = 16, vbx = 8, vby = 8, groups = 1, cell_log2 = 11;
+    int32_t tile_x = 16, tile_y = 16, vbx = 8, vby = 8, groups = 1, cell_log2 = 11, cell_log2_x = 11;
     int32_t coarse_log2 = 0, hx = 0, hy = 0, stage_cap = 0, rows = 0, rows_log2 = 0;
     int32_t packed = 0;  // packed 16-bit votes
     int32_t halves = 0;  // 16-bit histogram counts, two histograms by tile
@@ -124,8 +124,9 @@ struct sas_plan {
     int32_t e_first = 0;
     size_t lds_bytes = 0;
     int32_t *d_vel = nullptr, *d_seg = nullptr, *d_seg_v = nullptr, *d_seg_vel = nullptr;
-    int32_t *d_seg_guard = nullptr, *d_items = nullptr;
-    std::vector<int32_t> h_items;  // host copy of the work items
+    int32_t *d_seg_guard = nullptr, *d_items = nullptr, *d_groups = nullptr;
+    std::vector<int32_t> h_groups;  // host copy of the groups (first item, items)
+    int64_t n_groups_kept = 0;      // of them, those of the kept items
     double footprint_cells = 1.0;  // cells of the footprint (batch cost estimates)
     double vmax = 0.0;             // largest |v| of the grid, Q8 px/h
     // sort path
@@ -229,7 +230,8 @@ DenseArgs dense_args(const sas_plan *p, const WsLayout &L, char *w, const PrepBu
     a.cat.n_epochs = p->n_epochs;
     a.cat.ncx = p->ncx;
     a.cat.ncy = p->ncy;
-    a.cat.cell_log2 = p->cell_log2;
+    a.cat.cell_log2_x = p->cell_log2_x;
+    a.cat.cell_log2_y = p->cell_log2;
     a.cat.x0 = p->ext[0];
     a.cat.x1 = p->ext[1];
     a.cat.y0 = p->ext[2];
@@ -256,7 +258,9 @@ DenseArgs dense_args(const sas_plan *p, const WsLayout &L, char *w, const PrepBu
     a.seg_guard = p->d_seg_guard;
     a.items = p->d_items;
     a.n_items = p->n_items;
-    a.n_items_kept = p->n_items_kept;
+    a.groups = (const int2 *)p->d_groups;
+    a.n_groups = (int64_t)p->h_groups.size() / 2;
+    a.n_groups_kept = p->n_groups_kept;
     a.e_first = p->e_first;
     a.refine = (int4 *)(w + L.refine);
     a.refine_count = pb.refine_count;
@@ -395,15 +399,25 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
     // the guard cells of a tile grow with that spread, so blocks are kept
     // near one cell of spread where possible.
     int G = tu.groups;
+    const double spread8 = 7.0 * (double)d->binw_q8 / (double)cellw;  // 8 steps, in cells
     if (G == 0) {
-        const double spread8 = 7.0 * (double)d->binw_q8 / (double)cellw;  // 8 steps, in cells
         G = spread8 <= 2.0 ? 1 : 2;
     }
     if (G != 1 && G != 2 && G != 4)
         return fail(SAS_E_INVALID, "sas_plan_create: groups must be 1, 2 or 4");
     const int NV = 64 / G;
-    const int32_t vbx = tu.vblock_x ? tu.vblock_x : (G == 4 ? 4 : 8);
-    const int32_t vby = tu.vblock_y ? tu.vblock_y : (G == 1 ? 8 : 4);
+    // Two lane groups spread over twice as many steps along one axis as along
+    // the other, and their tiles come out as long along it: that is the
+    // footprint's long side, where fewer tiles hang over its edges (180 k
+    // detections in 60 epochs on 2048 x 4096 px: blocks 8 x 4 / 4 x 8 61.5 /
+    // 56.9 ms, on 4096 x 2048 px 56.5 / 60.9).  Cells below 16 px (2^12 Q8)
+    // give nearly square packed tiles and keep 8 x 4, which takes fewer index
+    // rows (160 k in 40, slow velocities: 9.26 / 9.43 ms; 75 k: 7.58 / 7.78).
+    // A caller's own tile keeps the block it was chosen with.
+    const bool tall = G == 2 && kc >= 12 && ex[3] - ex[2] > ex[1] - ex[0] && !tu.vblock_x &&
+                      !tu.vblock_y && !tu.tile_x && !tu.tile_y;
+    const int32_t vbx = tu.vblock_x ? tu.vblock_x : (G == 4 || tall ? 4 : 8);
+    const int32_t vby = tu.vblock_y ? tu.vblock_y : (G == 1 || tall ? 8 : 4);
     if (vbx < 1 || vby < 1 || vbx * vby > NV)
         return fail(SAS_E_INVALID, "sas_plan_create: vblock_x * vblock_y must be in [1, 64 / groups]");
 
@@ -541,6 +555,12 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
         return !weighted && tu.packed >= 0 && ((tx + guard_x) << kc) <= 65536 &&
                ((ty + guard_y) << kc) <= 65536 && (tx + guard_x) * bin_words_of(true) * 4 <= 65535;
     };
+    // Two groups with 16-bit counts and 32-bit votes give the histogram 16 / 20
+    // of the budget, since narrow index cells leave the stage less to hold (15
+    // / 16: 92.4 / 88.6 ms at 78 k detections in 93 epochs, 57.0 / 56.4 at
+    // 180 k in 60, 108.0 / 105.1 at 300 k in 89); a packed tile, where one
+    // fits, is preferred to a slightly better shape (9.7 against 10.3 ms at
+    // 150 k in 60, slow velocities).
     // tile shape: the largest interior under the histogram budget with the
     // best ratio of interior to window area (exact windows: the window adds
     // the average spread of a block to each side length); one lane group
@@ -556,24 +576,34 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
                 const bool pk = packs(tx, ty);
                 if (packed_only && !pk) continue;
                 // the stage of a packed tile takes half the bytes
-                const size_t hist_budget = target * (pk ? 17 : 15) / 20;
+                const bool two_halves = G == 2 && halves_of(pk) == 2;
+                const size_t hist_budget = target * (pk ? 17 : two_halves ? 16 : 15) / 20;
                 const size_t hb = (size_t)(tx + guard_x) * (ty + guard_y) * bin_words_of(pk) * 4;
                 if (hb > hist_budget) continue;
                 const double wx = tx + 0.5 * spread_x_avg / cellw + 0.5;
                 const double wy = ty + 0.5 * spread_y_avg / cellw + 0.5;
-                const double score = (double)tx * ty / (wx * wy);
+                const double score = (double)tx * ty / (wx * wy) * (two_halves && pk ? 1.05 : 1.0);
                 if (score > best + 1e-9) {
                     best = score;
                     TX = tx;
                     TY = ty;
                 }
             }
-        return best >= 0;
+        return best;
     };
-    bool three = false;  // three workgroups per CU
+    // three workgroups per CU unless the packed tile is much the smaller (cells
+    // of 32 px: 6 x 6 cells, 3.96 ms at 50 k detections in 120 epochs, against
+    // 2.61 with 14 x 11 unpacked ones)
+    bool three = false;
     if (!TX || !TY) {
-        three = three_ok && search(lds_target3, true);
-        if (!three && !search(lds_target2, false)) {
+        const double p3 = three_ok ? search(lds_target3, true) : -1.0;
+        const int32_t x3 = TX, y3 = TY;
+        const double p2 = search(lds_target2, false);
+        three = p3 >= 0 && p3 >= 0.9 * p2;
+        if (three) {
+            TX = x3;
+            TY = y3;
+        } else if (p2 < 0) {
             TX = tu.tile_x ? tu.tile_x : 1;
             TY = tu.tile_y ? tu.tile_y : 1;
         }
@@ -588,12 +618,38 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
     const int halves = halves_of(packed != 0);
     const int64_t bin_words = bin_words_of(packed != 0);
     const size_t entry_bytes = packed ? sizeof(uint32_t) : sizeof(int2);
-    if (!cl) cl = kc + 1;  // window-index cells of 2 x 2 histogram cells
+    // Window-index cells.  Along x the runs end at cell borders and finer
+    // cells only cost offsets, so that cells of half a histogram cell let a
+    // window read little past its edges; along y each row is a run of its
+    // own, and cells of four histogram cells (two: 110 k detections in 60
+    // epochs, slow velocities 3.99 against 3.89 ms, 50 k in 40 2.96 against
+    // 2.85) grow until a wave's (epoch, row) pairs fit.  Cells 2, 1,
+    // 1/2 and 1/4 histogram cells wide against cells as wide as high, vote
+    // kernel: 300 k detections in 100 epochs at slow velocities 7.50, 7.27,
+    // 7.14 and 7.36 ms against 7.78; 180 k in 60 epochs at fast ones 57.9,
+    // 57.2, 56.9 and 56.7 against 58.8.  At most kIndexCells cells then (the
+    // offsets of a quarter cell in the first of these, 13 MB a copy, no longer
+    // fit the L2 caches), and no more than the one-workgroup preparation
+    // takes where square cells stay below that.  The sort path reads whole
+    // rows and keeps square cells, as does a caller's own cell_log2 while the
+    // rows fit.
+    constexpr int64_t kIndexCells = (int64_t)1 << 21;
+    int clx = d->path == SAS_PATH_SORT ? 30 : cl ? cl : std::max(kc - 1, 0);
+    if (!cl) cl = kc + 2;
     while (ncells_of(cl, ex[0], ex[1]) > 32767 || ncells_of(cl, ex[2], ex[3]) > 32767 ||
            ((((int64_t)d->n_epochs + 7) / 8) << log2_ceil(rows_bound(cl, TY))) > kMaxWavePairs)
         ++cl;
     if (cl > 30) return fail(SAS_E_UNSUPPORTED, "sas_plan_create: footprint too large");
-    const int64_t ncx = ncells_of(cl, ex[0], ex[1]), ncy = ncells_of(cl, ex[2], ex[3]);
+    const int64_t ncy = ncells_of(cl, ex[2], ex[3]);
+    {
+        const int64_t square = (int64_t)d->n_epochs * ncells_of(cl, ex[0], ex[1]) * ncy;
+        const int64_t most = square <= kSmallCells ? kSmallCells : kIndexCells;
+        clx = std::min(clx, cl);
+        while (clx < cl && (ncells_of(clx, ex[0], ex[1]) > 32767 ||
+                            (int64_t)d->n_epochs * ncells_of(clx, ex[0], ex[1]) * ncy > most))
+            ++clx;
+    }
+    const int64_t ncx = ncells_of(clx, ex[0], ex[1]);
     const int64_t n_cells = (int64_t)d->n_epochs * ncx * ncy;
     // the column-major copy of the offsets holds E (ncx + 1) ncy words
     if (n_cells >= ((int64_t)1 << 30) || (int64_t)d->n_epochs * (ncx + 1) * ncy >= ((int64_t)1 << 30))
@@ -681,6 +737,7 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
     p->packed = packed;
     p->lds_bytes = lds + lds_static;
     p->cell_log2 = cl;
+    p->cell_log2_x = clx;
     p->ncx = (int32_t)ncx;
     p->ncy = (int32_t)ncy;
     p->n_cells = n_cells;
@@ -841,6 +898,26 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
     p->n_segments = n_seg;
     p->n_items_kept = (int64_t)items.size() / 4;
     items.insert(items.end(), tail.begin(), tail.end());
+    // Groups of rows: consecutive items of one segment (a band's rows), as many
+    // as leave every workgroup slot kSlotGroups groups, so that the last ones
+    // to finish do not hold up a launch for long (rows one by one / by four,
+    // 180 k detections in 60 epochs, 2.3 M rows: 64.4 / 61.8 ms; 300 k in 100,
+    // 88 k rows: 7.61 / 7.78, so that those stay single).
+    constexpr int64_t kGroupRows = 4, kSlotGroups = 256;
+    const int64_t rows_max =
+        packed ? 1
+               : std::max<int64_t>(1, std::min<int64_t>(kGroupRows, p->n_items_kept /
+                                                                        (kSlots * kSlotGroups)));
+    std::vector<int32_t> groups;
+    for (int64_t q = 0, n_it = (int64_t)items.size() / 4; q < n_it;) {
+        int64_t k = q + 1;
+        while (k < n_it && k != p->n_items_kept && k - q < rows_max &&
+               items[4 * k] == items[4 * q])
+            ++k;
+        groups.insert(groups.end(), {(int32_t)q, (int32_t)(k - q)});
+        if (q < p->n_items_kept) p->n_groups_kept = (int64_t)groups.size() / 2;
+        q = k;
+    }
     p->n_items = (int64_t)items.size() / 4;
     p->n_tiles = n_tiles;
     p->n_tiles_kept = n_tiles_kept;
@@ -939,7 +1016,8 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
     if ((st = upload(p.get(), &p->d_seg_vel, seg_vel)) != SAS_OK) goto fail_free;
     if ((st = upload(p.get(), &p->d_seg_guard, seg_guard)) != SAS_OK) goto fail_free;
     if ((st = upload(p.get(), &p->d_items, items)) != SAS_OK) goto fail_free;
-    p->h_items = items;
+    if ((st = upload(p.get(), &p->d_groups, groups)) != SAS_OK) goto fail_free;
+    p->h_groups = groups;
     for (int64_t j = 0; j < n_v; ++j)
         p->vmax = std::max(p->vmax, std::sqrt((double)V[2 * j] * V[2 * j] +
                                               (double)V[2 * j + 1] * V[2 * j + 1]));
@@ -1032,7 +1110,7 @@ sas_status vote_impl(const sas_plan *p, const int32_t *x_q8, const int32_t *y_q8
     char *w = (char *)workspace;
     const PrepBuffers pb = prep_buffers(L, w);
     hipError_t e = launch_prep(x_q8, y_q8, epoch, weight, n, p->d_t, p->n_epochs, p->ncx, p->ncy,
-                               p->cell_log2, p->ext, p->n_cells, pb, res_dev, s);
+                               p->cell_log2_x, p->cell_log2, p->ext, p->n_cells, pb, res_dev, s);
     if (e != hipSuccess) return hip_fail(e, "sas_vote: preparation launch");
     if (n == 0 || p->n_v == 0) return SAS_OK;
 
@@ -1178,8 +1256,8 @@ struct sas_batch {
     };
     struct Class {
         int mode = 0, groups = 1, packed = 0;
-        int32_t *d_items5 = nullptr;
-        int64_t n_items = 0, n_kept = 0;
+        int32_t *d_groups3 = nullptr;
+        int64_t n_groups = 0, n_kept = 0;
         int32_t hist_words_max = 0;
         size_t lds = 0;
     };
@@ -1271,7 +1349,7 @@ sas_status sas_batch_create(const sas_batch_chip *chips, int32_t n_chips, void *
     // a chip: its tiles times (expected votes of a tile + a fixed per-tile
     // cost in vote units).
     struct It {
-        int32_t v[5];
+        int32_t v[3];
     };
     std::vector<double> chip_cost(n_chips, 0.0);
     for (int32_t c = 0; c < n_chips; ++c) {
@@ -1291,15 +1369,9 @@ sas_status sas_batch_create(const sas_batch_chip *chips, int32_t n_chips, void *
         const sas_plan *p = chips[c].plan;
         if (chips[c].n == 0 || p->n_items == 0) continue;
         const int k = batch_class(p);
-        for (int64_t q = 0; q < p->n_items; ++q) {
-            It it;
-            const int32_t *src = &p->h_items[4 * q];
-            const bool kept = q < p->n_items_kept;
-            it.v[0] = kept ? c : ~c;  // skipped tiles carry ~chip
-            it.v[1] = src[0];
-            it.v[2] = src[1];
-            it.v[3] = src[2];
-            it.v[4] = src[3];
+        for (int64_t q = 0; q < (int64_t)p->h_groups.size() / 2; ++q) {
+            const bool kept = q < p->n_groups_kept;  // skipped tiles carry ~chip
+            const It it{{kept ? c : ~c, p->h_groups[2 * q], p->h_groups[2 * q + 1]}};
             (kept ? per_class[k] : tails[k]).push_back(it);
         }
     }
@@ -1314,8 +1386,8 @@ sas_status sas_batch_create(const sas_batch_chip *chips, int32_t n_chips, void *
         cl.groups = (k / 2 % 3 == 0) ? 1 : (k / 2 % 3 == 1) ? 2 : 4;
         cl.packed = k % 2;
         std::vector<int32_t> flat;
-        flat.reserve(v.size() * 5);
-        for (const It &it : v) flat.insert(flat.end(), it.v, it.v + 5);
+        flat.reserve(v.size() * 3);
+        for (const It &it : v) flat.insert(flat.end(), it.v, it.v + 3);
         for (int32_t c = 0; c < n_chips; ++c) {
             const sas_plan *p = chips[c].plan;
             if (batch_class(p) != k) continue;
@@ -1324,7 +1396,7 @@ sas_status sas_batch_create(const sas_batch_chip *chips, int32_t n_chips, void *
             cl.lds = std::max(cl.lds, dense_lds_bytes(p->groups, p->hx, p->hy, p->stage_cap,
                                                       p->packed, p->halves));
         }
-        cl.n_items = (int64_t)v.size();
+        cl.n_groups = (int64_t)v.size();
         void *d = nullptr;
         hipError_t e = hipMalloc(&d, flat.size() * sizeof(int32_t));
         if (e != hipSuccess) {
@@ -1337,7 +1409,7 @@ sas_status sas_batch_create(const sas_batch_chip *chips, int32_t n_chips, void *
             for (void *a : bt->allocs) hipFree(a);
             return hip_fail(e, "sas_batch_create: item upload");
         }
-        cl.d_items5 = (int32_t *)d;
+        cl.d_groups3 = (int32_t *)d;
         bt->classes.push_back(cl);
     }
     void *q = nullptr;
@@ -1396,7 +1468,8 @@ sas_status sas_vote_batch(const sas_batch *b, void *stream) {
         const sas_plan *p = ch.b.plan;
         char *w = b->ws + ch.ws_off;
         e = launch_prep(ch.b.x_q8, ch.b.y_q8, ch.b.epoch, nullptr, ch.b.n, p->d_t, p->n_epochs, p->ncx,
-                        p->ncy, p->cell_log2, p->ext, p->n_cells, prep_buffers(ch.L, w),
+                        p->ncy, p->cell_log2_x, p->cell_log2, p->ext, p->n_cells,
+                        prep_buffers(ch.L, w),
                         ch.b.res_dev, s);
         if (e != hipSuccess) return hip_fail(e, "sas_vote_batch: preparation launch");
     }
@@ -1405,7 +1478,7 @@ sas_status sas_vote_batch(const sas_batch *b, void *stream) {
     for (size_t k = 0; k < b->classes.size(); ++k) {
         const sas_batch::Class &cl = b->classes[k];
         e = launch_vote_dense_batch(cl.mode, cl.groups, cl.packed, b->d_args,
-                                    (int32_t)b->chips.size(), cl.d_items5, cl.n_items, cl.n_kept,
+                                    (int32_t)b->chips.size(), cl.d_groups3, cl.n_groups, cl.n_kept,
                                     cl.hist_words_max, cl.lds, b->queues + kXcds * k,
                                     b->counter, s);
         if (e != hipSuccess) return hip_fail(e, "sas_vote_batch: vote launch");

@@ -74,8 +74,8 @@ __device__ __attribute__((always_inline)) inline void walk_cell(const ExtractArg
         const int64_t ylo = ((int64_t)cd.by << lb) + shift_q8(vy, d);
         int cx0 = 0, cx1 = 0, cy = 0, cy1 = -1;
         if (d >= 0) {
-            if (!cell_span(xlo, xlo + ((int64_t)1 << lb), c.x0, c.x1, c.cell_log2, &cx0, &cx1) ||
-                !cell_span(ylo, ylo + ((int64_t)1 << lb), c.y0, c.y1, c.cell_log2, &cy, &cy1))
+            if (!cell_span(xlo, xlo + ((int64_t)1 << lb), c.x0, c.x1, c.cell_log2_x, &cx0, &cx1) ||
+                !cell_span(ylo, ylo + ((int64_t)1 << lb), c.y0, c.y1, c.cell_log2_y, &cy, &cy1))
                 cy1 = cy - 1;
         }
         int32_t j = 0, j1 = 0;

@@ -303,10 +303,10 @@ __global__ void __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(5))) k_
                         const int64_t xhi = xlo + ((int64_t)1 << lb),
                                       yhi = ylo + ((int64_t)1 << lb);
                         if (xhi > c.x0 && xlo < c.x1 && yhi > c.y0 && ylo < c.y1) {
-                            cx0 = (int)((max(xlo, (int64_t)c.x0) - c.x0) >> c.cell_log2);
-                            cx1 = (int)((min(xhi, (int64_t)c.x1) - 1 - c.x0) >> c.cell_log2);
-                            cy = (int)((max(ylo, (int64_t)c.y0) - c.y0) >> c.cell_log2);
-                            cy1 = (int)((min(yhi, (int64_t)c.y1) - 1 - c.y0) >> c.cell_log2);
+                            cx0 = (int)((max(xlo, (int64_t)c.x0) - c.x0) >> c.cell_log2_x);
+                            cx1 = (int)((min(xhi, (int64_t)c.x1) - 1 - c.x0) >> c.cell_log2_x);
+                            cy = (int)((max(ylo, (int64_t)c.y0) - c.y0) >> c.cell_log2_y);
+                            cy1 = (int)((min(yhi, (int64_t)c.y1) - 1 - c.y0) >> c.cell_log2_y);
                         }
                     }
                     continue;

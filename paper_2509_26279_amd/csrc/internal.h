@@ -12,6 +12,7 @@ constexpr int kMaxEpochs = 256;
 constexpr int kVoteThreads = 512;          // threads per vote workgroup
 constexpr int kVoteWaves = kVoteThreads / 64;
 constexpr int kMaxWavePairs = 128;         // (epoch, index row) pairs of one wave's windows
+constexpr int64_t kSmallCells = 12287;     // window-index cells of the one-workgroup preparation
 constexpr int kSlotWords = kMaxEpochs / 32;
 constexpr int kLdsPerCU = 160 * 1024;      // gfx950
 constexpr int kXcds = 8;                   // MI355X: accelerator dies, one L2 each
@@ -42,7 +43,7 @@ struct PreparedCatalog {
                           // column are adjacent
     const int32_t *dt;    // [E] t[e] - t0, Q16 h; -1 for epochs without detections
     int32_t n_epochs;
-    int32_t ncx, ncy, cell_log2;
+    int32_t ncx, ncy, cell_log2_x, cell_log2_y;
     int32_t x0, x1, y0, y1;
 };
 
@@ -69,7 +70,10 @@ struct DenseArgs {
     const int32_t *seg_guard; // [n_seg][NV] left guard cells gx | gy << 16
     const int32_t *items;     // [n_items][4] segment, ty0, first tx0, number of tiles
     int64_t n_items;
-    int64_t n_items_kept;     // items [0, n_items_kept) suffice when epoch e_first (the
+    const int2 *groups;       // [n_groups] first item and items of each group: rows of one
+                              // segment that a workgroup walks in sequence
+    int64_t n_groups;
+    int64_t n_groups_kept;    // groups [0, n_groups_kept) suffice when epoch e_first (the
     int32_t e_first;          // earliest scheduled) holds a detection; the rest hold only
                               // tiles that fewer than N_min epochs can reach from it
     int4 *refine;             // [refine_cap] queued (v_idx, cell x, cell y, 0)
@@ -105,7 +109,8 @@ constexpr int64_t kScanTile = (int64_t)kScanThreads * kScanPerThread;
 hipError_t launch_prep(const int32_t *x, const int32_t *y, const uint8_t *epoch,
                        const uint8_t *weight, int64_t n,
                        const int64_t *t_dev, int32_t n_epochs, int32_t ncx, int32_t ncy,
-                       int32_t cell_log2, const int32_t ext[4], int64_t n_cells,
+                       int32_t cell_log2_x, int32_t cell_log2_y, const int32_t ext[4],
+                       int64_t n_cells,
                        const PrepBuffers &pb, sas_vote_result *res, hipStream_t stream);
 
 // Exclusive scan of n int32 in place (blocksum: (n + kScanTile - 1) / kScanTile);
@@ -265,12 +270,12 @@ hipError_t mlp_refresh(const MlpBuffers &b, hipStream_t s);
 // ev0 / ev1 (optional) are recorded on the stream around the vote kernel.
 hipError_t launch_vote_dense(int mode, int groups, const DenseArgs &a, hipStream_t stream,
                              hipEvent_t ev0, hipEvent_t ev1);
-// One persistent launch over the merged items (chip, segment, ty0, txf,
-// ntiles) of many chips of one kernel class: every chip's kept items first
+// One persistent launch over the merged groups (chip, first item, rows) of
+// many chips of one kernel class: every chip's kept groups first
 // (n_kept of them), then the tiles skipped by coverage.  queue: kXcds device
 // counters of this launch's own, zeroed on the stream before the vote kernel.
 hipError_t launch_vote_dense_batch(int mode, int groups, int packed, const DenseArgs *chips_dev,
-                                   int32_t n_chips, const int32_t *items5_dev, int64_t n_items,
+                                   int32_t n_chips, const int32_t *groups3_dev, int64_t n_groups,
                                    int64_t n_kept, int32_t hist_words_max, size_t lds,
                                    unsigned long long *queue, unsigned long long *atomics,
                                    hipStream_t stream);

@@ -71,8 +71,9 @@ __global__ void k_prep_zero(int32_t *count, int64_t n_count, int32_t *present, i
 
 __global__ void k_prep_count(const int32_t *__restrict__ x, const int32_t *__restrict__ y,
                              const uint8_t *__restrict__ epoch, int64_t n, int32_t n_epochs,
-                             int32_t ncx, int32_t ncy, int32_t cell_log2, int32_t x0, int32_t x1,
-                             int32_t y0, int32_t y1, int32_t *__restrict__ count,
+                             int32_t ncx, int32_t ncy, int32_t cell_log2_x, int32_t cell_log2_y,
+                             int32_t x0, int32_t x1, int32_t y0, int32_t y1,
+                             int32_t *__restrict__ count,
                              int32_t *__restrict__ cellid, int32_t *__restrict__ rank,
                              int32_t *__restrict__ present, sas_vote_result *res) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -85,8 +86,8 @@ __global__ void k_prep_count(const int32_t *__restrict__ x, const int32_t *__res
     } else if (xi < x0 || xi >= x1 || yi < y0 || yi >= y1) {
         atomicOr(&res->status, SAS_DATA_OUTSIDE);
     } else {
-        const int32_t cx = (xi - x0) >> cell_log2;
-        const int32_t cy = (yi - y0) >> cell_log2;
+        const int32_t cx = (xi - x0) >> cell_log2_x;
+        const int32_t cy = (yi - y0) >> cell_log2_y;
         c = (e * ncy + cy) * ncx + cx;
         rank[i] = atomicAdd(&count[c], 1);
         present[e] = 1;
@@ -193,14 +194,14 @@ __global__ void k_prep_scatter(const int32_t *__restrict__ x, const int32_t *__r
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallPerThread = 8;
 constexpr int64_t kSmallDet = (int64_t)kSmallThreads * kSmallPerThread;
-constexpr int64_t kSmallCount = 12288;  // cells, and one (48 KB of LDS)
+constexpr int64_t kSmallCount = kSmallCells + 1;  // cells, and one (48 KB of LDS)
 
 __global__ void __launch_bounds__(kSmallThreads)
 k_prep_small(const int32_t *__restrict__ x, const int32_t *__restrict__ y,
              const uint8_t *__restrict__ epoch, const uint8_t *__restrict__ weight, int32_t n,
              const int64_t *__restrict__ t, int32_t n_epochs, int32_t ncx, int32_t ncy,
-             int32_t cell_log2, int32_t x0, int32_t x1, int32_t y0, int32_t y1, PrepBuffers pb,
-             sas_vote_result *res) {
+             int32_t cell_log2_x, int32_t cell_log2_y, int32_t x0, int32_t x1, int32_t y0,
+             int32_t y1, PrepBuffers pb, sas_vote_result *res) {
     __shared__ int32_t count[kSmallCount];
     __shared__ int32_t present[kMaxEpochs];
     __shared__ long long red[kMaxEpochs];
@@ -225,7 +226,7 @@ k_prep_small(const int32_t *__restrict__ x, const int32_t *__restrict__ y,
         } else if (xi < x0 || xi >= x1 || yi < y0 || yi >= y1) {
             atomicOr(&status, SAS_DATA_OUTSIDE);
         } else {
-            cell[k] = (e * ncy + ((yi - y0) >> cell_log2)) * ncx + ((xi - x0) >> cell_log2);
+            cell[k] = (e * ncy + ((yi - y0) >> cell_log2_y)) * ncx + ((xi - x0) >> cell_log2_x);
             rank[k] = atomicAdd(&count[cell[k]], 1);
             present[e] = 1;
             at[k] = make_int2(weight ? (int32_t)(((uint32_t)xi << 8) | weight[i]) : xi, yi);
@@ -300,12 +301,12 @@ hipError_t launch_scan_exclusive(int32_t *data, int64_t n, int32_t *blocksum, hi
 hipError_t launch_prep(const int32_t *x, const int32_t *y, const uint8_t *epoch,
                        const uint8_t *weight, int64_t n,
                        const int64_t *t_dev, int32_t n_epochs, int32_t ncx, int32_t ncy,
-                       int32_t cell_log2, const int32_t ext[4], int64_t n_cells,
-                       const PrepBuffers &pb, sas_vote_result *res, hipStream_t stream) {
+                       int32_t cell_log2_x, int32_t cell_log2_y, const int32_t ext[4],
+                       int64_t n_cells, const PrepBuffers &pb, sas_vote_result *res, hipStream_t stream) {
     const int64_t n_count = n_cells + 1;
     if (n <= kSmallDet && n_count <= kSmallCount) {
         hipLaunchKernelGGL(k_prep_small, dim3(1), dim3(kSmallThreads), 0, stream, x, y, epoch,
-                           weight, (int32_t)n, t_dev, n_epochs, ncx, ncy, cell_log2, ext[0],
+                           weight, (int32_t)n, t_dev, n_epochs, ncx, ncy, cell_log2_x, cell_log2_y, ext[0],
                            ext[1], ext[2], ext[3], pb, res);
         return hipGetLastError();
     }
@@ -315,7 +316,7 @@ hipError_t launch_prep(const int32_t *x, const int32_t *y, const uint8_t *epoch,
                        pb.present, n_epochs, res, pb.refine_count, pb.item_queue);
     if (n > 0) {
         hipLaunchKernelGGL(k_prep_count, dim3(blocks_for(n, 256)), dim3(256), 0, stream, x, y,
-                           epoch, n, n_epochs, ncx, ncy, cell_log2, ext[0], ext[1], ext[2],
+                           epoch, n, n_epochs, ncx, ncy, cell_log2_x, cell_log2_y, ext[0], ext[1], ext[2],
                            ext[3], pb.count, pb.cellid, pb.rank, pb.present, res);
     }
     const hipError_t e = launch_scan_exclusive(pb.count, n_count, pb.blocksum, stream, nullptr);

@@ -615,8 +615,8 @@ __global__ void __launch_bounds__(RT) k_refine_clusters(RefineArgs a) {
                     hi_y >= -2147483648.0 && lo_y < 2147483647.0) {
                     const int64_t xlo = (int64_t)floor(lo_x), xhi = (int64_t)floor(hi_x) + 2;
                     const int64_t ylo = (int64_t)floor(lo_y), yhi = (int64_t)floor(hi_y) + 2;
-                    if (!cell_span(xlo, xhi, c.x0, c.x1, c.cell_log2, &cx0, &cx1) ||
-                        !cell_span(ylo, yhi, c.y0, c.y1, c.cell_log2, &cy0, &cy1))
+                    if (!cell_span(xlo, xhi, c.x0, c.x1, c.cell_log2_x, &cx0, &cx1) ||
+                        !cell_span(ylo, yhi, c.y0, c.y1, c.cell_log2_y, &cy0, &cy1))
                         cy1 = cy0 - 1;  // the window misses the footprint
                 }
                 for (int cy2 = cy0 + tid % kGatherRows; cy2 <= cy1; cy2 += kGatherRows) {

@@ -288,7 +288,7 @@ __device__ __attribute__((always_inline)) inline int32_t window_row(
     if (sh.dt[e] < 0) return -1;
     const int32_t ylo = oy + sh.es[e].z, yhi = oy + sh.es[e].w + H;
     int cy0, cy1;
-    if (!cell_span(ylo, yhi, c.y0, c.y1, c.cell_log2, &cy0, &cy1)) return -1;
+    if (!cell_span(ylo, yhi, c.y0, c.y1, c.cell_log2_y, &cy0, &cy1)) return -1;
     if (r == 0 && cy1 - cy0 + 1 > a.rows)  // excluded by the planner
         __hip_atomic_fetch_or(gmem(&a.res->status), (int32_t)SAS_DATA_INTERNAL, __ATOMIC_RELAXED,
                               __HIP_MEMORY_SCOPE_AGENT);
@@ -305,7 +305,7 @@ __device__ __attribute__((always_inline)) inline void window_run(
     end = 0;
     if (row < 0) return;
     int cx0, cx1;
-    if (!cell_span(oxw + sh.es[e].x, oxw + sh.es[e].y + W, c.x0, c.x1, c.cell_log2, &cx0,
+    if (!cell_span(oxw + sh.es[e].x, oxw + sh.es[e].y + W, c.x0, c.x1, c.cell_log2_x, &cx0,
                    &cx1))
         return;
     src = gmem(c.offT)[row + cx0 * c.ncy];
@@ -369,15 +369,20 @@ constexpr int kStageBlocks = 1;
 
 // Dynamic LDS: histogram [HY][HX][NV] words, then the stage (int2), one
 // part of stage_cap / NW detections per wave.
-// One work item: a segment and a row of ntiles tiles starting at tile column
-// txf (cells), tile row ty0.  The histogram is all zero on entry and on exit;
-// sh.dt holds the catalog's d_e.
+// One group of work items: a segment and n_rows rows of tiles, each an entry
+// (segment, tile row ty0, first tile column, tiles) of the item table, walked
+// as one sequence of tiles: the first tile of a row is staged while the last
+// one of the row before it is voted, as any next tile is, and the segment's
+// tables, shifts and guard check are set up once (180 k detections in 60
+// epochs: 64.4 ms a row at a time, 61.8 with four rows in a group).
+// The histogram is all zero on entry and on exit; sh.dt holds the catalog's d_e.
 template <int MODE, int G, bool PK>
-__device__ void vote_item(const DenseArgs &a, Shared &sh, uint4 *smem4, int32_t sg, int32_t ty0,
-                          int32_t txf, int32_t ntiles, int32_t &tseq) {
+__device__ void vote_rows(const DenseArgs &a, Shared &sh, uint4 *smem4, const int32_t *items,
+                          int32_t n_rows, int32_t &tseq) {
     constexpr int NV = 64 / G;
     constexpr int LNV = G == 1 ? 6 : G == 2 ? 5 : 4;
     constexpr bool WT = weighted_mode<MODE>();
+    constexpr bool ROWS = !PK;  // several rows a group
     static_assert(!(WT && PK), "weighted votes use the 32-bit form");
     typedef typename std::conditional<
         PK, VoteAddr16, typename std::conditional<WT, VoteAddr32W, VoteAddr32>::type>::type VA;
@@ -418,6 +423,8 @@ __device__ void vote_item(const DenseArgs &a, Shared &sh, uint4 *smem4, int32_t 
     const bool hv = G == 1 && !PK && kHalvesOk && a.halves == 1;
     const bool hs = (G > 1 || PK) && kHalvesOk && a.halves == 2;
     const int LR = a.rows_log2;  // run rows per epoch: 2^LR
+    const int32_t sg = gmem(items)[0];
+    int32_t ty0 = gmem(items)[1], tx0 = gmem(items)[2], tiles = gmem(items)[3];  // left in the row
     const int32_t vx_lo = gmem(a.seg)[4 * sg], vx_hi = gmem(a.seg)[4 * sg + 1];
     const int32_t vy_lo = gmem(a.seg)[4 * sg + 2], vy_hi = gmem(a.seg)[4 * sg + 3];
     __syncthreads();  // the previous item no longer reads the segment tables
@@ -438,9 +445,6 @@ __device__ void vote_item(const DenseArgs &a, Shared &sh, uint4 *smem4, int32_t 
     __syncthreads();
     const int32_t my_vx = sh.svx[j], my_vy = sh.svy[j];
     const int32_t my_gx = sh.sg[j] & 0xffff, my_gy = sh.sg[j] >> 16;
-    const int32_t oy = ty0 * cellw;
-    // Q8 origin of this lane's histogram row 0: (ty0 - gy) cells
-    const uint32_t oy_lane = (uint32_t)(ty0 - my_gy) * (uint32_t)cellw;
     // The current tile's histogram form (block uniform):
     //   kForm32: 32-bit counts, NV words per bin;
     //   kFormHalves: 16-bit halves, NV / 2 words per bin (halves = 1: the
@@ -472,12 +476,17 @@ __device__ void vote_item(const DenseArgs &a, Shared &sh, uint4 *smem4, int32_t 
     set_form(hs ? kFormHalves : kForm32, 0, 0);
 
     // Lane shifts of this wave's epochs e = wave + k NW (k < ER), kept in
-    // registers for the whole item with the Q8 origin of the lane's
+    // registers for the whole group with the Q8 origin of the lane's
     // histogram added (row 0 at ty0 - gy cells, column 0 at tx0 - gx cells of
     // the current tile; packed: low 16 bits of x and y in one register).  The
     // window of any tile lands inside every lane's histogram (tile
     // independent; checked here).
-    const uint32_t ox_lane0 = (uint32_t)(txf - my_gx) * (uint32_t)cellw;
+    const auto lane_x = [&]() __attribute__((always_inline)) {
+        return (uint32_t)(tx0 - my_gx) * (uint32_t)cellw;
+    };
+    const auto lane_y = [&]() __attribute__((always_inline)) {
+        return (uint32_t)(ty0 - my_gy) * (uint32_t)cellw;
+    };
     int32_t Sx[ER], Sy[PK ? 1 : ER];
     bool bad = false;
     const auto guard_fails = [&](int e, int64_t sxe, int64_t sye) __attribute__((always_inline)) {
@@ -500,10 +509,10 @@ __device__ void vote_item(const DenseArgs &a, Shared &sh, uint4 *smem4, int32_t 
             }
         }
         if (PK) {
-            Sx[k] = (int32_t)pack16(sxe + (int32_t)ox_lane0, sye + (int32_t)oy_lane);
+            Sx[k] = (int32_t)pack16(sxe + (int32_t)lane_x(), sye + (int32_t)lane_y());
         } else {
-            Sx[k] = (int32_t)((uint32_t)(sxe + (int32_t)ox_lane0) << (WT ? 8 : 0));
-            Sy[PK ? 0 : k] = sye + (int32_t)oy_lane;
+            Sx[k] = (int32_t)((uint32_t)(sxe + (int32_t)lane_x()) << (WT ? 8 : 0));
+            Sy[PK ? 0 : k] = sye + (int32_t)lane_y();
         }
     }
     for (int e = wave + ER * NW; e < E; e += NW) {  // epochs past the registers
@@ -541,11 +550,14 @@ __device__ void vote_item(const DenseArgs &a, Shared &sh, uint4 *smem4, int32_t 
     const auto pair_epoch = [&](int s2) __attribute__((always_inline)) {
         return wave + NW * min((s2 * 64 + lane) >> LR, max(KW - 1, 0));
     };
+    const auto set_row = [&](int32_t oyw) __attribute__((always_inline)) {
 #pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) {
-        const int q = s2 * 64 + lane;
-        rowb[s2] = q < nq ? window_row(a, sh, pair_epoch(s2), q & ((1 << LR) - 1), oy, H) : -1;
-    }
+        for (int s2 = 0; s2 < 2; ++s2) {
+            const int q = s2 * 64 + lane;
+            rowb[s2] =
+                q < nq ? window_row(a, sh, pair_epoch(s2), q & ((1 << LR) - 1), oyw, H) : -1;
+        }
+    };
 
     // a tile's run bounds (window-index offsets), loaded ahead of the scans
     int32_t src[2], end[2];
@@ -580,7 +592,8 @@ __device__ void vote_item(const DenseArgs &a, Shared &sh, uint4 *smem4, int32_t 
     // lane takes the nearest mark at or below it, else the previous block's
     // owner.  kStageBlocks blocks are loaded before any is tested.
     int32_t *const hd = sh.heads[wave];
-    const auto stage_chunk = [&](int32_t oxw, int32_t c0) __attribute__((always_inline)) {
+    const auto stage_chunk = [&](int32_t oxw, int32_t oyw, int32_t c0)
+                                 __attribute__((always_inline)) {
         __builtin_amdgcn_s_setprio(2);
         const int32_t c1 = min(c0 + wcap, Mw);
         const bool two = nq > 64;  // slot 1 holds pairs (wave uniform)
@@ -632,7 +645,7 @@ __device__ void vote_item(const DenseArgs &a, Shared &sh, uint4 *smem4, int32_t 
             for (int u = 0; u < SB; ++u) {
                 const int32_t P0 = b0 + 64 * u;
                 if (P0 >= c1) break;  // wave uniform
-                Window w = window_of(sh, wave + NW * ek[u], oxw, oy, W, H);
+                Window w = window_of(sh, wave + NW * ek[u], oxw, oyw, W, H);
                 if (WT) {  // the index holds 256 x + w
                     w.x0 = (int32_t)((uint32_t)w.x0 << 8);
                     w.x1 = (int32_t)((uint32_t)w.x1 << 8);
@@ -665,10 +678,11 @@ __device__ void vote_item(const DenseArgs &a, Shared &sh, uint4 *smem4, int32_t 
         __builtin_amdgcn_s_setprio(0);
     };
 
-    run_bounds(txf * cellw);
+    set_row(ty0 * cellw);
+    run_bounds(tx0 * cellw);
     runs();
     if (Mw > 0) {
-        stage_chunk(txf * cellw, 0);
+        stage_chunk(tx0 * cellw, ty0 * cellw, 0);
         if (lane == 0) atomicAdd(&sh.voted[tseq & 3], Mw);
     }
     // This barrier publishes the guard check and completes the first tile's
@@ -684,12 +698,24 @@ __device__ void vote_item(const DenseArgs &a, Shared &sh, uint4 *smem4, int32_t 
         return;
     }
     int32_t staged = sh.voted[tseq & 3];  // this tile's total (block uniform)
-    for (int32_t ti = 0; ti < ntiles; ++ti, ++tseq) {
-        const int32_t tx0 = txf + ti * a.tile_x;
-        const int32_t ox = tx0 * cellw;
-        const uint32_t ox_lane = (uint32_t)(tx0 - my_gx) * (uint32_t)cellw;
-        const bool next = ti + 1 < ntiles;  // block uniform
-        const int32_t oxn = ox + a.tile_x * cellw;
+    for (;;) {
+        // the tile after this one: in the row, or the first of the next row
+        bool next = true;  // block uniform
+        int32_t txn = tx0 + a.tile_x, tyn = ty0;
+        if (--tiles == 0) {
+            next = false;
+            if constexpr (ROWS) {
+                if (--n_rows > 0) {
+                    next = true;
+                    items += 4;
+                    tyn = gmem(items)[1];
+                    txn = gmem(items)[2];
+                    tiles = gmem(items)[3];
+                    set_row(tyn * cellw);
+                }
+            }
+        }
+        const int32_t oxn = txn * cellw, oyn = tyn * cellw;
         // the next tile's run bounds load while this tile is voted
         if (next) run_bounds(oxn);
         if (hv) {
@@ -710,7 +736,7 @@ __device__ void vote_item(const DenseArgs &a, Shared &sh, uint4 *smem4, int32_t 
             // 2. vote this wave's entries, chunk by chunk (the first is staged;
             // a second pass stages it again when later chunks replaced it)
             for (int32_t c0 = 0; c0 < Mw; c0 += wcap) {
-                if (c0 > 0 || (pass > 0 && Mw > wcap)) stage_chunk(ox, c0);
+                if (c0 > 0 || (pass > 0 && Mw > wcap)) stage_chunk(tx0 * cellw, ty0 * cellw, c0);
 #pragma unroll
                 for (int k = 0; k < ER; ++k) {
                     const int e = wave + k * NW;
@@ -727,8 +753,8 @@ __device__ void vote_item(const DenseArgs &a, Shared &sh, uint4 *smem4, int32_t 
                     if (n == 0) continue;
                     const int32_t b = __builtin_amdgcn_readlane(my_b, k);
                     const int32_t d = __builtin_amdgcn_readlane(my_d, k);
-                    const int32_t sx = shift_q8(my_vx, d) + (int32_t)ox_lane;
-                    const int32_t sy = shift_q8(my_vy, d) + (int32_t)oy_lane;
+                    const int32_t sx = shift_q8(my_vx, d) + (int32_t)lane_x();
+                    const int32_t sy = shift_q8(my_vy, d) + (int32_t)lane_y();
                     const int32_t sxv = PK   ? (int32_t)pack16(sx, sy)
                                         : WT ? (int32_t)((uint32_t)sx << 8)
                                              : sx;
@@ -742,7 +768,7 @@ __device__ void vote_item(const DenseArgs &a, Shared &sh, uint4 *smem4, int32_t 
             if (last && next) {
                 runs();
                 if (Mw > 0) {
-                    stage_chunk(oxn, 0);
+                    stage_chunk(oxn, oyn, 0);
                     if (lane == 0) atomicAdd(&sh.voted[(tseq + 1) & 3], Mw);
                 }
             }
@@ -845,15 +871,22 @@ __device__ void vote_item(const DenseArgs &a, Shared &sh, uint4 *smem4, int32_t 
             // histogram, cleared before this tile's barrier
             if (!(hv && form == kFormHalves)) __syncthreads();
         }  // passes
+        ++tseq;
+        if (!next) break;
+        const int32_t dx = (ROWS ? txn - tx0 : a.tile_x) * cellw;
+        const int32_t dy = ROWS ? (tyn - ty0) * cellw : 0;
 #pragma unroll
         for (int k = 0; k < ER; ++k) {
             if constexpr (PK) {  // low half only, modulo 2^16
-                const us2 step = {(unsigned short)(a.tile_x << kc), 0};
+                const us2 step = {(unsigned short)dx, 0};
                 Sx[k] = (int32_t)__builtin_bit_cast(uint32_t, __builtin_bit_cast(us2, Sx[k]) + step);
             } else {
-                Sx[k] = (int32_t)((uint32_t)Sx[k] + ((uint32_t)(a.tile_x * cellw) << (WT ? 8 : 0)));
+                Sx[k] = (int32_t)((uint32_t)Sx[k] + ((uint32_t)dx << (WT ? 8 : 0)));
+                Sy[PK ? 0 : k] += dy;
             }
         }
+        tx0 = txn;
+        ty0 = tyn;
     }
 }
 
@@ -881,10 +914,10 @@ __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(kWavesPe
         sh.spill[0] = sh.spill[1] = 0;
         sh.n_spill = 0;
     }
-    // The items past n_items_kept hold tiles that fewer than N_min epochs
+    // The groups past n_groups_kept hold tiles that fewer than N_min epochs
     // reach when the reference epoch is the earliest scheduled one; they are
     // voted only when that epoch holds no detection (then t0 is later).
-    const int64_t n_walk = a.cat.dt[a.e_first] == 0 ? a.n_items_kept : a.n_items;
+    const int64_t n_walk = a.cat.dt[a.e_first] == 0 ? a.n_groups_kept : a.n_groups;
     // Persistent workgroups (as many as are resident) take items from queues:
     // XCD x's range is [x n / 8, (x + 1) n / 8) of the L2-friendly item order
     // and workgroups are dispatched round-robin over the XCDs (each with its
@@ -895,8 +928,8 @@ __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(kWavesPe
     if constexpr (EACH) {
         // few items: no queues
         for (int64_t q = blockIdx.x; q < n_walk; q += gridDim.x) {
-            const int32_t *it = a.items + 4 * q;
-            vote_item<MODE, G, PK>(a, sh, smem4, it[0], it[1], it[2], it[3], tseq);
+            const int2 g = a.groups[q];
+            vote_rows<MODE, G, PK>(a, sh, smem4, a.items + 4 * (int64_t)g.x, g.y, tseq);
         }
     } else {
         const int x0 = blockIdx.x % kXcds;
@@ -907,10 +940,11 @@ __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(kWavesPe
                 __syncthreads();  // every thread has read the previous ticket
                 if (tid == 0) sh.ticket = atomicAdd(&a.item_queue[x], 1ull);
                 __syncthreads();
-                const int64_t t = (int64_t)sh.ticket;  // block uniform
+                // block uniform: in a scalar register, and so what follows from it
+                const int64_t t = __builtin_amdgcn_readfirstlane((int32_t)sh.ticket);
                 if (t >= n_x) break;
-                const int32_t *it = a.items + 4 * (lo + t);
-                vote_item<MODE, G, PK>(a, sh, smem4, it[0], it[1], it[2], it[3], tseq);
+                const int2 g = a.groups[lo + t];
+                vote_rows<MODE, G, PK>(a, sh, smem4, a.items + 4 * (int64_t)g.x, g.y, tseq);
             }
         }
     }
@@ -922,21 +956,20 @@ __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(kWavesPe
 }
 
 // Many catalogs in one persistent launch (one workgroup per resident slot):
-// the merged items (items5: chip, segment, ty0, txf, ntiles; chip-major, each
-// chip in its own L2-friendly order) are taken from per-XCD queues like the
-// single-catalog kernel takes its items (so an XCD's range holds few chips),
-// and each item reads its chip's parameters from
-// chips[].  Every chip of the launch uses this kernel's cell variant and lane
+// the merged groups (groups3: chip, first item and rows of the chip's item table;
+// chip-major, each chip in its own L2-friendly order) are taken from per-XCD
+// queues like the single-catalog kernel takes its groups (so an XCD's range
+// holds few chips), and each group reads its chip's parameters from chips[].  Every chip of the launch uses this kernel's cell variant and lane
 // groups (and vote form); hist_words_max covers the largest histogram among
-// them.  Items [0, n_kept) are every chip's kept items; the rest hold tiles
+// them.  Groups [0, n_kept) are every chip's kept ones; the rest hold tiles
 // that fewer than N_min epochs reach (see k_vote_dense), with the chip stored
 // as ~chip, voted only for the chips whose earliest scheduled epoch holds no
 // detection.
 template <int MODE, int G, bool PK>
 __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<G, PK>))) k_vote_dense_batch(const DenseArgs *__restrict__ chips,
                                                          int32_t n_chips,
-                                                         const int32_t *__restrict__ items5,
-                                                         int64_t n_items, int64_t n_kept,
+                                                         const int32_t *__restrict__ groups3,
+                                                         int64_t n_groups, int64_t n_kept,
                                                          int32_t hist_words_max,
                                                          unsigned long long *queue,
                                                          unsigned long long *atomics) {
@@ -957,7 +990,7 @@ __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(kWavesPe
     for (int c = tid; c < n_chips; c += T)
         later_t0 |= gmem(chips[c].cat.dt)[chips[c].e_first] != 0;
     later_t0 = __syncthreads_or(later_t0);
-    const int64_t n_walk = later_t0 ? n_items : n_kept;
+    const int64_t n_walk = later_t0 ? n_groups : n_kept;
     const int x0 = blockIdx.x % kXcds;
     for (int k = 0; k < kXcds; ++k) {
       const int x = (x0 + k) % kXcds;
@@ -966,10 +999,10 @@ __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(kWavesPe
         __syncthreads();  // every thread has read the previous ticket
         if (tid == 0) sh.ticket = atomicAdd(&queue[x], 1ull);
         __syncthreads();
-        const int64_t t = (int64_t)sh.ticket;  // block uniform
+        const int64_t t = __builtin_amdgcn_readfirstlane((int32_t)sh.ticket);  // block uniform
         if (t >= n_x) break;
-        const int32_t *it = items5 + 5 * (lo + t);
-        int chip = it[0];
+        const int32_t *it = groups3 + 3 * (lo + t);
+        int chip = gmem(it)[0];
         if (chip < 0) {  // skipped tiles of chip ~chip: block uniform
             chip = ~chip;
             if (gmem(chips[chip].cat.dt)[chips[chip].e_first] == 0) continue;
@@ -988,7 +1021,7 @@ __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(kWavesPe
             for (int i = tid; i < hw / 4; i += T) smem4[i] = make_uint4(0, 0, 0, 0);
             chip_now = chip;
         }
-        vote_item<MODE, G, PK>(a, sh, smem4, it[1], it[2], it[3], it[4], tseq);
+        vote_rows<MODE, G, PK>(a, sh, smem4, a.items + 4 * (int64_t)gmem(it)[1], gmem(it)[2], tseq);
       }
     }
     __syncthreads();
@@ -1039,8 +1072,8 @@ __global__ void __launch_bounds__(T) k_refine(DenseArgs a) {
             const int32_t sx = shift_q8(vx, d), sy = shift_q8(vy, d);
             const int64_t xlo = ((int64_t)fbx0 << k) + sx, ylo = ((int64_t)fby0 << k) + sy;
             int cx0, cx1, cy0, cy1;
-            if (!cell_span(xlo, xlo + ((int64_t)cw << k), c.x0, c.x1, c.cell_log2, &cx0, &cx1) ||
-                !cell_span(ylo, ylo + ((int64_t)cw << k), c.y0, c.y1, c.cell_log2, &cy0, &cy1))
+            if (!cell_span(xlo, xlo + ((int64_t)cw << k), c.x0, c.x1, c.cell_log2_x, &cx0, &cx1) ||
+                !cell_span(ylo, ylo + ((int64_t)cw << k), c.y0, c.y1, c.cell_log2_y, &cy0, &cy1))
                 continue;
             uint64_t touched = 0;  // kRefineWeightEpochs: bins this lane's epoch reached
             for (int cy = cy0; cy <= cy1; ++cy) {
@@ -1145,8 +1178,8 @@ hipError_t launch_vote(const DenseArgs &a, int64_t grid, size_t lds, hipStream_t
 template <int MODE, int G, bool PK>
 hipError_t launch_mg(const DenseArgs &a, size_t lds, hipStream_t stream, hipEvent_t ev0,
                      hipEvent_t ev1) {
-    const int64_t grid = resident_grid<G, PK>(lds, a.n_items_kept);
-    return grid >= a.n_items_kept
+    const int64_t grid = resident_grid<G, PK>(lds, a.n_groups_kept);
+    return grid >= a.n_groups_kept
                ? launch_vote<MODE, G, PK, true>(a, grid, lds, stream, ev0, ev1)
                : launch_vote<MODE, G, PK, false>(a, grid, lds, stream, ev0, ev1);
 }
@@ -1164,8 +1197,8 @@ hipError_t launch_m(int groups, const DenseArgs &a, size_t lds, hipStream_t s, h
 struct BatchLaunch {
     const DenseArgs *chips;
     int32_t n_chips;
-    const int32_t *items5;
-    int64_t n_items, n_kept;
+    const int32_t *groups3;
+    int64_t n_groups, n_kept;
     int32_t hist_words_max;
     size_t lds;
     unsigned long long *queue;
@@ -1185,7 +1218,7 @@ hipError_t launch_batch_mg(const BatchLaunch &b, hipStream_t stream) {
     hipLaunchKernelGGL(k_zero_queue, dim3(1), dim3(64), 0, stream, b.queue);
     const int64_t grid = resident_grid<G, PK>(b.lds, b.n_kept);
     hipLaunchKernelGGL((k_vote_dense_batch<MODE, G, PK>), dim3((unsigned)grid), dim3(T), b.lds,
-                       stream, b.chips, b.n_chips, b.items5, b.n_items, b.n_kept,
+                       stream, b.chips, b.n_chips, b.groups3, b.n_groups, b.n_kept,
                        b.hist_words_max, b.queue, b.atomics);
     return hipGetLastError();
 }
@@ -1237,12 +1270,12 @@ size_t dense_lds_bytes(int groups, int hx, int hy, int stage_cap, int packed, in
 size_t dense_static_lds_bytes() { return sizeof(Shared); }
 
 hipError_t launch_vote_dense_batch(int mode, int groups, int packed, const DenseArgs *chips_dev,
-                                   int32_t n_chips, const int32_t *items5_dev, int64_t n_items,
+                                   int32_t n_chips, const int32_t *groups3_dev, int64_t n_groups,
                                    int64_t n_kept, int32_t hist_words_max, size_t lds,
                                    unsigned long long *queue, unsigned long long *atomics,
                                    hipStream_t stream) {
-    if (n_items <= 0) return hipSuccess;
-    const BatchLaunch b{chips_dev, n_chips, items5_dev, n_items, n_kept, hist_words_max, lds,
+    if (n_groups <= 0) return hipSuccess;
+    const BatchLaunch b{chips_dev, n_chips, groups3_dev, n_groups, n_kept, hist_words_max, lds,
                         queue, atomics};
     return packed ? launch_batch_p<true>(mode, groups, b, stream)
                   : launch_batch_p<false>(mode, groups, b, stream);

@@ -223,7 +223,7 @@ __global__ void __launch_bounds__(BT) k_band_vote(SortArgs a, const int32_t *__r
             const int32_t sx = shift_q8(vx, d), sy = shift_q8(vy, d);
             int cy0, cy1;
             if (!cell_span(((int64_t)by0 << lb) + sy, ((int64_t)(by0 + rows) << lb) + sy, c.y0,
-                           c.y1, c.cell_log2, &cy0, &cy1))
+                           c.y1, c.cell_log2_y, &cy0, &cy1))
                 continue;
             const int32_t j0 = c.off[((int64_t)e * c.ncy + cy0) * c.ncx];
             const int32_t j1 = c.off[((int64_t)e * c.ncy + cy1 + 1) * c.ncx];
