@@ -1039,6 +1039,11 @@ __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(kWavesPe
 // (sum of the weights) or kRefineWeightEpochs (per epoch the largest
 // weight, summed: each lane keeps its epoch's maxima in a private column of
 // LDS and adds them to the bins when the epoch is done).
+// A chain of loads bounds it (entry, velocity, offsets, detections): the next
+// entry and its velocity are loaded ahead, d_e stays in registers, two index
+// rows are read as one run, and only the bins of the cell are cleared (300 k
+// detections in 100 epochs: 365 -> 334 us; weighted, 180 k in 60: 199 us, as
+// before).  What is left is one cache line a lane for each offset read.
 constexpr int kRefineBins = 64;  // up to 8 x 8 bins per cell
 enum RefineMode : int { kRefineCount = 0, kRefineWeightDet = 1, kRefineWeightEpochs = 2 };
 
@@ -1056,18 +1061,28 @@ __global__ void __launch_bounds__(T) k_refine(DenseArgs a) {
     if (blockIdx.x == 0 && threadIdx.x == 0 && n_all > a.refine_cap)
         atomicOr(&a.res->status, SAS_DATA_REFINE_FULL);
     const int64_t n_q = min(n_all, a.refine_cap);
-    for (int64_t qi = (int64_t)blockIdx.x * NW + wave; qi < n_q; qi += (int64_t)gridDim.x * NW) {
-        const int4 q = a.refine[qi];
-        const int32_t v = q.x;
-        const int32_t vx = a.vel[2 * (int64_t)v], vy = a.vel[2 * (int64_t)v + 1];
+    const int64_t step = (int64_t)gridDim.x * NW;
+    int64_t qi = (int64_t)blockIdx.x * NW + wave;
+    if (qi >= n_q) return;
+    int32_t de[kMaxEpochs / 64];
+#pragma unroll
+    for (int i = 0; i < kMaxEpochs / 64; ++i)
+        de[i] = 64 * i + lane < E ? c.dt[64 * i + lane] : -1;
+    if (WM == kRefineWeightEpochs)  // every epoch leaves its column zero
+        for (int i = 0; i < kRefineBins; ++i) best[wave][i][lane] = 0;
+    int4 q = a.refine[qi];
+    int2 vq = load_g((const int2 *)a.vel + q.x);
+    for (; qi < n_q; qi += step) {
+        const int32_t v = q.x, vx = vq.x, vy = vq.y;
         const int32_t fbx0 = q.y * cw, fby0 = q.z * cw;  // first bin of the cell
-        for (int i = lane; i < kRefineBins * kSlotWords; i += 64) mk[i] = 0;
-        if (WM == kRefineWeightEpochs)
-            for (int i = 0; i < kRefineBins; ++i) best[wave][i][lane] = 0;
+        if (qi + step < n_q) q = a.refine[qi + step];
+        for (int i = lane; i < nb * kSlotWords; i += 64) mk[i] = 0;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_wave_barrier();
-        for (int e = lane; e < E; e += 64) {
-            const int32_t d = c.dt[e];
+#pragma unroll
+        for (int i = 0; i < kMaxEpochs / 64; ++i) {
+            const int e = 64 * i + lane;
+            const int32_t d = de[i];
             if (d < 0) continue;
             const int32_t sx = shift_q8(vx, d), sy = shift_q8(vy, d);
             const int64_t xlo = ((int64_t)fbx0 << k) + sx, ylo = ((int64_t)fby0 << k) + sy;
@@ -1076,18 +1091,23 @@ __global__ void __launch_bounds__(T) k_refine(DenseArgs a) {
                 !cell_span(ylo, ylo + ((int64_t)cw << k), c.y0, c.y1, c.cell_log2_y, &cy0, &cy1))
                 continue;
             uint64_t touched = 0;  // kRefineWeightEpochs: bins this lane's epoch reached
-            for (int cy = cy0; cy <= cy1; ++cy) {
+            for (int cy = cy0; cy <= cy1; cy += 2) {
+                // rows cy and cy + 1: n0 detections from j0, then n1 from j1
                 const int64_t base = ((int64_t)e * c.ncy + cy) * c.ncx;
-                const int32_t j1 = c.off[base + cx1 + 1];
+                const int64_t base1 = base + (cy < cy1 ? c.ncx : 0);
+                const int32_t j0 = c.off[base + cx0], j1 = c.off[base1 + cx0];
+                const int32_t n0 = c.off[base + cx1 + 1] - j0;
+                const int32_t n1 = cy < cy1 ? c.off[base1 + cx1 + 1] - j1 : 0;
                 // kCopyAhead detections loaded at a time, then binned
-                for (int32_t j0 = c.off[base + cx0]; j0 < j1; j0 += kCopyAhead) {
+                for (int32_t i0 = 0; i0 < n0 + n1; i0 += kCopyAhead) {
                     int2 pq[kCopyAhead];
 #pragma unroll
                     for (int u = 0; u < kCopyAhead; ++u)
-                        if (j0 + u < j1) pq[u] = c.sxy[j0 + u];
+                        if (i0 + u < n0 + n1)
+                            pq[u] = c.sxy[i0 + u < n0 ? j0 + i0 + u : j1 + (i0 + u - n0)];
 #pragma unroll
                     for (int u = 0; u < kCopyAhead; ++u) {
-                        if (j0 + u >= j1) break;
+                        if (i0 + u >= n0 + n1) break;
                         const int2 p = pq[u];
                         // weighted plans: the index holds 256 x + w
                         const int32_t px = WM == kRefineCount ? p.x : p.x >> 8;
@@ -1127,6 +1147,7 @@ __global__ void __launch_bounds__(T) k_refine(DenseArgs a) {
                 cnt = mk[lane * kSlotWords];
             }
         }
+        if (qi + step < n_q) vq = load_g((const int2 *)a.vel + q.x);
         const bool ok = lane < nb && cnt >= (uint32_t)a.n_min;
         const int64_t idx = wave_append(ok, (unsigned long long *)&a.res->n_cand);
         if (ok && idx < a.cand_cap)
