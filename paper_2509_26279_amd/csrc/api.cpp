@@ -1015,9 +1015,10 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
     if ((st = upload(p.get(), &p->d_seg_v, seg_v)) != SAS_OK) goto fail_free;
     if ((st = upload(p.get(), &p->d_seg_vel, seg_vel)) != SAS_OK) goto fail_free;
     if ((st = upload(p.get(), &p->d_seg_guard, seg_guard)) != SAS_OK) goto fail_free;
+    items.insert(items.end(), groups.begin(), groups.end());  // one upload for both
     if ((st = upload(p.get(), &p->d_items, items)) != SAS_OK) goto fail_free;
-    if ((st = upload(p.get(), &p->d_groups, groups)) != SAS_OK) goto fail_free;
-    p->h_groups = groups;
+    if (p->d_items) p->d_groups = p->d_items + 4 * p->n_items;
+    p->h_groups.swap(groups);
     for (int64_t j = 0; j < n_v; ++j)
         p->vmax = std::max(p->vmax, std::sqrt((double)V[2 * j] * V[2 * j] +
                                               (double)V[2 * j + 1] * V[2 * j + 1]));
