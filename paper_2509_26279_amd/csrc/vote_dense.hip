@@ -76,10 +76,16 @@ struct Shared {
     unsigned long long ticket;  // the item queue's answer to this workgroup
 };
 
-// Epochs per wave whose lane shifts stay in registers over a work item (two
-// registers each, or one packed).
-constexpr int kEpochRegs = 8;
-constexpr int kEpochRegsPacked = 8;  // packed: one register per epoch
+// Epochs per wave whose lane shifts stay in registers over a work item.  Each
+// is a copy of the vote loop in the code and moves by a tile at every tile; the
+// shift itself is two multiplications.  Unpacked votes (two registers each): 12,
+// 10, 8, 4, 2, 1 and 0 epochs took 90.3, 88.6, 88.4, 86.0, 85.1, 84.6 and 84.3
+// ms at 78 k detections in 93 epochs, 56.8, 56.5, 56.3, 55.2, 55.0, 54.6 and
+// 54.8 at 180 k in 60, and 1.88, 1.86, 1.87, 1.85, 1.83, 1.82 and 1.84 at 172 k
+// in 57 over few velocities.  Packed votes (one register): 8 and 2 took 9.58
+// and 9.60 at 160 k in 60.
+constexpr int kEpochRegs = 1;
+constexpr int kEpochRegsPacked = 8;
 
 // Waves per SIMD the vote kernels are compiled for: 4 (128 registers, two
 // workgroups of 8 waves per CU); 6 (80 registers, three workgroups) for one
