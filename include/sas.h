@@ -500,7 +500,8 @@ typedef struct {
  *                sas_peaks refuses) gives a wrong extraction.
  *   member_cap:  capacity of the contributor lists (sum over the cells of
  *                their contributors); see res->n_members when exceeded.
- *   scratch:     device, >= sas_extract_scratch_size(n, n_cand, member_cap).
+ *   scratch:     device, >= sas_extract_scratch_size(n, n_cand, member_cap)
+ *                bytes, of any alignment.
  *   clusters_dev: device [cluster_cap] clusters in extraction order, count =
  *                the count at extraction (saturated like the vote's).
  *   cluster_of_dev: device int32 [n] by catalog index: the cluster that took
@@ -548,8 +549,8 @@ sas_status sas_extract_scratch_size(int64_t n, int64_t n_cand, int64_t member_ca
  *               neighbours when those indices and their bins differ by at
  *               most 1 per component.  0 leaves features 9 and 10 at zero.
  *   scratch:    device memory of sas_features_scratch_size(n_cand) bytes or
- *               more (a table of neighbour keys); unused when
- *               spacing_q8 is 0 (may then be NULL).
+ *               more, of any alignment (a table of neighbour keys); unused
+ *               when spacing_q8 is 0 (may then be NULL).
  *   feat_dev:   device [n_cand][32] float, row-major.
  * Asynchronous, no allocation.  Errors: SAS_E_INVALID (n_cand >= 2^31,
  * negative spacing), SAS_E_WORKSPACE (workspace or scratch too small).

@@ -1506,8 +1506,19 @@ int feat_table_log2(int64_t n_cand) {
     return l;
 }
 
-size_t feat_scratch_bytes(int64_t n_cand) {
+size_t feat_table_bytes(int64_t n_cand) {
     return sizeof(uint64_t) << feat_table_log2(n_cand);
+}
+
+// Scratch may have any alignment: what is kept in it (64-bit atomics, 16-byte
+// records) begins at its first 256-byte boundary, and the sizes that callers
+// ask for hold the bytes up to it.
+constexpr size_t kScratchSlack = 255;
+
+// The 256-byte aligned part of a scratch, when it holds `need` bytes; else null.
+char *scratch_base(void *scratch, size_t bytes, size_t need) {
+    const size_t skip = (256 - ((uintptr_t)scratch & 255)) & 255;
+    return scratch && bytes >= skip && bytes - skip >= need ? (char *)scratch + skip : nullptr;
 }
 
 constexpr int64_t kMaxFeatureCands = (int64_t)1 << 31;
@@ -1517,7 +1528,7 @@ constexpr int64_t kMaxFeatureCands = (int64_t)1 << 31;
 extern "C" sas_status sas_features_scratch_size(int64_t n_cand, size_t *bytes) {
     if (!bytes || n_cand < 0 || n_cand >= kMaxFeatureCands)
         return fail(SAS_E_INVALID, "sas_features_scratch_size: bad argument");
-    *bytes = feat_scratch_bytes(n_cand);
+    *bytes = feat_table_bytes(n_cand) + kScratchSlack;
     return SAS_OK;
 }
 
@@ -1535,7 +1546,8 @@ extern "C" sas_status sas_features(const sas_plan *p, const void *workspace, siz
     const WsLayout L = ws_layout(p, n);
     if (!workspace || ws_bytes < L.total)
         return fail(SAS_E_WORKSPACE, "sas_features: workspace smaller than sas_vote_workspace_size()");
-    if (spacing_q8 > 0 && n_cand > 0 && (!scratch || scratch_bytes < feat_scratch_bytes(n_cand)))
+    char *table = scratch_base(scratch, scratch_bytes, feat_table_bytes(n_cand));
+    if (spacing_q8 > 0 && n_cand > 0 && !table)
         return fail(SAS_E_WORKSPACE, "sas_features: scratch smaller than sas_features_scratch_size()");
     if (n_cand == 0 || n == 0) return SAS_OK;
     char *w = (char *)workspace;
@@ -1551,7 +1563,7 @@ extern "C" sas_status sas_features(const sas_plan *p, const void *workspace, siz
     a.n_cand = n_cand;
     a.feat = feat_dev;
     a.spacing = spacing_q8;
-    a.table = (uint64_t *)scratch;
+    a.table = (uint64_t *)table;
     a.table_log2 = feat_table_log2(n_cand);
     hipError_t e = launch_features(a, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "sas_features: launch");
@@ -1599,7 +1611,7 @@ extern "C" sas_status sas_extract_scratch_size(int64_t n, int64_t n_cand, int64_
     if (!bytes || n < 0 || n_cand < 0 || n_cand >= kMaxFeatureCands || member_cap < 0 ||
         member_cap > kMaxMembers)
         return fail(SAS_E_INVALID, "sas_extract_scratch_size: bad argument");
-    *bytes = extract_layout(n, n_cand, member_cap).total;
+    *bytes = extract_layout(n, n_cand, member_cap).total + kScratchSlack;
     return SAS_OK;
 }
 
@@ -1625,9 +1637,9 @@ extern "C" sas_status sas_extract_clusters(const sas_plan *p, const void *worksp
     if (!workspace || ws_bytes < L.total)
         return fail(SAS_E_WORKSPACE, "sas_extract_clusters: workspace smaller than sas_vote_workspace_size()");
     const ExtractScratch S = extract_layout(n, n_cand, member_cap);
-    if (!scratch || scratch_bytes < S.total)
+    char *w = (char *)workspace, *s = scratch_base(scratch, scratch_bytes, S.total);
+    if (!s)
         return fail(SAS_E_WORKSPACE, "sas_extract_clusters: scratch smaller than sas_extract_scratch_size()");
-    char *w = (char *)workspace, *s = (char *)scratch;
     const PrepBuffers pb = prep_buffers(L, w);
     ExtractArgs a{};
     a.cat = dense_args(p, L, w, pb, nullptr, 0, nullptr).cat;
