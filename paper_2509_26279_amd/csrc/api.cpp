@@ -133,8 +133,9 @@ struct sas_plan {
     std::vector<SortBlock> sort_blocks;
     int64_t sort_max_nv = 0;
     int32_t sort_vblock = 0;
-    int64_t n_bands = 0;        // band items (0: a velocity's bins are too many for them)
-    int32_t *d_bands = nullptr;
+    bool banded = false;        // a velocity's bins are few enough for bands
+    int64_t n_band_items = 0;   // bands listed one by one (0: many velocities, not listed)
+    int32_t *d_band_items = nullptr;
     int32_t *d_sort_vel = nullptr, *d_sort_vidx = nullptr;
     hipEvent_t probe[2] = {nullptr, nullptr};
     unsigned long long *counter = nullptr;  // device: LDS atomic vote instructions (probe)
@@ -927,11 +928,11 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
 
     // Sort path: blocks of consecutive segments, up to sort_vblock velocities,
     // each with the bin extent every (velocity, detection) of it can reach.
-    std::vector<int32_t> sort_vel, sort_vidx, bands;
-    // Band items replace the sort where every velocity's bin rows fit LDS and its
-    // bins at most kMaxBands items (each reads about its share of the catalog, but
+    std::vector<int32_t> sort_vel, sort_vidx;
+    // Bands replace the sort where every velocity's bin rows fit LDS and its
+    // bins at most kMaxBands bands (each reads about its share of the catalog, but
     // walks every epoch); an explicit sort_vblock asks for the sort.
-    constexpr int64_t kMaxBands = 32;
+    std::vector<int32_t> band_items;
     bool banded = tu.sort_vblock <= 0;
     if (p->path == SAS_PATH_SORT) {
         int64_t vb = tu.sort_vblock;
@@ -940,13 +941,6 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
                                          ((int64_t)1 << 25) / tu.n_det_hint))
                                    : 64;
         const int lb = log2b;
-        auto bin_range = [&](int32_t v, int32_t lo, int32_t hi, int64_t *b0, int64_t *b1) {
-            // x - S(v, d) for x in [lo, hi), d in [0, D]: S is monotone in d
-            const int64_t sD = (int64_t)(((__int128)v * D + 65535) >> 16);
-            const int64_t smin = std::min<int64_t>(0, sD), smax = std::max<int64_t>(0, sD);
-            *b0 = floor_div((__int128)lo - smax, (__int128)1 << lb);
-            *b1 = floor_div((__int128)hi - 1 - smin, (__int128)1 << lb);
-        };
         SortBlock cur{};
         int64_t bx0 = 0, bx1 = 0, by0 = 0, by1 = 0;
         auto flush = [&]() -> bool {
@@ -972,26 +966,23 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
                 const int32_t vi = seg_v[sg * NV + l];
                 if (vi < 0) continue;
                 const int32_t u = seg_vel[2 * (sg * NV + l)], w = seg_vel[2 * (sg * NV + l) + 1];
-                int64_t a0, a1, c0, c1;
-                bin_range(u, ex[0], ex[1], &a0, &a1);
-                bin_range(w, ex[2], ex[3], &c0, &c1);
+                const BandBins r = reached_bins(u, w, D, ex, lb);
                 if (cur.nv == 0) {
-                    bx0 = a0; bx1 = a1; by0 = c0; by1 = c1;
+                    bx0 = r.bx0; bx1 = r.bx1; by0 = r.by0; by1 = r.by1;
                 } else {
-                    bx0 = std::min(bx0, a0); bx1 = std::max(bx1, a1);
-                    by0 = std::min(by0, c0); by1 = std::max(by1, c1);
+                    bx0 = std::min(bx0, r.bx0); bx1 = std::max(bx1, r.bx1);
+                    by0 = std::min(by0, r.by0); by1 = std::max(by1, r.by1);
                 }
                 if (bx0 <= -((int64_t)1 << 31) || bx1 >= ((int64_t)1 << 31) ||
                     by0 <= -((int64_t)1 << 31) || by1 >= ((int64_t)1 << 31))
                     return fail(SAS_E_UNSUPPORTED, "sas_plan_create: sort-path bins exceed 32 bits");
-                const int64_t nbx = a1 - a0 + 1, nby = c1 - c0 + 1;
-                const int64_t rows = nbx <= kBandBins ? std::min<int64_t>(kBandBins / nbx, nby) : 0;
-                banded = banded && rows > 0 && (nby + rows - 1) / rows <= kMaxBands &&
-                         (int64_t)bands.size() / 5 < ((int64_t)1 << 30);
-                for (int64_t r = 0; banded && r < nby; r += rows)
-                    bands.insert(bands.end(), {(int32_t)sort_vidx.size(), (int32_t)a0, (int32_t)nbx,
-                                               (int32_t)(c0 + r),
-                                               (int32_t)std::min<int64_t>(rows, nby - r)});
+                banded = banded && r.rows() > 0 && r.bands() <= kMaxBands;
+                for (int64_t by = r.by0; banded && n_v <= kBandItemVelocities && by <= r.by1;
+                     by += r.rows())
+                    band_items.insert(band_items.end(),
+                                      {(int32_t)sort_vidx.size(), (int32_t)r.bx0,
+                                       (int32_t)(r.bx1 - r.bx0 + 1), (int32_t)by,
+                                       (int32_t)std::min<int64_t>(r.rows(), r.by1 - by + 1)});
                 sort_vel.push_back(u);
                 sort_vel.push_back(w);
                 sort_vidx.push_back(vi);
@@ -1004,8 +995,9 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
             return fail(SAS_E_UNSUPPORTED, "sas_plan_create: sort keys exceed 64 bits; lower "
                                            "sort_vblock");
         p->sort_vblock = (int32_t)vb;
-        if (!banded) bands.clear();
-        p->n_bands = (int64_t)bands.size() / 5;
+        if (!banded) band_items.clear();
+        p->banded = banded;
+        p->n_band_items = (int64_t)band_items.size() / 5;
     }
 
     std::vector<int32_t> vel(V, V + 2 * n_v);
@@ -1026,7 +1018,7 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
     if ((st = upload(p.get(), &p->d_t, p->t)) != SAS_OK) goto fail_free;
     if ((st = upload(p.get(), &p->d_sort_vel, sort_vel)) != SAS_OK) goto fail_free;
     if ((st = upload(p.get(), &p->d_sort_vidx, sort_vidx)) != SAS_OK) goto fail_free;
-    if ((st = upload(p.get(), &p->d_bands, bands)) != SAS_OK) goto fail_free;
+    if ((st = upload(p.get(), &p->d_band_items, band_items)) != SAS_OK) goto fail_free;
     *plan_out = p.release();
     return SAS_OK;
 fail_free:
@@ -1150,8 +1142,14 @@ sas_status vote_impl(const sas_plan *p, const int32_t *x_q8, const int32_t *y_q8
         // velocities and 1.8e5 detections, thresholds 1 / 8 / 23: 6.8 / 3.0 / 0.16 ms
         // against 22.6 / 12.7 / 5.3 ms at 60 epochs, 12.4 / 4.5 / 0.34 against
         // 26.2 / 18.8 / 6.3 ms at 256.
-        if (p->n_bands > 0) {
-            e = launch_band_vote(sa, p->d_bands, p->n_bands, s);
+        if (p->banded) {
+            BandArgs b{};
+            b.n_v = p->n_v;
+            b.items = p->n_band_items ? p->d_band_items : nullptr;
+            b.n_items = p->n_band_items;
+            std::memcpy(b.extent, p->ext, sizeof(b.extent));
+            b.span = p->span;
+            e = launch_band_vote(sa, b, s);
             if (e != hipSuccess) return hip_fail(e, "sas_vote: band launch");
         } else {
             for (const SortBlock &b : p->sort_blocks) {

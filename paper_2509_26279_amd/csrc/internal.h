@@ -146,12 +146,43 @@ struct SortArgs {
     sas_vote_result *res;
 };
 
-// Band items of the sort path: [n][5] velocity (block order), first bin and
-// bins in x, first bin row and rows.
-constexpr int kBandBins = 16384;   // bins of an item (64 KB of LDS)
+// Bands of the sort path: runs of whole bin rows of one velocity.
+constexpr int kBandBins = 16384;   // bins of a band (64 KB of LDS)
 constexpr int kBandMasks = 2048;   // words of epoch masks
-hipError_t launch_band_vote(const SortArgs &a, const int32_t *items, int64_t n_items,
-                            hipStream_t stream);
+constexpr int kMaxBands = 32;      // bands of a velocity
+constexpr int64_t kBandItemVelocities = 16384;  // most velocities with an item for each band
+
+// Bins of a velocity that a detection of the footprint reaches at some epoch.
+struct BandBins {
+    int64_t bx0, bx1, by0, by1;  // first and last
+    // Rows of a band (0: a row of bins exceeds kBandBins) and bands of whole rows.
+    __host__ __device__ int32_t rows() const {
+        const int64_t nbx = bx1 - bx0 + 1;
+        return nbx <= kBandBins ? (int32_t)((uint32_t)kBandBins / (uint32_t)nbx) : 0;
+    }
+    __host__ __device__ int64_t bands() const { return (by1 - by0 + rows()) / rows(); }
+};
+
+// x - S(v, d) for x in [x0, x1) and d in [0, span], S = ceil(v d / 65536), which
+// is monotone in d; the same in y.  Bins of 2^log2b; |v| span < 2^46.
+__host__ __device__ inline BandBins reached_bins(int32_t vx, int32_t vy, int64_t span,
+                                                 const int32_t *extent, int log2b) {
+    const int64_t sx = (vx * span + 65535) >> 16, sy = (vy * span + 65535) >> 16;
+    return BandBins{(extent[0] - (sx > 0 ? sx : 0)) >> log2b,
+                    (extent[1] - 1 - (sx < 0 ? sx : 0)) >> log2b,
+                    (extent[2] - (sy > 0 ? sy : 0)) >> log2b,
+                    (extent[3] - 1 - (sy < 0 ? sy : 0)) >> log2b};
+}
+
+struct BandArgs {
+    int64_t n_v;             // velocities (block order)
+    const int32_t *items;    // [n_items][5] velocity, first bin and bins in x, first bin row and
+    int64_t n_items;         // rows: a workgroup's band; null: every band of a velocity
+    int32_t extent[4];       // footprint
+    int64_t span;            // largest t - t0
+    int64_t first;           // first item or velocity of a launch
+};
+hipError_t launch_band_vote(const SortArgs &a, const BandArgs &b, hipStream_t stream);
 
 constexpr int kSortKeysPerTile = 4096;  // radix tile: 256 threads x 16 keys
 

@@ -13,13 +13,15 @@
 // and one read and one write for the scatter, then one read to count.
 //
 // Where a velocity's bins fit a few histograms in LDS, the sort is left out:
-// k_band_vote counts one (velocity, band of bin rows) per workgroup, reading
+// k_band_vote counts bands of whole bin rows of a velocity, reading
 // for each epoch the contiguous stretch of the window index whose rows the
 // band can reach, and counts distinct epochs in a second reading for the bins
 // whose detections reach N_min.  A vote then costs about 9 bytes of L2 reads
 // and one LDS atomic in place of 80 to 104 bytes of HBM traffic: a block of
 // 512 velocities of the fast grid took 5.15 ms by the sort, now 0.21 ms with
 // the preparation (0.13 ms k_band_vote, 7e11 votes/s).
+#include <algorithm>
+
 #include "internal.h"
 
 namespace sas {
@@ -194,103 +196,149 @@ __device__ inline bool cell_span(int64_t lo, int64_t hi, int32_t f0, int32_t f1,
 constexpr int BT = 512;  // threads of a band workgroup; two are resident on a CU
 constexpr uint32_t kHot = 0x80000000u;
 
-// One band item (v, bx0, nbx, by0, rows): counts of the bins [bx0, bx0 + nbx) x
-// [by0, by0 + rows) of velocity v; nbx * rows <= kBandBins.
-__global__ void __launch_bounds__(BT) k_band_vote(SortArgs a, const int32_t *__restrict__ items) {
+struct BandOut {
+    const int32_t *v_idx;
+    sas_candidate *cand;
+    int64_t cand_cap;
+    sas_vote_result *res;
+    uint32_t sat;
+};
+
+// Counts of the bins [bx0, bx0 + nbx) x [by0, by0 + rows) of one velocity, nbx *
+// rows <= kBandBins.  A workgroup takes one band of a table of them while the
+// velocities are few, so that they share the chip evenly, and (EVERY) the bands
+// of a velocity one after the other where there are many: dispatching a
+// workgroup costs the chip some 15 ns, and the fast grid of 1.2e6 velocities has
+// 1.6e7 bands, too many for one launch.  20000 of its velocities: 5.67 ms with
+// the loop, 5.84 a band each; 512 fast ones: 208 us a band each, 223 us with the
+// loop over eight shares of a velocity's bands, 221 us with bands worked out here
+// instead of read.
+template <bool EVERY>
+__global__ void __launch_bounds__(BT) k_band_vote(SortArgs a, BandArgs b) {
     __shared__ uint32_t hist[kBandBins];
     __shared__ uint32_t mask[kBandMasks];
     __shared__ int32_t n_hot;
+    // what only candidates need: over the loop in LDS, not in scalar registers
+    // that it has none left of
+    __shared__ BandOut out_s;
+    const BandOut out_a{a.v_idx, a.cand, a.cand_cap, a.res, (uint32_t)a.count_sat};
+    if (EVERY && threadIdx.x == 0) out_s = out_a;
+    const BandOut &out = EVERY ? out_s : out_a;
     const int tid = threadIdx.x;
     const PreparedCatalog &c = a.cat;
     const int E = c.n_epochs, lb = a.log2b;
-    const int32_t *it = items + 5 * (int64_t)blockIdx.x;
-    const int32_t v = it[0], bx0 = it[1], nbx = it[2], by0 = it[3], rows = it[4];
-    const int32_t vx = a.vel[2 * (int64_t)v], vy = a.vel[2 * (int64_t)v + 1];
-    const int n_bins = nbx * rows;
-    for (int i = tid; i < n_bins; i += BT) hist[i] = 0;
-    if (tid == 0) n_hot = 0;
-    __syncthreads();
-    // f(word of the histogram, epoch) for every detection that projects into the
-    // band: a wave an epoch, or the workgroup when there are few epochs
-    const auto each = [&](const auto &f) __attribute__((always_inline)) {
-        const bool by_wave = E >= 2 * (BT / 64);
-        const int step = by_wave ? 64 : BT;
-        const int first = by_wave ? (tid & 63) : tid;
-        for (int e = by_wave ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0; e < E;
-             e += by_wave ? BT / 64 : 1) {
-            const int32_t d = c.dt[e];
-            if (d < 0) continue;
-            const int32_t sx = shift_q8(vx, d), sy = shift_q8(vy, d);
-            int cy0, cy1;
-            if (!cell_span(((int64_t)by0 << lb) + sy, ((int64_t)(by0 + rows) << lb) + sy, c.y0,
-                           c.y1, c.cell_log2_y, &cy0, &cy1))
-                continue;
-            const int32_t j0 = c.off[((int64_t)e * c.ncy + cy0) * c.ncx];
-            const int32_t j1 = c.off[((int64_t)e * c.ncy + cy1 + 1) * c.ncx];
-            for (int32_t j = j0 + first; j < j1; j += 4 * step) {
-                int2 p[4];
+    const int64_t u = b.first + blockIdx.x;
+    int64_t v = u, by = 0, by_end = 0;
+    int32_t bx0, nbx, by0, rows, high = 0;
+    if constexpr (EVERY) {
+        const BandBins r = reached_bins(a.vel[2 * u], a.vel[2 * u + 1], b.span, b.extent, lb);
+        bx0 = (int32_t)r.bx0;
+        nbx = (int32_t)(r.bx1 - r.bx0 + 1);
+        high = __builtin_amdgcn_readfirstlane(r.rows());  // a division ends in a vector register
+        by = r.by0;
+        by_end = r.by1 + 1;
+    } else {
+        const int32_t *it = b.items + 5 * u;
+        v = it[0];
+        bx0 = it[1];
+        nbx = it[2];
+        by0 = it[3];
+        rows = it[4];
+    }
+    const int32_t vx = a.vel[2 * v], vy = a.vel[2 * v + 1];
+    do {
+        if constexpr (EVERY) {
+            by0 = (int32_t)by;
+            rows = (int32_t)min((int64_t)high, by_end - by);
+        }
+        const int n_bins = nbx * rows;
+        for (int i = tid; i < n_bins; i += BT) hist[i] = 0;
+        if (tid == 0) n_hot = 0;
+        __syncthreads();
+        // f(word of the histogram, epoch) for every detection that projects into the
+        // band: a wave an epoch, or the workgroup when there are few epochs
+        const auto each = [&](const auto &f) __attribute__((always_inline)) {
+            const bool by_wave = E >= 2 * (BT / 64);
+            const int step = by_wave ? 64 : BT;
+            const int first = by_wave ? (tid & 63) : tid;
+            for (int e = by_wave ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0; e < E;
+                 e += by_wave ? BT / 64 : 1) {
+                const int32_t d = c.dt[e];
+                if (d < 0) continue;
+                const int32_t sx = shift_q8(vx, d), sy = shift_q8(vy, d);
+                int cy0, cy1;
+                if (!cell_span(((int64_t)by0 << lb) + sy, ((int64_t)(by0 + rows) << lb) + sy, c.y0,
+                               c.y1, c.cell_log2_y, &cy0, &cy1))
+                    continue;
+                const int32_t j0 = c.off[((int64_t)e * c.ncy + cy0) * c.ncx];
+                const int32_t j1 = c.off[((int64_t)e * c.ncy + cy1 + 1) * c.ncx];
+                for (int32_t j = j0 + first; j < j1; j += 4 * step) {
+                    int2 p[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (j + u * step < j1) p[u] = c.sxy[j + u * step];
+                    for (int u = 0; u < 4; ++u)
+                        if (j + u * step < j1) p[u] = c.sxy[j + u * step];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (j + u * step >= j1) break;
-                    const int32_t ix = ((p[u].x - sx) >> lb) - bx0, iy = ((p[u].y - sy) >> lb) - by0;
-                    if ((uint32_t)iy < (uint32_t)rows && (uint32_t)ix < (uint32_t)nbx)
-                        f(iy * nbx + ix, e);
+                    for (int u = 0; u < 4; ++u) {
+                        if (j + u * step >= j1) break;
+                        const int32_t ix = ((p[u].x - sx) >> lb) - bx0, iy = ((p[u].y - sy) >> lb) - by0;
+                        if ((uint32_t)iy < (uint32_t)rows && (uint32_t)ix < (uint32_t)nbx)
+                            f(iy * nbx + ix, e);
+                    }
                 }
             }
-        }
-    };
-    each([&](int i, int) __attribute__((always_inline)) { atomicAdd(&hist[i], 1u); });
-    __syncthreads();
-    const uint32_t nmin = (uint32_t)a.n_min, sat = (uint32_t)a.count_sat;
-    const auto emit = [&](bool ok, int i, uint32_t cnt) __attribute__((always_inline)) {
-        const int64_t idx = wave_append(ok, (unsigned long long *)&a.res->n_cand);
-        if (ok && idx < a.cand_cap) {
-            uint4 rec;
-            rec.x = (uint32_t)a.v_idx[v];
-            rec.y = (uint32_t)(bx0 + i % nbx);
-            rec.z = (uint32_t)(by0 + i / nbx);
-            rec.w = (cnt > sat ? sat : cnt) | ((cnt > sat ? 1u : 0u) << 16);
-            *(uint4 *)(a.cand + idx) = rec;
-        }
-    };
-    if (!a.mode_epochs) {
-        for (int i0 = 0; i0 < n_bins; i0 += BT) {
-            const int i = i0 + tid;
-            const uint32_t n = i < n_bins ? hist[i] : 0;
-            if (__any(n >= nmin)) emit(n >= nmin, i, n);
-        }
-        return;
-    }
-    // distinct epochs of the bins with nmin detections: each gets a number, and
-    // the catalog is read again for as many of them as the masks hold
-    const int W = (E + 31) / 32, held = kBandMasks / W;
-    for (int i = tid; i < n_bins; i += BT)
-        hist[i] = hist[i] >= nmin ? kHot | (uint32_t)atomicAdd(&n_hot, 1) : 0;
-    __syncthreads();
-    const int hot = n_hot;
-    for (int s0 = 0; s0 < hot; s0 += held) {  // block uniform
-        for (int i = tid; i < kBandMasks; i += BT) mask[i] = 0;
+        };
+        each([&](int i, int) __attribute__((always_inline)) { atomicAdd(&hist[i], 1u); });
         __syncthreads();
-        each([&](int i, int e) __attribute__((always_inline)) {
-            const uint32_t s = (hist[i] & ~kHot) - (uint32_t)s0;
-            if (hist[i] & kHot && s < (uint32_t)held)
-                atomicOr(&mask[s * W + (e >> 5)], 1u << (e & 31));
-        });
-        __syncthreads();
-        for (int i0 = 0; i0 < n_bins; i0 += BT) {
-            const int i = i0 + tid;
-            const uint32_t h = i < n_bins ? hist[i] : 0;
-            const uint32_t s = (h & ~kHot) - (uint32_t)s0;
-            uint32_t n = 0;
-            if (h & kHot && s < (uint32_t)held)
-                for (int w = 0; w < W; ++w) n += __popc(mask[s * W + w]);
-            if (__any(n >= nmin)) emit(n >= nmin, i, n);
+        const uint32_t nmin = (uint32_t)a.n_min;
+        const auto emit = [&](bool ok, int i, uint32_t cnt) __attribute__((always_inline)) {
+            const int64_t idx = wave_append(ok, (unsigned long long *)&out.res->n_cand);
+            if (ok && idx < out.cand_cap) {
+                const uint32_t sat = out.sat;
+                uint4 rec;
+                rec.x = (uint32_t)out.v_idx[v];
+                rec.y = (uint32_t)(bx0 + i % nbx);
+                rec.z = (uint32_t)(by0 + i / nbx);
+                rec.w = (cnt > sat ? sat : cnt) | ((cnt > sat ? 1u : 0u) << 16);
+                *(uint4 *)(out.cand + idx) = rec;
+            }
+        };
+        if (!a.mode_epochs) {
+            for (int i0 = 0; i0 < n_bins; i0 += BT) {
+                const int i = i0 + tid;
+                const uint32_t n = i < n_bins ? hist[i] : 0;
+                if (__any(n >= nmin)) emit(n >= nmin, i, n);
+            }
+            if (EVERY) __syncthreads();  // the counts are read before they are cleared
+            continue;
         }
+        // distinct epochs of the bins with nmin detections: each gets a number, and
+        // the catalog is read again for as many of them as the masks hold
+        const int W = (E + 31) / 32, held = kBandMasks / W;
+        for (int i = tid; i < n_bins; i += BT)
+            hist[i] = hist[i] >= nmin ? kHot | (uint32_t)atomicAdd(&n_hot, 1) : 0;
         __syncthreads();
-    }
+        const int hot = n_hot;
+        for (int s0 = 0; s0 < hot; s0 += held) {  // block uniform
+            for (int i = tid; i < kBandMasks; i += BT) mask[i] = 0;
+            __syncthreads();
+            each([&](int i, int e) __attribute__((always_inline)) {
+                const uint32_t s = (hist[i] & ~kHot) - (uint32_t)s0;
+                if (hist[i] & kHot && s < (uint32_t)held)
+                    atomicOr(&mask[s * W + (e >> 5)], 1u << (e & 31));
+            });
+            __syncthreads();
+            for (int i0 = 0; i0 < n_bins; i0 += BT) {
+                const int i = i0 + tid;
+                const uint32_t h = i < n_bins ? hist[i] : 0;
+                const uint32_t s = (h & ~kHot) - (uint32_t)s0;
+                uint32_t n = 0;
+                if (h & kHot && s < (uint32_t)held)
+                    for (int w = 0; w < W; ++w) n += __popc(mask[s * W + w]);
+                if (__any(n >= nmin)) emit(n >= nmin, i, n);
+            }
+            __syncthreads();
+        }
+    } while (EVERY && (by += high) < by_end);
 }
 
 inline unsigned grid_for(int64_t n, int64_t cap) {
@@ -320,10 +368,18 @@ hipError_t launch_radix_sort_u64(uint64_t *keys, uint64_t *alt, int64_t m, int l
     return hipGetLastError();
 }
 
-hipError_t launch_band_vote(const SortArgs &a, const int32_t *items, int64_t n_items,
-                            hipStream_t stream) {
-    if (n_items <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_band_vote, dim3((unsigned)n_items), dim3(BT), 0, stream, a, items);
+hipError_t launch_band_vote(const SortArgs &a, const BandArgs &b, hipStream_t stream) {
+    constexpr int64_t kGroups = (int64_t)1 << 22;
+    static_assert(kGroups * BT < (int64_t)1 << 32, "a launch holds less than 2^32 threads");
+    const int64_t n = b.items ? b.n_items : b.n_v;
+    BandArgs l = b;
+    for (; l.first < n; l.first += kGroups) {
+        const dim3 grid((unsigned)std::min(n - l.first, kGroups));
+        if (b.items)
+            hipLaunchKernelGGL(k_band_vote<false>, grid, dim3(BT), 0, stream, a, l);
+        else
+            hipLaunchKernelGGL(k_band_vote<true>, grid, dim3(BT), 0, stream, a, l);
+    }
     return hipGetLastError();
 }
 
