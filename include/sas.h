@@ -153,8 +153,9 @@ typedef struct {
 
 #define SAS_PATH_AUTO 0
 #define SAS_PATH_DENSE 1   /* LDS-resident count tiles (velocity block x spatial tile) */
-#define SAS_PATH_SORT 2    /* sort-by-bin-key in HBM; whole-band LDS counts where a velocity's
-                              bins are few enough and sort_vblock is not given */
+#define SAS_PATH_SORT 2    /* sort-by-bin-key in HBM, or LDS counts of bands of bin rows where a
+                              velocity's bins are few enough for them and they are expected
+                              to be faster for the catalog's size (tuning.sort_vblock) */
 
 /* Launch shape of the dense path; zeros select the built-in defaults. */
 typedef struct {
@@ -168,7 +169,10 @@ typedef struct {
                                    processed in chunks) */
     int32_t cell_log2;          /* log2 of the window-index cell width in Q8 px (the cells grow
                                    higher than wide when a window has too many rows of them) */
-    int32_t sort_vblock;        /* velocities per sort-path block (given: always the sort) */
+    int32_t sort_vblock;        /* sort path: velocities per block of the sort; > 0: always the
+                                   sort; 0: chosen from n_det_hint, and bands in place of the
+                                   sort where they are expected to be faster; < 0: bands for
+                                   every catalog size, where the bins allow them */
     int32_t n_det_hint;         /* expected detections per catalog: chooses the cell size */
     int32_t coarse_log2;        /* histogram cells of 2^m x 2^m bins, m in [0, 3]; -1: single
                                    bins; 0: chosen from n_det_hint */

@@ -45,6 +45,17 @@ int ilog2_exact(int64_t v) {  // -1 unless v is a power of two
     return k;
 }
 
+// P(Poisson(lam) >= k)
+double poisson_tail(double lam, int32_t k) {
+    double term = std::exp(-lam), cdf = 0.0;
+    if (term == 0.0) return 1.0;
+    for (int i = 0; i < k && !(i > lam && term < 1e-18); ++i) {  // what follows adds nothing
+        cdf += term;
+        term *= lam / (i + 1);
+    }
+    return std::max(0.0, 1.0 - cdf);
+}
+
 size_t align_up(size_t v) { return (v + 255) & ~size_t(255); }
 
 using Pt = std::pair<__int128, __int128>;
@@ -133,7 +144,7 @@ struct sas_plan {
     std::vector<SortBlock> sort_blocks;
     int64_t sort_max_nv = 0;
     int32_t sort_vblock = 0;
-    bool banded = false;        // a velocity's bins are few enough for bands
+    uint32_t band_sizes = 0;    // bit k: catalogs of (2^(k-1), 2^k] detections take bands
     int64_t n_band_items = 0;   // bands listed one by one (0: many velocities, not listed)
     int32_t *d_band_items = nullptr;
     int32_t *d_sort_vel = nullptr, *d_sort_vidx = nullptr;
@@ -166,6 +177,46 @@ bool is_weighted(int32_t mode) {
 
 bool refines(int dense_mode) { return dense_mode == kCountRef || dense_mode == kWeightRef; }
 
+// Whether bands are expected to take less time than the sort: `share` detections
+// and `hot` bins with N_min detections a band, of n_bands in all.  In ns, from
+// 852 timings (16 to 20000 velocities of 1 to 26 bands, 10, 60 and 256 epochs,
+// 100 to 180000 detections, thresholds from 1): a band costs its dispatch and
+// clearing, and for every reading of the catalog a walk over the epochs and its
+// share of the detections; at least 512 run at once.  In EPOCHS mode there is a
+// second reading where a bin is hot, and one for every mask-full of them (64 at
+// 256 epochs and a threshold of 1).  A block of the sort costs its 20 launches,
+// a key its passes, and an addition to the candidate counter for every wave that
+// has one.  20000 velocities of 26 bands in 60 epochs, 1000 and 16000 detections:
+// bands 9.5 and 11.7 ms, the sort 3.4 and 16.2.  The way chosen took 1 % more than
+// the faster one in the mean; bands, where chosen, at most 1.29 times the sort.
+bool bands_faster(double share, double hot, double n_bands, int32_t n_epochs, int32_t mode,
+                  int32_t n_min, double n_blocks) {
+    hot = std::min(hot, share / n_min);
+    const double held = kBandMasks / ((n_epochs + 31) / 32);
+    const double again = mode != SAS_MODE_EPOCHS ? 0.0
+                         : hot < held            ? 1.0 - std::exp(-hot)
+                                                 : std::ceil(hot / held);
+    const double band = 15.0 + 20.0 * again +
+                        (1.0 + again) * (0.25 * std::min((double)n_epochs, share) + 0.001 * share);
+    const double key = 0.05 + 0.15 * (1.0 - std::exp(-64.0 * hot / share));
+    return band * std::max(n_bands, 512.0) <= 1e5 * n_blocks + key * share * n_bands;
+}
+
+// Bit of sas_plan::band_sizes of a catalog of n detections.
+int size_bit(int64_t n) {
+    int k = 0;
+    while (((int64_t)1 << k) < n) ++k;
+    return k;
+}
+
+// Largest catalog of at most n detections that this sort-path plan sorts.
+int64_t sorted_at_most(const sas_plan *p, int64_t n) {
+    int k = size_bit(n);
+    if (!(p->band_sizes >> k & 1u)) return n;
+    while (k > 0 && (p->band_sizes >> k & 1u)) --k;
+    return p->band_sizes >> k & 1u ? 0 : (int64_t)1 << k;
+}
+
 struct WsLayout {
     size_t count, offT, blocksum, cellid, rank, sxy, sidx, present, dt, refine_count, item_queue,
         refine;
@@ -193,7 +244,9 @@ WsLayout ws_layout(const sas_plan *p, int64_t n) {
     L.refine = o;
     o = align_up(o + sizeof(int4) * (p->path == SAS_PATH_DENSE && refines(p->dense_mode)
                                          ? p->refine_cap : 1));
-    const int64_t keys = p->path == SAS_PATH_SORT ? p->sort_max_nv * std::max<int64_t>(n, 1) : 1;
+    // keys of any catalog up to this size, as a workspace may serve smaller ones too
+    const int64_t keys = p->path == SAS_PATH_SORT
+                             ? std::max<int64_t>(p->sort_max_nv * sorted_at_most(p, n), 1) : 1;
     const int64_t tiles = (keys + kSortKeysPerTile - 1) / kSortKeysPerTile;
     const int64_t hist = 256 * tiles;
     L.keys = o; o = align_up(o + sizeof(uint64_t) * keys);
@@ -376,13 +429,7 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
         const double lam1 = (double)tu.n_det_hint * (double)d->binw_q8 * d->binw_q8 / area;
         for (int mm = 3; mm >= 1; --mm) {
             const double lam = lam1 * (double)(1 << (2 * mm));
-            // P(Poisson(lam) >= n_eq)
-            double term = std::exp(-lam), cdf = 0.0;
-            for (int k = 0; k < n_eq; ++k) {
-                cdf += term;
-                term *= lam / (k + 1);
-            }
-            const double tail = std::max(0.0, 1.0 - cdf);
+            const double tail = poisson_tail(lam, n_eq);
             const double cells_per_v = area / ((double)d->binw_q8 * d->binw_q8 * (1 << (2 * mm)));
             const double flags = tail * cells_per_v * (double)n_v;
             if (lam < 0.5 * n_eq && flags < 2.0e5) {
@@ -931,9 +978,10 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
     std::vector<int32_t> sort_vel, sort_vidx;
     // Bands replace the sort where every velocity's bin rows fit LDS and its
     // bins at most kMaxBands bands (each reads about its share of the catalog, but
-    // walks every epoch); an explicit sort_vblock asks for the sort.
+    // walks every epoch), for the catalogs that they are faster for.
     std::vector<int32_t> band_items;
     bool banded = tu.sort_vblock <= 0;
+    double n_bands = 0, n_bins = 0;  // of all velocities
     if (p->path == SAS_PATH_SORT) {
         int64_t vb = tu.sort_vblock;
         if (vb <= 0)
@@ -977,6 +1025,10 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
                     by0 <= -((int64_t)1 << 31) || by1 >= ((int64_t)1 << 31))
                     return fail(SAS_E_UNSUPPORTED, "sas_plan_create: sort-path bins exceed 32 bits");
                 banded = banded && r.rows() > 0 && r.bands() <= kMaxBands;
+                if (banded) {
+                    n_bands += (double)r.bands();
+                    n_bins += (double)(r.bx1 - r.bx0 + 1) * (double)(r.by1 - r.by0 + 1);
+                }
                 for (int64_t by = r.by0; banded && n_v <= kBandItemVelocities && by <= r.by1;
                      by += r.rows())
                     band_items.insert(band_items.end(),
@@ -996,7 +1048,15 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
                                            "sort_vblock");
         p->sort_vblock = (int32_t)vb;
         if (!banded) band_items.clear();
-        p->banded = banded;
+        const double bin_area = (double)d->binw_q8 * (double)d->binw_q8;
+        for (int k = 0; banded && k < 32 && n_v > 0; ++k) {
+            const double n = std::ldexp(0.75, k);  // of (2^(k-1), 2^k]
+            const double p_bin = poisson_tail(n * bin_area / area, d->n_min);
+            if (tu.sort_vblock < 0 ||
+                bands_faster(n * (double)n_v / n_bands, p_bin * n_bins / n_bands, n_bands,
+                             d->n_epochs, d->mode, d->n_min, (double)p->sort_blocks.size()))
+                p->band_sizes |= 1u << k;
+        }
         p->n_band_items = (int64_t)band_items.size() / 5;
     }
 
@@ -1136,13 +1196,7 @@ sas_status vote_impl(const sas_plan *p, const int32_t *x_q8, const int32_t *y_q8
             e = hipEventRecord(p->probe[0], s);
             if (e != hipSuccess) return hip_fail(e, "sas_vote: probe");
         }
-        // Band items read the catalog once, and in EPOCHS mode once more for every
-        // kBandMasks / ceil(E / 32) bins that hold N_min detections.  Also where
-        // every occupied bin does (up to 64 readings) they beat the sort: 512
-        // velocities and 1.8e5 detections, thresholds 1 / 8 / 23: 6.8 / 3.0 / 0.16 ms
-        // against 22.6 / 12.7 / 5.3 ms at 60 epochs, 12.4 / 4.5 / 0.34 against
-        // 26.2 / 18.8 / 6.3 ms at 256.
-        if (p->banded) {
+        if (p->band_sizes >> size_bit(n) & 1u) {
             BandArgs b{};
             b.n_v = p->n_v;
             b.items = p->n_band_items ? p->d_band_items : nullptr;
