@@ -416,9 +416,11 @@ sas_status sas_vote_weighted(const sas_plan *plan, const int32_t *x_q8, const in
  *   one GPU (concurrent streams or threads) race on the array: order them.
  *   Extraction, features and refinement read a vote's workspace and so need
  *   sas_vote, not this variant.
+ * A plan whose sas_vote_workspace_size(plan, n) exceeds the array is voted
+ * with wider window-index cells where that makes it fit (slower, the same list).
  * Errors (host side, nothing enqueued): those of sas_vote, and
- * SAS_E_WORKSPACE when sas_vote_workspace_size(plan, n) exceeds
- * SAS_STATIC_SCRATCH_BYTES (a plan with a smaller tuning.refine_cap may fit).
+ * SAS_E_WORKSPACE when it does not fit with cells four times as wide as high
+ * either (a plan with a smaller tuning.refine_cap may fit).
  */
 #define SAS_STATIC_SCRATCH_BYTES (64 * 1024 * 1024)
 sas_status sas_vote_static(const sas_plan *plan, const int32_t *x_q8, const int32_t *y_q8,

@@ -127,8 +127,8 @@ struct sas_plan {
     int32_t coarse_log2 = 0, hx = 0, hy = 0, stage_cap = 0, rows = 0, rows_log2 = 0;
     int32_t packed = 0;  // packed 16-bit votes
     int32_t halves = 0;  // 16-bit histogram counts, two histograms by tile
-    int32_t ncx = 1, ncy = 1;
-    int64_t n_cells = 0, n_items = 0, n_segments = 0, n_tiles = 0, refine_cap = 0;
+    int32_t ncy = 1;
+    int64_t n_items = 0, n_segments = 0, n_tiles = 0, refine_cap = 0;
     // items [0, n_items_kept) are the tiles that can hold a candidate when the
     // earliest epoch e_first holds a detection; the rest are voted otherwise
     int64_t n_items_kept = 0, n_tiles_kept = 0;
@@ -218,20 +218,27 @@ int64_t sorted_at_most(const sas_plan *p, int64_t n) {
 }
 
 struct WsLayout {
+    int32_t cell_log2_x, ncx;  // width of the window-index cells
+    int64_t n_cells;
     size_t count, offT, blocksum, cellid, rank, sxy, sidx, present, dt, refine_count, item_queue,
         refine;
     size_t keys, keys_alt, hist, hist_blocksum;  // sort path
     size_t total;
 };
 
-WsLayout ws_layout(const sas_plan *p, int64_t n) {
+// Layout with window-index cells 2^cell_log2_x wide (the plan's width or wider).
+WsLayout ws_layout(const sas_plan *p, int64_t n, int32_t cell_log2_x) {
     WsLayout L{};
     size_t o = 0;
-    const int64_t n_count = p->n_cells + 1;
+    const int64_t width = (int64_t)p->ext[1] - p->ext[0];
+    L.cell_log2_x = cell_log2_x;
+    L.ncx = (int32_t)((width + ((int64_t)1 << cell_log2_x) - 1) >> cell_log2_x);
+    L.n_cells = (int64_t)p->n_epochs * L.ncx * p->ncy;
+    const int64_t n_count = L.n_cells + 1;
     const int64_t nb = (n_count + kScanTile - 1) / kScanTile;
     const size_t nn = (size_t)std::max<int64_t>(n, 1);
     L.count = o; o = align_up(o + sizeof(int32_t) * n_count);
-    L.offT = o; o = align_up(o + sizeof(int32_t) * (size_t)p->n_epochs * (p->ncx + 1) * p->ncy);
+    L.offT = o; o = align_up(o + sizeof(int32_t) * (size_t)p->n_epochs * (L.ncx + 1) * p->ncy);
     L.blocksum = o; o = align_up(o + sizeof(int32_t) * nb);
     L.cellid = o; o = align_up(o + sizeof(int32_t) * nn);
     L.rank = o; o = align_up(o + sizeof(int32_t) * nn);
@@ -256,6 +263,8 @@ WsLayout ws_layout(const sas_plan *p, int64_t n) {
     L.total = o;
     return L;
 }
+
+WsLayout ws_layout(const sas_plan *p, int64_t n) { return ws_layout(p, n, p->cell_log2_x); }
 
 PrepBuffers prep_buffers(const WsLayout &L, char *w) {
     PrepBuffers pb;
@@ -282,9 +291,9 @@ DenseArgs dense_args(const sas_plan *p, const WsLayout &L, char *w, const PrepBu
     a.cat.offT = pb.offT;
     a.cat.dt = pb.dt;
     a.cat.n_epochs = p->n_epochs;
-    a.cat.ncx = p->ncx;
+    a.cat.ncx = L.ncx;
     a.cat.ncy = p->ncy;
-    a.cat.cell_log2_x = p->cell_log2_x;
+    a.cat.cell_log2_x = L.cell_log2_x;
     a.cat.cell_log2_y = p->cell_log2;
     a.cat.x0 = p->ext[0];
     a.cat.x1 = p->ext[1];
@@ -786,9 +795,7 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
     p->lds_bytes = lds + lds_static;
     p->cell_log2 = cl;
     p->cell_log2_x = clx;
-    p->ncx = (int32_t)ncx;
     p->ncy = (int32_t)ncy;
-    p->n_cells = n_cells;
 
     // Tiles of each segment: the projections x - v dt of the footprint for v
     // in the segment's box and dt in [0, span] lie inside the convex hull of
@@ -1148,13 +1155,13 @@ namespace {
 sas_status vote_impl(const sas_plan *p, const int32_t *x_q8, const int32_t *y_q8,
                      const uint8_t *epoch, const uint8_t *weight, int64_t n,
                      sas_candidate *cand_dev, int64_t cand_cap, sas_vote_result *res_dev,
-                     void *workspace, size_t ws_bytes, void *stream) {
+                     void *workspace, size_t ws_bytes, int32_t cell_log2_x, void *stream) {
     if (n < 0 || n >= ((int64_t)1 << 31)) return fail(SAS_E_INVALID, "sas_vote: n must be in [0, 2^31)");
     if (n > 0 && (!x_q8 || !y_q8 || !epoch)) return fail(SAS_E_INVALID, "sas_vote: null catalog array");
     if (!res_dev) return fail(SAS_E_INVALID, "sas_vote: null result pointer");
     if (cand_cap < 0 || (cand_cap > 0 && !cand_dev))
         return fail(SAS_E_INVALID, "sas_vote: bad candidate buffer");
-    const WsLayout L = ws_layout(p, n);
+    const WsLayout L = ws_layout(p, n, cell_log2_x);
     if (!workspace || ws_bytes < L.total)
         return fail(SAS_E_WORKSPACE, "sas_vote: workspace smaller than sas_vote_workspace_size()");
     if (((uintptr_t)workspace & 255) != 0)
@@ -1162,8 +1169,8 @@ sas_status vote_impl(const sas_plan *p, const int32_t *x_q8, const int32_t *y_q8
     hipStream_t s = (hipStream_t)stream;
     char *w = (char *)workspace;
     const PrepBuffers pb = prep_buffers(L, w);
-    hipError_t e = launch_prep(x_q8, y_q8, epoch, weight, n, p->d_t, p->n_epochs, p->ncx, p->ncy,
-                               p->cell_log2_x, p->cell_log2, p->ext, p->n_cells, pb, res_dev, s);
+    hipError_t e = launch_prep(x_q8, y_q8, epoch, weight, n, p->d_t, p->n_epochs, L.ncx, p->ncy,
+                               L.cell_log2_x, p->cell_log2, p->ext, L.n_cells, pb, res_dev, s);
     if (e != hipSuccess) return hip_fail(e, "sas_vote: preparation launch");
     if (n == 0 || p->n_v == 0) return SAS_OK;
 
@@ -1226,16 +1233,34 @@ sas_status vote_impl(const sas_plan *p, const int32_t *x_q8, const int32_t *y_q8
 
 }  // namespace
 
+namespace sas {
+
+int32_t index_width_within(const sas_plan *p, int64_t n, size_t bytes, size_t *need) {
+    int32_t c = p->cell_log2_x;
+    while ((*need = ws_layout(p, n, c).total) > bytes && c < p->cell_log2 + kIndexWiden) ++c;
+    return c;
+}
+
+sas_status vote_indicator(const sas_plan *p, const int32_t *x_q8, const int32_t *y_q8,
+                          const uint8_t *epoch, int64_t n, sas_candidate *cand_dev,
+                          int64_t cand_cap, sas_vote_result *res_dev, void *workspace,
+                          size_t ws_bytes, int32_t cell_log2_x, void *stream) {
+    if (is_weighted(p->mode))
+        return fail(SAS_E_INVALID, "sas_vote: the plan counts weights; use sas_vote_weighted");
+    return vote_impl(p, x_q8, y_q8, epoch, nullptr, n, cand_dev, cand_cap, res_dev, workspace,
+                     ws_bytes, cell_log2_x, stream);
+}
+
+}  // namespace sas
+
 extern "C" {
 
 sas_status sas_vote(const sas_plan *p, const int32_t *x_q8, const int32_t *y_q8,
                     const uint8_t *epoch, int64_t n, sas_candidate *cand_dev, int64_t cand_cap,
                     sas_vote_result *res_dev, void *workspace, size_t ws_bytes, void *stream) {
     if (!p) return fail(SAS_E_INVALID, "sas_vote: null plan");
-    if (is_weighted(p->mode))
-        return fail(SAS_E_INVALID, "sas_vote: the plan counts weights; use sas_vote_weighted");
-    return vote_impl(p, x_q8, y_q8, epoch, nullptr, n, cand_dev, cand_cap, res_dev, workspace,
-                     ws_bytes, stream);
+    return vote_indicator(p, x_q8, y_q8, epoch, n, cand_dev, cand_cap, res_dev, workspace,
+                          ws_bytes, p->cell_log2_x, stream);
 }
 
 sas_status sas_vote_weighted(const sas_plan *p, const int32_t *x_q8, const int32_t *y_q8,
@@ -1248,7 +1273,7 @@ sas_status sas_vote_weighted(const sas_plan *p, const int32_t *x_q8, const int32
                                    "sas_vote");
     if (n > 0 && !weight) return fail(SAS_E_INVALID, "sas_vote_weighted: null weight array");
     return vote_impl(p, x_q8, y_q8, epoch, weight, n, cand_dev, cand_cap, res_dev, workspace,
-                     ws_bytes, stream);
+                     ws_bytes, p->cell_log2_x, stream);
 }
 
 sas_status sas_peaks(const sas_candidate *cand_dev, const sas_vote_result *res_dev,
@@ -1520,8 +1545,8 @@ sas_status sas_vote_batch(const sas_batch *b, void *stream) {
     for (const sas_batch::Chip &ch : b->chips) {
         const sas_plan *p = ch.b.plan;
         char *w = b->ws + ch.ws_off;
-        e = launch_prep(ch.b.x_q8, ch.b.y_q8, ch.b.epoch, nullptr, ch.b.n, p->d_t, p->n_epochs, p->ncx,
-                        p->ncy, p->cell_log2_x, p->cell_log2, p->ext, p->n_cells,
+        e = launch_prep(ch.b.x_q8, ch.b.y_q8, ch.b.epoch, nullptr, ch.b.n, p->d_t, p->n_epochs,
+                        ch.L.ncx, p->ncy, ch.L.cell_log2_x, p->cell_log2, p->ext, ch.L.n_cells,
                         prep_buffers(ch.L, w),
                         ch.b.res_dev, s);
         if (e != hipSuccess) return hip_fail(e, "sas_vote_batch: preparation launch");

@@ -336,4 +336,16 @@ struct RefineArgs {
 };
 hipError_t launch_refine_clusters(const RefineArgs &a, hipStream_t stream);
 
+// Narrowest window-index cells (log2 of their width, from the plan's to four
+// times its height) with which a vote of n detections fits a workspace of
+// `bytes`, and the bytes that it needs then (more than `bytes`: with none).
+constexpr int32_t kIndexWiden = 2;
+int32_t index_width_within(const sas_plan *p, int64_t n, size_t bytes, size_t *need);
+
+// sas_vote with window-index cells of a given width.
+sas_status vote_indicator(const sas_plan *p, const int32_t *x_q8, const int32_t *y_q8,
+                          const uint8_t *epoch, int64_t n, sas_candidate *cand_dev,
+                          int64_t cand_cap, sas_vote_result *res_dev, void *workspace,
+                          size_t ws_bytes, int32_t cell_log2_x, void *stream);
+
 }  // namespace sas

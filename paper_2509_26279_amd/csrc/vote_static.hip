@@ -63,9 +63,10 @@ extern "C" sas_status sas_vote_static(const sas_plan *p, const int32_t *x_q8,
                                       sas_vote_result *res_dev, void *stream) {
     if (!p) return sfail(SAS_E_INVALID, "sas_vote_static: null plan");
     if (n < 0) return sfail(SAS_E_INVALID, "sas_vote_static: n must be >= 0");
+    // The plan's narrow index cells where they fit, else wider ones: the array
+    // holds what it held when the cells were as wide as high.
     size_t need = 0;
-    sas_status st = sas_vote_workspace_size(p, n, &need);
-    if (st != SAS_OK) return st;
+    const int32_t width = sas::index_width_within(p, n, kStaticScratchBytes, &need);
     if (need > kStaticScratchBytes)
         return sfail(SAS_E_WORKSPACE,
                          "sas_vote_static: this plan and catalog need " + std::to_string(need) +
@@ -79,6 +80,6 @@ extern "C" sas_status sas_vote_static(const sas_plan *p, const int32_t *x_q8,
         return sfail(SAS_E_UNSUPPORTED, "sas_vote_static: device ordinal above 63");
     void *ws = scratch_of_device(dev, &e);
     if (!ws) return shipfail(e, "sas_vote_static: looking up the scratch array");
-    return sas_vote(p, x_q8, y_q8, epoch, n, cand_dev, cand_cap, res_dev, ws,
-                    kStaticScratchBytes, stream);
+    return sas::vote_indicator(p, x_q8, y_q8, epoch, n, cand_dev, cand_cap, res_dev, ws,
+                               kStaticScratchBytes, width, stream);
 }
