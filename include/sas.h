@@ -167,8 +167,9 @@ typedef struct {
                                    instruction for 64 / G velocities */
     int32_t stage_cap;          /* detections staged in LDS at a time (larger windows are
                                    processed in chunks) */
-    int32_t cell_log2;          /* log2 of the window-index cell width in Q8 px (the cells grow
-                                   higher than wide when a window has too many rows of them) */
+    int32_t cell_log2;          /* log2 of the window-index cell width in Q8 px, wider when the
+                                   index would hold more than 2^21 cells; their height is
+                                   the plan's choice, at least as much (sort path: square) */
     int32_t sort_vblock;        /* sort path: velocities per block of the sort; > 0: always the
                                    sort; 0: chosen from n_det_hint, and bands in place of the
                                    sort where they are expected to be faster; < 0: bands for
@@ -245,7 +246,7 @@ typedef struct {
     int32_t path;
     int32_t tile_x, tile_y;
     int32_t vblock_x, vblock_y;
-    int32_t cell_log2;     /* log2 of the window-index cell height in Q8 px */
+    int32_t cell_log2;     /* log2 of the window-index cell width in Q8 px (as the tuning's) */
     int32_t coarse_log2;   /* histogram cells of 2^m x 2^m bins */
     int32_t mode_variant;  /* 0 epoch masks, 1 detection counts, 2 counts + refinement,
                               3 weight sums, 4 weight sums + refinement */
@@ -297,7 +298,7 @@ typedef struct {
  * sas_autotune_default_candidates: the built-in candidate list around the
  * planner's choice for desc (its tuning field is the base every candidate
  * starts from): the planner default, each lane-group count, window-index
- * cells one step finer and coarser, and five tile shapes per lane-group
+ * cells one step narrower and wider, and five tile shapes per lane-group
  * count.  *n_out receives the count; SAS_E_OVERFLOW when cap is smaller.
  * Creates (and destroys) a plan on the current device.
  */

@@ -688,11 +688,13 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
     // offsets of a quarter cell in the first of these, 13 MB a copy, no longer
     // fit the L2 caches), and no more than the one-workgroup preparation
     // takes where square cells stay below that.  The sort path reads whole
-    // rows and keeps square cells, as does a caller's own cell_log2 while the
-    // rows fit.
+    // rows and keeps square cells.  A caller's own cell_log2 is the width, with
+    // the same rule for the height, so that a plan's reported width asks for
+    // the plan again.
     constexpr int64_t kIndexCells = (int64_t)1 << 21;
-    int clx = d->path == SAS_PATH_SORT ? 30 : cl ? cl : std::max(kc - 1, 0);
-    if (!cl) cl = kc + 2;
+    const bool square_cells = d->path == SAS_PATH_SORT;
+    int clx = square_cells ? 30 : cl ? cl : std::max(kc - 1, 0);
+    if (!cl || !square_cells) cl = std::max(cl, kc + 2);
     while (ncells_of(cl, ex[0], ex[1]) > 32767 || ncells_of(cl, ex[2], ex[3]) > 32767 ||
            ((((int64_t)d->n_epochs + 7) / 8) << log2_ceil(rows_bound(cl, TY))) > kMaxWavePairs)
         ++cl;
@@ -1115,7 +1117,7 @@ sas_status sas_plan_get_info(const sas_plan *p, sas_plan_info *info) {
     info->vblock_y = p->vby;
     info->coarse_log2 = p->coarse_log2;
     info->mode_variant = p->dense_mode;
-    info->cell_log2 = p->cell_log2;
+    info->cell_log2 = p->cell_log2_x;
     info->n_v = p->n_v;
     info->groups = p->groups;
     info->hist_x = p->hx;

@@ -140,7 +140,7 @@ std::vector<sas_tuning> default_candidates(const sas_tuning &base, int32_t plann
         sas_tuning t = base;
         t.groups = g;
         out.push_back(t);
-        for (int step : {-1, 1}) {  // window-index cells one step finer or coarser
+        for (int step : {-1, 1}) {  // window-index cells one step narrower or wider
             sas_tuning c = t;
             c.cell_log2 = planner_cell_log2 + step;
             if (c.cell_log2 > 0) out.push_back(c);
