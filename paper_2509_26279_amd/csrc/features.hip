@@ -68,8 +68,9 @@ __device__ inline uint64_t slot_of(uint64_t key, int table_log2) {
 }
 
 __global__ void k_table_clear(uint64_t *__restrict__ table, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) table[i] = kNoNeighbourKey;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
+        table[i] = kNoNeighbourKey;
 }
 
 // Each candidate's key into the table; candidates that share a key keep the
@@ -429,9 +430,11 @@ __global__ void __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(5))) k_
 hipError_t launch_features(const FeatureArgs &a, hipStream_t stream) {
     if (a.n_cand <= 0) return hipSuccess;
     if (a.spacing > 0) {
+        // up to 2^32 slots, as many as a launch may hold threads: 65536 workgroups stride
         const int64_t slots = (int64_t)1 << a.table_log2;
-        hipLaunchKernelGGL(k_table_clear, dim3((unsigned)((slots + 255) / 256)), dim3(256), 0,
-                           stream, a.table, slots);
+        const int64_t clear_blocks = slots / 256 < 65536 ? slots / 256 : 65536;
+        hipLaunchKernelGGL(k_table_clear, dim3((unsigned)clear_blocks), dim3(256), 0, stream,
+                           a.table, slots);
         hipLaunchKernelGGL(k_table_insert, dim3((unsigned)((a.n_cand + 255) / 256)), dim3(256), 0,
                            stream, a);
     }

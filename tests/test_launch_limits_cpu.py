@@ -26,3 +26,25 @@ out = {"status": st, "n_v": len(v), "grown": grown, "launches": got}
     assert all(grid * block < 1 << 32 for _, grid, block in out["launches"])
     # no table of the bands: 80 bytes of host memory a velocity are the segments' and the sort's
     assert out["grown"] * 1024 < 160 * out["n_v"]
+
+
+def test_features_of_the_longest_lists(tmp_path):
+    # the neighbour table of more than 2^30 candidates has 2^32 slots
+    out = run(tmp_path, """
+V = np.zeros((4, 2), np.int32)
+p = sas.Plan(V, np.arange(8) * 4096, 1024, 3, (0, 1 << 14, 0, 1 << 14))
+b = buffer(4096)
+out = []
+for k in (1, 128, 129, 1 << 30, (1 << 30) + 1, (1 << 31) - 1):
+    size = ctypes.c_size_t()
+    assert lib.sas_features_scratch_size(ctypes.c_int64(k), ctypes.byref(size)) == 0
+    launches()
+    st = lib.sas_features(p.handle, b, p.workspace_size(100), 100, None, b,
+                          ctypes.c_int64(k), 1024, b, size.value, b, None)
+    out.append([k, st, launches()])
+""")
+    for k, status, got in out:
+        assert status == 0
+        names = [g[0] for g in got]
+        assert names == ["k_table_clear", "k_table_insert", "k_neighbours", "k_features"]
+        assert all(0 < grid * block < 1 << 32 for _, grid, block in got), k
