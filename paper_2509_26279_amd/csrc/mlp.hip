@@ -254,10 +254,11 @@ __global__ void __launch_bounds__(MT) k_mlp_rows(MlpBuffers b, const float *__re
         for (int c = 0; c < 2; ++c) {
             const int col = 32 * wave + 16 * c + r16;
             h1[c] = relu_store(mma(a, w.w1[c], zero4), w.b1[c], h1s, q4, col);
-            v4bf s = h1[c];
+            // no activation past the batch: its gradients are masked with it, also
+            // where a zero meets an infinite weight
 #pragma unroll
-            for (int i = 0; i < 4; ++i) s[i] = in[i] ? s[i] : zb;
-            *(v4bf *)(b.h1 + act_offset(t, NT, 2 * wave + c, lane)) = s;
+            for (int i = 0; i < 4; ++i) h1[c][i] = in[i] ? h1[c][i] : zb;
+            *(v4bf *)(b.h1 + act_offset(t, NT, 2 * wave + c, lane)) = h1[c];
         }
         __syncthreads();
         if (wave < kMlpIn / 16) {  // the inputs by column
@@ -276,10 +277,9 @@ __global__ void __launch_bounds__(MT) k_mlp_rows(MlpBuffers b, const float *__re
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             h2[c] = relu_store(acc[c], w.b2[c], h2s, q4, 32 * wave + 16 * c + r16);
-            v4bf s = h2[c];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) s[i] = in[i] ? s[i] : zb;
-            *(v4bf *)(b.h2 + act_offset(t, NT, 2 * wave + c, lane)) = s;
+            for (int i = 0; i < 4; ++i) h2[c][i] = in[i] ? h2[c][i] : zb;
+            *(v4bf *)(b.h2 + act_offset(t, NT, 2 * wave + c, lane)) = h2[c];
         }
         __syncthreads();
         v4f z = zero4;  // every wave: column 0 holds the logits, less b3
