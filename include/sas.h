@@ -609,7 +609,8 @@ sas_status sas_mlp_set_params(sas_mlp *mlp, const float *host, int64_t n);
  */
 sas_status sas_mlp_save(const sas_mlp *mlp, void *host, int64_t cap, int64_t *n_out);
 sas_status sas_mlp_load(sas_mlp *mlp, const void *host, int64_t n);
-/* Logits of n rows (any n, also above max_batch). */
+/* Logits of n rows (any n, also above max_batch).  logits_dev may overlap x_dev
+ * (then max_batch rows at a time, a row's logit written after its read). */
 sas_status sas_mlp_forward(const sas_mlp *mlp, const float *x_dev, int64_t n, float *logits_dev,
                            void *stream);
 /* Mean loss (device float) and gradient (device [20865] float) of one batch

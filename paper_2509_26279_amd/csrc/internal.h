@@ -289,6 +289,7 @@ struct MlpBuffers {
 };
 
 hipError_t mlp_logits(const MlpBuffers &b, const float *x, int64_t n, float *out, hipStream_t s);
+hipError_t mlp_copy(const float *from, int64_t n, float *to, hipStream_t s);
 hipError_t mlp_grad(const MlpBuffers &b, const float *x, const float *y, int64_t B, float pw,
                     float *loss, float *grad, hipStream_t s);
 // One AdamW step; c1, c2: the moments' bias corrections.

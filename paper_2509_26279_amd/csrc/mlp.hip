@@ -557,6 +557,11 @@ __global__ void k_refresh(MlpBuffers b) {
     if (i < kMlpParams) mlp_store_working(b.w, i, b.p[i]);
 }
 
+__global__ void k_mlp_copy(const float *__restrict__ from, int64_t n, float *__restrict__ to) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) to[i] = from[i];
+}
+
 inline unsigned nblk(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 
 constexpr int64_t kMaxRowBlocks = 2048;  // workgroups of a pass over rows (they stride)
@@ -582,6 +587,11 @@ hipError_t mlp_logits(const MlpBuffers &b, const float *x, int64_t n, float *out
                            dim3(MT), 0, s, b, x, n, out);
     else
         hipLaunchKernelGGL(k_mlp_forward<1>, dim3(nblk(n, 16)), dim3(MT), 0, s, b, x, n, out);
+    return hipGetLastError();
+}
+
+hipError_t mlp_copy(const float *from, int64_t n, float *to, hipStream_t s) {
+    hipLaunchKernelGGL(k_mlp_copy, dim3(nblk(n, 256)), dim3(256), 0, s, from, n, to);
     return hipGetLastError();
 }
 

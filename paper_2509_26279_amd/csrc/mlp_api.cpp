@@ -224,8 +224,21 @@ sas_status sas_mlp_forward(const sas_mlp *m, const float *x_dev, int64_t n, floa
     if (!m || n < 0 || (n > 0 && (!x_dev || !logits_dev)))
         return mfail(SAS_E_INVALID, "sas_mlp_forward: bad argument");
     if (n == 0) return SAS_OK;
-    // one pass over any number of rows: it keeps nothing outside registers and LDS
-    hipError_t e = mlp_logits(m->b, x_dev, n, logits_dev, (hipStream_t)stream);
+    // One pass over any number of rows: it keeps nothing outside registers and LDS.
+    // Logits that overlap the rows would overwrite what other workgroups have yet
+    // to read: those take the batch's own buffer, at most max_batch rows at a time.
+    const uintptr_t x0 = (uintptr_t)x_dev, z0 = (uintptr_t)logits_dev;
+    const bool apart = z0 + sizeof(float) * (size_t)n <= x0 ||
+                       x0 + sizeof(float) * kMlpIn * (size_t)n <= z0;
+    hipError_t e = hipSuccess;
+    for (int64_t r = 0; r < n && e == hipSuccess;) {
+        const int64_t k = apart ? n : std::min(m->max_batch, n - r);
+        e = mlp_logits(m->b, x_dev + r * kMlpIn, k, apart ? logits_dev : m->b.row_loss,
+                       (hipStream_t)stream);
+        if (e == hipSuccess && !apart)
+            e = mlp_copy(m->b.row_loss, k, logits_dev + r, (hipStream_t)stream);
+        r += k;
+    }
     if (e != hipSuccess) return mfail(SAS_E_DEVICE, std::string("sas_mlp_forward: ") + hipGetErrorString(e));
     return SAS_OK;
 }

@@ -69,3 +69,19 @@ def test_gradient_second_trip(gpu, B):
     for name, a, b in BLOCKS:
         assert rel_l2(g[a:b], rg[a:b]) < TOL, name
     net.close()
+
+
+@pytest.mark.parametrize("n,max_batch", [(1, 64), (1000, 64), (20000, 4096), (20000, 20000)])
+@pytest.mark.parametrize("at", [0, 1])
+def test_logits_over_their_rows(gpu, n, max_batch, at):
+    import torch
+    p, x, y, mu, sd = case(n, n)
+    net = _net(p, mu, sd, max_batch)
+    xt = torch.as_tensor(x).cuda()
+    ref = net.forward(xt).cpu().numpy()
+    over = xt.flatten().clone()
+    assert sas.load().sas_mlp_forward(net._m, over.data_ptr(), n, over.data_ptr() + 4 * at,
+                                      None) == sas.SAS_OK
+    torch.cuda.synchronize()
+    assert np.array_equal(over[at:at + n].cpu().numpy(), ref)
+    net.close()
