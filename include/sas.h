@@ -698,7 +698,9 @@ typedef struct {
  *   out_dev:     device [n_clusters] results.
  *   gathered_dev: device [n_clusters][gather_cap] or NULL: the final
  *                gathered set, catalog indices ascending (the first
- *                min(n_gathered, gather_cap) of them).
+ *                min(n_gathered, gather_cap) of them).  Where a fit gathered
+ *                more than SAS_REFINE_MAX_POINTS (SAS_REFINE_TOO_LARGE): the
+ *                set that was fitted, and -1 in the rest of the entries.
  *   subset_dev:  device [n_clusters][SAS_REFINE_MAX_POINTS] or NULL: the
  *                MCD subset of the last fit, ascending (n_points of them).
  * Asynchronous, allocates nothing.  An invalid cluster gets status

@@ -682,9 +682,10 @@ __global__ void __launch_bounds__(RT) k_refine_clusters(RefineArgs a) {
             }
         }
         if (last > 0 && a.gathered) {
-            const int m = min(n_g, min(kMaxPoints, a.gather_cap));
+            // (a gathered set too large to hold leaves the set just fitted, then -1)
+            const int m = min(n_g, min(kMaxPoints, a.gather_cap)), held = sh.n_set[out_set];
             for (int i = tid; i < m; i += RT)
-                a.gathered[cl * (int64_t)a.gather_cap + i] = sh.sets[out_set][i];
+                a.gathered[cl * (int64_t)a.gather_cap + i] = i < held ? sh.sets[out_set][i] : -1;
         }
         if (tid == 0) {
             sas_refined res{};

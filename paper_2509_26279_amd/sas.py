@@ -596,7 +596,8 @@ class Search:
         x, y, e): clusters is a list of catalog-index arrays, starts the
         uint32 [k, 4] draws of the FAST-MCD starts.  Returns (records as
         REFINED_DTYPE, gathered sets, MCD subsets) with the sets as sorted
-        catalog-index arrays."""
+        catalog-index arrays; of a fit that gathered more than
+        REFINE_MAX_POINTS, the set that was fitted."""
         import torch
         lens = np.array([len(c) for c in clusters], dtype=np.int64)
         first = np.zeros(len(clusters) + 1, dtype=np.int32)
@@ -623,6 +624,8 @@ class Search:
         g = _to_host(gath)
         gathered = [g[i, :min(int(r["n_gathered"]), gather_cap)].copy() if r["rounds"] > 0
                     else np.zeros(0, np.int32) for i, r in enumerate(recs)]
+        for i in np.flatnonzero(recs["n_gathered"] > REFINE_MAX_POINTS):  # padded with -1
+            gathered[i] = gathered[i][gathered[i] >= 0]
         subs = None
         if sub is not None:
             sm = _to_host(sub)
