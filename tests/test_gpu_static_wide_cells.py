@@ -18,7 +18,7 @@ def test_wider_cells(gpu):
 
     def plan(cap):
         return sas.Plan(v, wl.t_q16, wl.binw_q8, 7, wl.extent_q8,
-                        tuning={"n_det_hint": wl.n, "refine_cap": cap})
+                        tuning={"n_det_hint": wl.n, "refine_cap": cap, "cell_log2": 10})
     p = plan(1)
     index = p.workspace_size(wl.n)          # bytes but for the list
     p.close()
