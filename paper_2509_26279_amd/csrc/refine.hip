@@ -15,7 +15,7 @@
 // One workgroup per cluster (grid-stride over clusters).  The point set
 // (at most kMaxPoints) lives in LDS as t (h since t0), x, y (px) in FP64.
 // The starts of FAST-MCD are independent, and their C-steps are nearly all
-// the arithmetic.  A start takes one row of 16 lanes (4 starts a wave, 64 a
+// the arithmetic.  A start takes one row of 16 lanes (4 starts a wave, 32 a
 // workgroup; a whole wave above 128 points); a lane holds every 16th (64th)
 // point in registers.  The sums cross the row by data-parallel primitive
 // moves, the six or three divisions of a C-step are made by six or three
@@ -30,8 +30,9 @@
 // the slowest cluster, which follow one another.
 //   With one start a wave, ranks by comparing all pairs through LDS and
 // reductions by LDS permutes, the 160 clusters of a fast chip (500 starts)
-// took 8.0 ms, now 0.64 ms (1.5 ms before rounds that repeat were
-// recognised).
+// took 5.9 ms, now 0.63 ms; the more of them gather sets in a cycle until the
+// round limit, the longer (a chip of 8.0 ms: 1.5 ms before rounds that repeat
+// were recognised, 0.64 after).
 //
 // Rules shared with the reference definition: a point set is ordered by
 // catalog index; h = (n + 4) / 2; a start whose 4 points repeat, or whose
@@ -45,7 +46,13 @@
 namespace sas {
 namespace {
 
-constexpr int RT = 1024;            // threads per cluster workgroup
+// Threads per cluster workgroup.  512 leave a lane 256 registers; 1024 leave 128,
+// with 116 more in scratch: 1000 clusters of 16 points and 30 starts took 1.7 times
+// as long, 256 of 8 points 1.4 times what one start a wave had taken.
+// Clusters, points and starts, in us for 1024 / 512 / 256 threads: 1000, 16, 30
+// 712 / 417 / 416; 1000, 40, 500 1512 / 1367 / 1578; 160 of a fast chip, 500 starts
+// 644 / 633 / 934.
+constexpr int RT = 512;
 constexpr int RW = RT / 64;
 constexpr int kMaxPoints = 512;     // points of one set held in LDS
 constexpr int kMaskWords = kMaxPoints / 32;
