@@ -742,7 +742,11 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
     // window read little past its edges; along y each row is a run of its
     // own, and cells of four histogram cells (two: 110 k detections in 60
     // epochs, slow velocities 3.99 against 3.89 ms, 50 k in 40 2.96 against
-    // 2.85) grow until a wave's (epoch, row) pairs fit.  Cells 2, 1,
+    // 2.85) grow until a wave's (epoch, row) pairs fit.  Two where all of a
+    // wave's pairs still fit its lanes: nothing is saved with fewer rows then,
+    // and high ones read more past the window (300 k detections on 1024 x 1024
+    // px in 20 epochs, 8000 velocities 872 us against 927 with four; 20 k to
+    // 80 k in 8 or 20 epochs 0.97 to 1.01).  Cells 2, 1,
     // 1/2 and 1/4 histogram cells wide against cells as wide as high, vote
     // kernel: 300 k detections in 100 epochs at slow velocities 7.50, 7.27,
     // 7.14 and 7.36 ms against 7.78; 180 k in 60 epochs at fast ones 57.9,
@@ -761,14 +765,26 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
     constexpr int64_t kIndexCells = (int64_t)1 << 21, kVotesPerCell = 1000;
     const bool square_cells = d->path == SAS_PATH_SORT;
     int clx = square_cells ? 30 : cl ? cl : std::max(kc - 1, 0);
-    if (!cl || !square_cells) cl = std::max(cl, kc + 2);
+    const auto wave_pairs = [&](int c) {
+        return (((int64_t)d->n_epochs + 7) / 8) << log2_ceil(rows_bound(c, TY));
+    };
+    const auto square_of = [&](int c) {
+        return (int64_t)d->n_epochs * ncells_of(c, ex[0], ex[1]) * ncells_of(c, ex[2], ex[3]);
+    };
+    int high = kc + 2;
+    if (!square_cells && std::max(ncells_of(kc + 1, ex[0], ex[1]),
+                                  ncells_of(kc + 1, ex[2], ex[3])) <= 32767 &&
+        wave_pairs(kc + 1) <= 64 &&
+        (square_of(kc + 1) <= kSmallCells || square_of(kc + 2) > kSmallCells))
+        high = kc + 1;
+    if (!cl || !square_cells) cl = std::max(cl, high);
     while (ncells_of(cl, ex[0], ex[1]) > 32767 || ncells_of(cl, ex[2], ex[3]) > 32767 ||
-           ((((int64_t)d->n_epochs + 7) / 8) << log2_ceil(rows_bound(cl, TY))) > kMaxWavePairs)
+           wave_pairs(cl) > kMaxWavePairs)
         ++cl;
     if (cl > 30) return fail(SAS_E_UNSUPPORTED, "sas_plan_create: footprint too large");
     const int64_t ncy = ncells_of(cl, ex[2], ex[3]);
     {
-        const int64_t square = (int64_t)d->n_epochs * ncells_of(cl, ex[0], ex[1]) * ncy;
+        const int64_t square = square_of(cl);
         int64_t most = square <= kSmallCells ? kSmallCells : kIndexCells;
         if (square > kSmallCells && tu.n_det_hint > 0 && !tu.cell_log2)
             most = std::min(most, square + n_v * tu.n_det_hint / kVotesPerCell);
