@@ -10,6 +10,7 @@
 #include <cstring>
 #include <functional>
 #include <queue>
+#include <set>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -111,64 +112,96 @@ bool hull_x_range(const std::vector<Pt> &h, long double ylo, long double yhi, lo
     return any;
 }
 
-// Cuts rows of tiles (entries of 4: segment, tile row, first tile column, tiles)
-// into pieces of at most some number of tiles that share `slots` workgroups out
-// best: the time of the last to end when each takes the next piece, in tiles,
-// with kPiece for a piece's set-up and kQueue where there are more pieces than
-// slots.  kPiece 0.3, 0.7, 1.2 and 2 took 0.862, 0.856, 0.854 and 0.859 of the
-// time of uncut rows over 108 votes of 100 to 8000 velocities in the geometric
-// mean (without kQueue 0.7: 0.862); long rows and short votes gain up to 2/3.
-void cut_rows(std::vector<int32_t> &rows, int64_t n_tiles, int64_t slots, int32_t tile_x) {
-    constexpr double kPiece = 0.7, kQueue = 1.0;
-    const size_t n = rows.size() / 4;
-    const auto pieces = [&](size_t q, int64_t most) { return (rows[4 * q + 3] + most - 1) / most; };
-    // first tile of piece k of p of row q: pieces are alike within a tile
-    const auto from = [&](size_t q, int64_t k, int64_t p) { return k * rows[4 * q + 3] / p; };
-    const auto count = [&](int64_t most) {
-        int64_t c = 0;
-        for (size_t q = 0; q < n; ++q) c += pieces(q, most);
-        return c;
+// Time until the last of some pieces of rows of tiles has ended, in tiles, on
+// kCus compute units of two workgroups each, when a workgroup that ends makes
+// room for the next piece.  A piece takes its tiles and kPiece; the workgroups
+// of a unit run as fast as alone, or (shared) take turns.
+constexpr int64_t kCus = 256, kSlots = 2 * kCus;
+constexpr double kPiece = 0.7;
+double time_of_pieces(const std::vector<int32_t> &rows, bool shared) {
+    struct Cu {
+        double at = 0.0, done = 0.0;  // time, and what each resident has done
+        std::multiset<double> ends;   // `done` at which a resident ends
     };
-    std::vector<int64_t> tries{INT32_MAX};  // uncut
-    if ((int64_t)n <= slots) {              // the shortest that leave one a slot
+    using Event = std::pair<double, size_t>;
+    std::vector<Cu> cus(kCus);
+    std::priority_queue<Event, std::vector<Event>, std::greater<Event>> next;
+    const auto push = [&](size_t c) {
+        Cu &u = cus[c];
+        if (!u.ends.empty())
+            next.push({u.at + (*u.ends.begin() - u.done) * (shared ? (double)u.ends.size() : 1.0), c});
+    };
+    const size_t n = rows.size() / 4;
+    size_t k = 0;
+    for (; k < n && k < (size_t)kSlots; ++k) cus[k % kCus].ends.insert(kPiece + rows[4 * k + 3]);
+    for (size_t c = 0; c < cus.size(); ++c) push(c);
+    double last = 0.0;
+    while (!next.empty()) {
+        const size_t c = next.top().second;
+        Cu &u = cus[c];
+        last = u.at = next.top().first;
+        next.pop();
+        u.done = *u.ends.begin();
+        u.ends.erase(u.ends.begin());
+        if (k < n) u.ends.insert(u.done + kPiece + rows[4 * k++ + 3]);
+        push(c);
+    }
+    return last;
+}
+
+// Cuts rows of tiles (entries of 4: segment, tile row, first tile column, tiles)
+// so that they share the kSlots workgroups that run at once out.  Below a row a
+// slot the pieces are of the mean share, or (even) the shortest that leave one a
+// slot; with more rows they stay whole, or (even) become one to three a slot.
+// Workgroups that wait for memory run as if alone on their unit, and those that
+// fill it take turns: an even cut is taken if it is expected to gain a tenth in
+// sum and to lose in neither case, and fills three quarters of the slots.  Over
+// 259 votes of 100 to 3000 velocities, 8 to 256 epochs and 20 k to 300 k
+// detections the even cuts took 0.47 to 1.03 of the vote kernel's time, 0.969 in
+// the geometric mean (one to three a slot below a row a slot too: 0.966, up to
+// 1.14; by the times alone on a unit only, up to six a slot: 0.964, up to 1.24;
+// 354 whole rows in place of 560 pieces: 1.24).  Plans with three workgroups on
+// a unit lost up to 1.39 and keep to the mean share.
+void cut_rows(std::vector<int32_t> &rows, int64_t n_tiles, int32_t tile_x, bool even_too) {
+    const size_t n = rows.size() / 4;
+    const auto cut = [&](int64_t most, bool even) {
+        std::vector<int32_t> out;
+        for (size_t q = 0; q < 4 * n; q += 4) {
+            const int64_t len = rows[q + 3], p = (len + most - 1) / most;
+            for (int64_t k = 0; k < p; ++k) {
+                const int64_t a = even ? k * len / p : k * most;
+                const int64_t b = even ? (k + 1) * len / p : std::min(len, a + most);
+                out.insert(out.end(), {rows[q], rows[q + 1], (int32_t)(rows[q + 2] + a * tile_x),
+                                       (int32_t)(b - a)});
+            }
+        }
+        return out;
+    };
+    const auto share = [&](int64_t m) { return std::max<int64_t>(1, (n_tiles + m * kSlots - 1) / (m * kSlots)); };
+    const bool few = (int64_t)n < kSlots;
+    const std::vector<int32_t> base = few ? cut(share(1), false) : cut(INT32_MAX, false);
+    std::vector<int32_t> best = base;
+    const double alone = time_of_pieces(base, false), shared = time_of_pieces(base, true);
+    double least = 0.9;
+    const auto attempt = [&](int64_t most) {
+        std::vector<int32_t> r = cut(most, true);
+        if (r.size() == base.size() || (int64_t)r.size() < 3 * kSlots) return;
+        const double a = time_of_pieces(r, false) / alone, b = time_of_pieces(r, true) / shared;
+        if (std::max(a, b) > 1.02 || a * b >= least) return;
+        least = 0.999 * a * b;
+        best.swap(r);
+    };
+    if (even_too && few) {
         int64_t lo = 1, hi = n_tiles;
         while (lo < hi) {
             const int64_t mid = (lo + hi) / 2;
-            if (count(mid) <= slots) hi = mid; else lo = mid + 1;
+            if ((int64_t)cut(mid, true).size() / 4 <= kSlots) hi = mid; else lo = mid + 1;
         }
-        tries.push_back(lo);
+        attempt(lo);
+    } else if (even_too) {
+        for (int64_t m = 1; m <= 3; ++m) attempt(share(m));
     }
-    for (int64_t m = 1; m <= 6; ++m)        // about m a slot
-        tries.push_back(std::max<int64_t>(1, (n_tiles + m * slots - 1) / (m * slots)));
-    int64_t best_most = INT32_MAX;
-    double best = 0.0;
-    for (const int64_t most : tries) {
-        const double start = count(most) > slots ? kQueue : 0.0;
-        std::priority_queue<double, std::vector<double>, std::greater<double>> ends;
-        double last = 0.0;
-        for (size_t q = 0; q < n; ++q)
-            for (int64_t k = 0, p = pieces(q, most); k < p; ++k) {
-                double t = start;
-                if ((int64_t)ends.size() == slots) {
-                    t = ends.top();
-                    ends.pop();
-                }
-                t += kPiece + (double)(from(q, k + 1, p) - from(q, k, p));
-                ends.push(t);
-                last = std::max(last, t);
-            }
-        if (most == INT32_MAX || last < 0.999 * best) {
-            best = last;
-            best_most = most;
-        }
-    }
-    std::vector<int32_t> cut;
-    for (size_t q = 0; q < n; ++q)
-        for (int64_t k = 0, p = pieces(q, best_most); k < p; ++k)
-            cut.insert(cut.end(), {rows[4 * q], rows[4 * q + 1],
-                                   (int32_t)(rows[4 * q + 2] + from(q, k, p) * tile_x),
-                                   (int32_t)(from(q, k + 1, p) - from(q, k, p))});
-    rows.swap(cut);
+    rows.swap(best);
 }
 
 }  // namespace
@@ -1004,12 +1037,11 @@ sas_status sas_plan_create(const sas_plan_desc *d, sas_plan **plan_out) {
     // Where the kept rows do not share the workgroup slots out evenly, they are
     // cut, up to two rows a slot (a row's tiles follow one another on one
     // workgroup: the 121 tiles of the tiny workload took 33.6 us as 33 rows, 14.3
-    // us one by one; 2000 velocities at 60 epochs 341 us as 708 rows of 11 tiles,
-    // 279 as 1414).  With more rows than that whole rows are as fast or faster.
-    constexpr int64_t kSlots = 512;  // two workgroups on each of 256 CUs
-    const int64_t slots = three ? kSlots / 2 * 3 : kSlots;
-    if ((int64_t)items.size() / 4 < 2 * slots && n_tiles_kept > (int64_t)items.size() / 4)
-        cut_rows(items, n_tiles_kept, slots, TX);
+    // us one by one; 2000 velocities at 60 epochs and 80 k detections 207 us as
+    // 684 rows of 10 tiles, 169 as 1368; 1000 at 32 epochs 111 us as 1.2 pieces a
+    // slot, 77 as 504).  With more rows than that they are left whole.
+    const int64_t n_rows = (int64_t)items.size() / 4;
+    if (n_rows < 2 * kSlots && n_tiles_kept > n_rows) cut_rows(items, n_tiles_kept, TX, !three);
     // Work order: segments of one velocity-block row share their y shifts,
     // so (block row, band of tile rows, segment, tile row) keeps the windows
     // of neighbouring items in one band of the catalog; the kernel gives each
