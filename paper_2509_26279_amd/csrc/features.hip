@@ -20,10 +20,11 @@
 // (1.79 ms before, at 5 waves a SIMD; 0.60 ms at the compiler's 3, 0.55 and
 // 0.60 ms at 6 and 8, which spill), k_neighbours 0.17 ms with 0.02 ms for the
 // table, in place of a sort of the keys (0.24 ms) and binary searches.
-// Wave reductions then give the 32 features:
+// The features, all by k_features but f9 and f10, which k_neighbours writes:
 //   f0 c/E  f1 n/E  f2 min d/D  f3 (max d - min d)/D  f4 longest epoch run/E
-//   f5 vx/vmax  f6 vy/vmax  f7 |v|/vmax  f8 sum snr/E  f9 max snr - 3
-//   f10 min snr - 3  f11 mean snr - 3  f12, f13 mean r  f14, f15 std r
+//   f5 vx/vmax  f6 vy/vmax  f7 |v|/vmax  f8 sum snr/E
+//   f9 neighbouring candidates/80  f10 largest count among them/own count
+//   f11 mean snr - 3  f12, f13 mean r  f14, f15 std r
 //   f16, f17 least-squares slope of r against tau (0 if all d equal)
 //   f18..f25 per-slice mean r_x, r_y  f26..f29 slice fractions
 //   f30 (n - c)/n  f31 RMS of r about the least-squares lines (x and y)

@@ -1047,9 +1047,10 @@ __global__ void __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(kWavesPe
 // LDS and adds them to the bins when the epoch is done).
 // A chain of loads bounds it (entry, velocity, offsets, detections): the next
 // entry and its velocity are loaded ahead, d_e stays in registers, two index
-// rows are read as one run, and only the bins of the cell are cleared (300 k
-// detections in 100 epochs: 365 -> 334 us; weighted, 180 k in 60: 199 us, as
-// before).  What is left is one cache line a lane for each offset read.
+// rows are read as one run, and only the bins of the cell are cleared.  With
+// that and narrow index cells two chips of 300 k detections in 100 epochs took
+// 331 and 415 us (411 and 494 before); weighted, 180 k in 60 epochs, 199 us, as
+// before.  What is left is one cache line a lane for each offset read.
 constexpr int kRefineBins = 64;  // up to 8 x 8 bins per cell
 enum RefineMode : int { kRefineCount = 0, kRefineWeightDet = 1, kRefineWeightEpochs = 2 };
 
