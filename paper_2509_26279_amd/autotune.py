@@ -10,6 +10,8 @@ epoch, detection and velocity counts by powers of two, mode) in a text file.
     best = autotune.tune(v, t_q16, binw_q8, n_min, extent_q8, x, y, e)
 
 ``CACHE`` is the committed cache of the benchmarked workloads' shape classes.
+Its classes carry no values: every shape is the planner's own choice, and
+nothing in it is tuned.
 """
 from __future__ import annotations
 
