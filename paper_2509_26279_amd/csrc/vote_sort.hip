@@ -220,7 +220,7 @@ template <bool EVERY>
 __global__ void __launch_bounds__(BT) k_band_vote(SortArgs a, BandArgs b) {
     __shared__ uint32_t hist[kBandBins];
     __shared__ uint32_t mask[kBandMasks];
-    __shared__ int32_t n_hot, n_out;
+    __shared__ int32_t n_hot, n_out, n_put;
     __shared__ unsigned long long out_base;
     // what only candidates need: over the loop in LDS, not in scalar registers
     // that it has none left of
@@ -257,7 +257,7 @@ __global__ void __launch_bounds__(BT) k_band_vote(SortArgs a, BandArgs b) {
         }
         const int n_bins = nbx * rows;
         for (int i = tid; i < n_bins; i += BT) hist[i] = 0;
-        if (tid == 0) n_hot = n_out = 0;
+        if (tid == 0) n_hot = n_out = n_put = 0;
         __syncthreads();
         // f(word of the histogram, epoch) for every detection that projects into the
         // band: a wave an epoch, or the workgroup when there are few epochs
@@ -294,37 +294,34 @@ __global__ void __launch_bounds__(BT) k_band_vote(SortArgs a, BandArgs b) {
         each([&](int i, int) __attribute__((always_inline)) { atomicAdd(&hist[i], 1u); });
         __syncthreads();
         const uint32_t nmin = (uint32_t)a.n_min;
-        // the bins whose count reaches nmin, by the workgroup: one global addition for
-        // all of them (one a wave and 64 bins took 14 of the 14 ms of 512 velocities
-        // and 4000 detections at a threshold of 1)
-        const auto report = [&](const auto &count_of) __attribute__((always_inline)) {
-            int32_t mine = 0;
-            for (int i = tid; i < n_bins; i += BT) mine += count_of(i) >= nmin ? 1 : 0;
-            const int32_t at = mine ? atomicAdd(&n_out, mine) : 0;
+        // the bins whose count reaches nmin, `mine` of them found by this thread: one
+        // global addition a workgroup (one a wave and 64 bins took 14 of the 14 ms of
+        // 512 velocities and 4000 detections at a threshold of 1)
+        const auto report = [&](int32_t mine, const auto &count_of) __attribute__((always_inline)) {
+            if (mine) atomicAdd(&n_out, mine);
             __syncthreads();
-            const int32_t total = n_out;
-            if (total == 0) return;  // block uniform
+            if (n_out == 0) return;  // block uniform
             if (tid == 0)
                 out_base = atomicAdd((unsigned long long *)&out.res->n_cand,
-                                     (unsigned long long)total);
+                                     (unsigned long long)n_out);
             __syncthreads();
-            int64_t idx = (int64_t)out_base + at;
-            for (int i = tid; mine && i < n_bins; i += BT) {
+            for (int i = tid; i < n_bins; i += BT) {
                 const uint32_t cnt = count_of(i), sat = out.sat;
                 if (cnt < nmin) continue;
-                if (idx < out.cand_cap) {
-                    uint4 rec;
-                    rec.x = (uint32_t)out.v_idx[v];
-                    rec.y = (uint32_t)(bx0 + i % nbx);
-                    rec.z = (uint32_t)(by0 + i / nbx);
-                    rec.w = (cnt > sat ? sat : cnt) | ((cnt > sat ? 1u : 0u) << 16);
-                    *(uint4 *)(out.cand + idx) = rec;
-                }
-                ++idx;
+                const int64_t idx = (int64_t)out_base + atomicAdd(&n_put, 1);
+                if (idx >= out.cand_cap) continue;
+                uint4 rec;
+                rec.x = (uint32_t)out.v_idx[v];
+                rec.y = (uint32_t)(bx0 + i % nbx);
+                rec.z = (uint32_t)(by0 + i / nbx);
+                rec.w = (cnt > sat ? sat : cnt) | ((cnt > sat ? 1u : 0u) << 16);
+                *(uint4 *)(out.cand + idx) = rec;
             }
         };
+        int32_t mine = 0;
         if (!a.mode_epochs) {
-            report([&](int i) __attribute__((always_inline)) { return hist[i]; });
+            for (int i = tid; i < n_bins; i += BT) mine += hist[i] >= nmin ? 1 : 0;
+            report(mine, [&](int i) __attribute__((always_inline)) { return hist[i]; });
             if (EVERY) __syncthreads();  // the counts are read before they are cleared
             continue;
         }
@@ -337,7 +334,7 @@ __global__ void __launch_bounds__(BT) k_band_vote(SortArgs a, BandArgs b) {
         const int hot = n_hot;
         for (int s0 = 0; s0 < hot; s0 += held) {  // block uniform
             for (int i = tid; i < kBandMasks; i += BT) mask[i] = 0;
-            if (tid == 0) n_out = 0;
+            if (tid == 0) n_out = n_put = 0;
             __syncthreads();
             each([&](int i, int e) __attribute__((always_inline)) {
                 const uint32_t s = (hist[i] & ~kHot) - (uint32_t)s0;
@@ -345,12 +342,18 @@ __global__ void __launch_bounds__(BT) k_band_vote(SortArgs a, BandArgs b) {
                     atomicOr(&mask[s * W + (e >> 5)], 1u << (e & 31));
             });
             __syncthreads();
-            report([&](int i) __attribute__((always_inline)) {
-                const uint32_t h = hist[i], s = (h & ~kHot) - (uint32_t)s0;
+            // the masks are counted first, in their first words: few bins are hot, and
+            // most bands report none of them
+            mine = 0;
+            for (int s = tid; s < min(held, hot - s0); s += BT) {
                 uint32_t n = 0;
-                if (h & kHot && s < (uint32_t)held)
-                    for (int w = 0; w < W; ++w) n += __popc(mask[s * W + w]);
-                return n;
+                for (int w = 0; w < W; ++w) n += __popc(mask[s * W + w]);
+                mask[s * W] = n;
+                mine += n >= nmin ? 1 : 0;
+            }
+            report(mine, [&](int i) __attribute__((always_inline)) {
+                const uint32_t h = hist[i], s = (h & ~kHot) - (uint32_t)s0;
+                return h & kHot && s < (uint32_t)held ? mask[s * W] : 0u;
             });
             __syncthreads();
         }
