@@ -19,7 +19,7 @@
 // for the bins whose detections reach N_min.  A vote then costs about 9 bytes of
 // L2 reads and one LDS atomic in place of 80 to 104 bytes of HBM traffic: 512 of
 // the slowest velocities of the fast grid and 180 k detections, of 4.5 bands
-// each, take 5.15 ms by the sort and 0.21 ms with the preparation (0.13 ms
+// each, take 5.15 ms by the sort and 0.21 ms with the preparation (0.12 ms
 // k_band_vote, 7e11 votes/s).  A band costs its clearing, its dispatch and a walk
 // over the epochs however few detections it holds: 1000 detections over 20000
 // velocities of 26 bands take 9.5 ms, and 3.4 by the sort.
